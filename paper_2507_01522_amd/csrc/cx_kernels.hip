@@ -60,28 +60,12 @@ __device__ __forceinline__ int arrivals_lds(const __attribute__((address_space(3
 }
 
 // Stay length of an arriving car: 1 + #{thresholds below w}, bisecting the
-// table in LDS (staged by the block) or in device memory.
-__device__ __forceinline__ int stay_len(const uint32_t *tab, bool in_lds, int log2n, uint32_t w) {
+// table in LDS (staged by the block).
+__device__ __forceinline__ int stay_len(const __attribute__((address_space(3))) uint32_t *t, int log2n, uint32_t w) {
   int pos = 0;
-  if (in_lds) {
-    const __attribute__((address_space(3))) uint32_t *t = (const __attribute__((address_space(3))) uint32_t *)tab;
-    for (int s = 1 << (log2n - 1); s >= 1; s >>= 1)
-      if (t[pos + s - 1] < w) pos += s;
-  } else {
-    for (int s = 1 << (log2n - 1); s >= 1; s >>= 1)
-      if (gld(tab, pos + s - 1) < w) pos += s;
-  }
+  for (int s = 1 << (log2n - 1); s >= 1; s >>= 1)
+    if (t[pos + s - 1] < w) pos += s;
   return 1 + pos;
-}
-
-// A pointer the compiler may not know to be wave-uniform, held in scalar
-// registers (so loads through it can be scalar loads).
-template <class T>
-__device__ __forceinline__ const T *uniform_ptr(const T *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const T *>(((uint64_t)hi << 32) | lo);
 }
 
 // Exchange with the lane whose index differs in bit K (K = 0..5), for use in
@@ -214,8 +198,10 @@ __device__ __forceinline__ void st_at(T *base, uint32_t byte_off, T v) {
   *(gT *)((gchar *)(char *)base + byte_off) = v;
 }
 template <class T>
-__device__ __forceinline__ T ld_at(const T *base, uint32_t byte_off) {
-  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte_off);
+__device__ __forceinline__ T gl_at(const T *base, uint32_t byte_off) {
+  typedef const __attribute__((address_space(1))) T gT;
+  typedef const __attribute__((address_space(1))) char gchar;
+  return *(gT *)((gchar *)(const char *)base + byte_off);
 }
 
 // Observation records staged in LDS (SIMPLE classes).  Per step
@@ -228,6 +214,8 @@ __device__ __forceinline__ T ld_at(const T *base, uint32_t byte_off) {
 typedef __attribute__((address_space(3))) float lds_float;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
+typedef __attribute__((address_space(3))) f32x4u lds_f32x4u;
 
 // Write n staged floats to dst (4-byte aligned).  The stage holds them from
 // float pad = (dst / 4) mod 4 on, so that LDS and HBM agree on 16-byte chunks:
@@ -267,6 +255,7 @@ __device__ __forceinline__ void flush_stage(const lds_float *sb, float *dst, int
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
 // The fused policy rollout: after every step the block's staged observations
 // (E = 32 envs, row stride obs_dim floats) go through the MLP on the matrix
@@ -410,22 +399,28 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
   __syncthreads();
 }
 
-// exo_tp / exo_pr: the block's LDS copies of the first four arrival thresholds
-// and the base price of every step of the day (NULL: read device memory).
+// sg: the segment's descriptor; seg_args: take the horizon, clock, modes and
+// record pointers from it (serving) instead of from the launch arguments.
+// tdw: the block's LDS copy of the stay thresholds; exo_tp / exo_pr: its LDS
+// copies of the first four arrival thresholds and the base price of every step
+// of the day (NULL: read device memory).
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, bool POL = false>
-__device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int group, const uint32_t *tdw,
-                                          bool tdw_lds, const lds_u32x4 *exo_tp, const lds_float *exo_pr,
-                                          lds_float *stage, int stage_floats, int g_blk0, int n_run,
+__device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, int group, const lds_u32 *tdw,
+                                          const lds_u32x4 *exo_tp, const lds_float *exo_pr, lds_float *stage,
+                                          int stage_floats, int g_blk0, int n_run,
                                           const LaunchArgs::Pol *pol = nullptr, lds_char *lds = nullptr) {
   constexpr int SPW = 64 / L;
   constexpr int LOGL = (L == 4) ? 2 : (L == 8) ? 3 : (L == 16) ? 4 : (L == 32) ? 5 : 6;
   constexpr bool NOPAD = SIMPLE;  // every slot holds a port: slot s = port s
-  const ClassDev C = *sg.cls;  // by value: scalar loads once, kept in SGPRs
+  CX_KONST SegDev &sg = *sgp;
+  CX_KONST ClassDev *const cls = konst((const ClassDev *)sg.cls);
+  CX_KONST ClassDev &C = *cls;
   const int lane = __lane_id();
   const int l = lane & (L - 1);
   const int sbase = lane & ~(L - 1);
   const int env = group * SPW + (lane >> LOGL);     // env index inside the segment
-  const bool active = env < sg.n_envs;
+  const int n_envs = (int)sg.n_envs;
+  const bool active = env < n_envs;
   const int S = NOPAD ? L * P : C.S;
   const int D = C.D;
   const int N = NOPAD ? L * P : C.n_ports;
@@ -481,41 +476,61 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
 #pragma unroll
   for (int j = 0; j < P; ++j) {
     const int64_t i = sofs + j * L + l;
-    q[j] = active ? sg.q[i] : 0.0;
+    q[j] = active ? gld(sg.q, i) : 0.0;
     qf[j] = (float)q[j];
-    u[j] = active ? sg.u[i] : 0.f;
-    cap[j] = active ? sg.cap[i] : 0.f;
-    plast[j] = active ? sg.p_last[i] : 0.f;
-    dw[j] = active ? (int)sg.dwell[i] : 0;
-    cs[j] = (users && active) ? (int)sg.utype[i] : 0;
-    rb[j] = models ? (active ? sg.rbar[i] : 0.f) : pmax[j];
+    u[j] = active ? gld(sg.u, i) : 0.f;
+    cap[j] = active ? gld(sg.cap, i) : 0.f;
+    plast[j] = active ? gld(sg.p_last, i) : 0.f;
+    dw[j] = active ? (int)gld(sg.dwell, i) : 0;
+    cs[j] = (users && active) ? (int)gld(sg.utype, i) : 0;
+    rb[j] = models ? (active ? gld(sg.rbar, i) : 0.f) : pmax[j];
     dc[j] = models ? gld(C.slot_dc, j * L + l) : 0;
     icap[j] = cap[j] > 0.f ? frcp(cap[j]) : 0.f;
   }
+  // The state is in registers before the first step: a load still pending when
+  // the loop is entered would be waited for in every step, and with it the
+  // records in flight.
+#pragma unroll
+  for (int j = 0; j < P; ++j) asm volatile("" ::"v"(u[j]), "v"(plast[j]), "v"(dw[j]), "v"(cs[j]), "v"(rb[j]), "v"(dc[j]));
+  // the constants of every step, in scalar registers (the others are read where
+  // they are used)
+  const float dt = C.dt, inv_dt = C.inv_dt, inv_1mtau = C.inv_1mtau, inv_n_levels = C.inv_n_levels;
+  const float p_sell = C.p_sell, p_sell_grid = C.p_sell_grid, fixed_cost = C.fixed_cost, alpha_dec = C.alpha_dec;
+  const float inv_steps_ep = C.inv_steps_ep, inv_eta_u = C.inv_eta_uniform, alpha_sat = C.alpha_sat;
+  const f32x4 *const glob = reinterpret_cast<const f32x4 *>(C.glob);
   // a slot is occupied while its car's stay runs, or while a charge-sensitive
   // user waits to be charged
 #define CX_OCCUPIED(j) (EXT ? (dw[j] > 0 || cs[j] != 0) : dw[j] > 0)
-  double ret = active ? sg.ret[env] : 0.0;
+  double ret = active ? gld(sg.ret, env) : 0.0;
   // station battery (EXT): SoC in FP64 and last power, alike in every lane of the station
   double bsoc = 0.0;
   float bpw = 0.f;
   if constexpr (EXT) {
     if (batt && active) {
-      bsoc = sg.bsoc[env];
-      bpw = sg.bp[env];
+      bsoc = gld(sg.bsoc, env);
+      bpw = gld(sg.bp, env);
     }
   }
-  uint32_t bkp[2] = {0u, 0u};  // EXT: the battery's action bytes of the current group of 8 steps
+  uint32_t bkp = 0u, bkq = 0u;  // EXT: the battery's action bytes of the current group of 8 steps
+  // the levels of a SIMPLE class by block size (as a copy in scalar registers)
+  constexpr int kBlk = LOGL + (P == 1 ? 0 : P == 2 ? 1 : 2);
+  [[maybe_unused]] float blk_cap[kBlk + 1];
+  [[maybe_unused]] const uint32_t blk_mask = SIMPLE ? C.blk_mask : 0u;
+  if constexpr (SIMPLE) {
+#pragma unroll
+    for (int k = 0; k < kBlk; ++k) blk_cap[k] = C.blk_cap[k];
+  }
   // limit of the root (the whole station)
   const float c_root = D == 1 ? lcap[0][0] : D == 2 ? lcap[1][0] : D == 3 ? lcap[2][0] : lcap[3][0];
 
-  const uint32_t k0 = (uint32_t)sg.seed, k1 = (uint32_t)(sg.seed >> 32);
+  const uint64_t seed = sg.seed;
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   const uint32_t env_id = (uint32_t)(sg.env0 + env);
   // the day clock is the same in every lane: kept in scalar registers, the
   // end-of-day reset is a branch, not selects in every step
-  const int steps_ep = __builtin_amdgcn_readfirstlane(C.steps_ep);
+  const int steps_ep = C.steps_ep;
   const int n_levels = C.n_levels;
-  int t_day = __builtin_amdgcn_readfirstlane(dy.t_day0);
+  int t_day = uni(dy.t_day0);
   uint32_t g = dy.g0;
   int dday = 0;  // EXT: price day of the current episode (drawn at its first step)
   if constexpr (EXT) {
@@ -529,10 +544,10 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
   int bdw1 = 1;
   float bcp1 = 0.f, bs01 = 0.f, btg1 = 0.f;
   // RANDOM: each slot's action bytes of the current group of 8 steps, one per
-  // byte (steps 0-3 of the group in kp[0], 4-7 in kp[1])
-  uint32_t kp[P][2];
+  // byte (steps 0-3 of the group in kp, 4-7 in kq)
+  uint32_t kp[P], kq[P];
 #pragma unroll
-  for (int j = 0; j < P; ++j) kp[j][0] = kp[j][1] = 0u;
+  for (int j = 0; j < P; ++j) kp[j] = kq[j] = 0u;
   const uint64_t smask = (L == 64) ? ~0ull : (((1ull << (L & 63)) - 1ull) << sbase);
   const uint64_t below_mask = (1ull << lane) - 1ull;
 
@@ -551,15 +566,23 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
   const int64_t obs_step = w_obs ? dy.obs_stride : 0;
   const int64_t act_step = (w_act || ai_t) ? dy.act_stride : 0;
   const int64_t env_step = (rw_t || dn_t) ? dy.env_stride : 0;
-  // rewards and done flags share their step: each is written under its own
-  // flag (with one of them NULL, its advanced pointer is no address)
-  const bool w_rew = rw_t != nullptr, w_done = dn_t != nullptr;
+  // What the steps branch on, as bits of one scalar register that is read
+  // afresh every step (a bit test and a scalar branch each).  Rewards and done
+  // flags share their step: each is written under its own flag (with one of
+  // them NULL, its advanced pointer is no address).
+  enum : uint32_t { kWObs = 1, kWAct = 2, kWRew = 4, kWDone = 8, kActQuads = 16, kSat = 32, kRandom = 64, kMax = 128 };
+  const uint32_t flags0 =
+      (uint32_t)uni((w_obs ? kWObs : 0) | (w_act ? kWAct : 0) | (rw_t ? kWRew : 0) | (dn_t ? kWDone : 0) |
+                    // every step's action row is 4-byte aligned
+                    (((reinterpret_cast<uintptr_t>(ab_t) | (uint64_t)act_step) & 3u) == 0 ? kActQuads : 0) |
+                    (alpha_sat != 0.0f ? kSat : 0) | (dy.mode == CX_ACT_RANDOM ? kRandom : 0) |
+                    (dy.mode == CX_ACT_MAX ? kMax : 0));
   // the block's LDS observation stage (staging packings, whenever observations
   // are written): the block's first env, the floats the block writes per step
   // and this lane's env in the stage
   const int env_blk0 = g_blk0 * SPW;
-  const int64_t blk_envs = sg.n_envs - env_blk0 < (int64_t)n_run * SPW ? sg.n_envs - env_blk0 : (int64_t)n_run * SPW;
-  const int n_blk = (int)blk_envs * obs_dim;
+  const int blk_envs = min(n_envs - env_blk0, n_run * SPW);
+  const int n_blk = blk_envs * obs_dim;
   const uint32_t stage_bo = (uint32_t)(env - env_blk0) * (uint32_t)obs_dim * 4u;
   // the fused policy: every wave of the block takes part (waves past the last
   // env too, their lanes inactive); the first step's levels come from the
@@ -573,13 +596,19 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
     const float *src = pol->obs0 + sg.obs_off + (int64_t)env_blk0 * obs_dim;
     for (int i = wv * 64 + lane; i < n_blk; i += kPolRolloutWaves * 64) stage[i] = gld(src, i);
     __syncthreads();
-    policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, (int)blk_envs, wv, env_id0, g, k0, k1, true);
+    policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true);
   }
 
-  for (int t = 0; t < dy.T; ++t, ++g) {
+  [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
+  [[maybe_unused]] int kb_in = 0;
+  const int T = uni(dy.T);
+  for (int t = 0; t < T; ++t, ++g) {
+    uint32_t flags = flags0;
+    asm volatile("" : "+s"(flags));
     // ---- exogenous draws for the next L steps, lane l -> step t + l: the
     // arrival count, the price noise and the first arriving car's profile
     if ((t & (L - 1)) == 0) {
+      CX_KONST ClassDev &C = *reload(cls);  // (constants of the draws: not held across the steps)
       int td = t_day + l;
       while (td >= steps_ep) td -= steps_ep;
       const uint32_t gl = g + (uint32_t)l;
@@ -616,7 +645,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       }
       bs0 = C.soc_lo + C.soc_span * u24(b.y);
       btg = C.tgt_lo + C.tgt_span * u24(b.z);
-      bdw = stay_len(tdw, tdw_lds, C.dwell_log2, b.w);
+      bdw = stay_len(tdw, C.dwell_log2, b.w);
       if constexpr (EXT) {
         if (users) bus = philox(env_id, gl, 0u, kDomUser, k0, k1).x <= C.cs_thresh ? 1 : 0;
       }
@@ -626,19 +655,17 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
           bcp1 = C.cap_lo + C.cap_span * u24(b1.x);
           bs01 = C.soc_lo + C.soc_span * u24(b1.y);
           btg1 = C.tgt_lo + C.tgt_span * u24(b1.z);
-          bdw1 = stay_len(tdw, tdw_lds, C.dwell_log2, b1.w);
+          bdw1 = stay_len(tdw, C.dwell_log2, b1.w);
         }
       }
     }
     const int tb = t & (L - 1);
     const int M = bcast<L>(bM, tb);
     const float pbuy = bcastf<L>(bpb, tb);
-    // the observation's time features of the step after this one (scalar loads,
-    // issued early; they do not wait for the records in flight)
-    const int t_obs = __builtin_amdgcn_readfirstlane(t_day + 1 == steps_ep ? 0 : t_day + 1);
-    const float *glob_u = uniform_ptr(C.glob);
-    const float gl_sin = sld(glob_u, 4 * t_obs), gl_cos = sld(glob_u, 4 * t_obs + 1),
-                gl_price = sld(glob_u, 4 * t_obs + 2);
+    // the observation's time features of the step after this one (a scalar
+    // load, issued early; it does not wait for the records in flight)
+    const int t_obs = t_day + 1 == steps_ep ? 0 : t_day + 1;
+    const f32x4 gl = sld(glob, t_obs);
 
     // ---- actions: action bytes k (level + n_neg)
     int k[P];
@@ -647,7 +674,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       const lds_u8 *lv = reinterpret_cast<const lds_u8 *>(lds + pol->act_off) + (env - env_blk0) * N;
 #pragma unroll
       for (int j = 0; j < P; ++j) k[j] = active ? (int)lv[port[j]] : 0;
-    } else if (dy.mode == CX_ACT_RANDOM) {
+    } else if (flags & kRandom) {
       if (t == 0 || (g & 7u) == 0) {
         // one Philox call gives the 8 steps' bytes: its 16-bit halves (low
         // half first) scaled to the n byte values, (h n) >> 16; n <= 255, so
@@ -657,15 +684,15 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
 #pragma unroll
         for (int j = 0; j < P; ++j) {
           const U4 w = philox(env_id, g >> 3, (uint32_t)port[j], kDomAct, k0, k1);
-          kp[j][0] = act_bytes(w.x, w.y, nk);
-          kp[j][1] = act_bytes(w.z, w.w, nk);
+          kp[j] = act_bytes(w.x, w.y, nk);
+          kq[j] = act_bytes(w.z, w.w, nk);
         }
         if constexpr (EXT) {
           if (batt) {
             const U4 w = philox(env_id, g >> 3, (uint32_t)N, kDomAct, k0, k1);
             const uint32_t nb = (uint32_t)(2 * n_levels + 1);
-            bkp[0] = act_bytes(w.x, w.y, nb);
-            bkp[1] = act_bytes(w.z, w.w, nb);
+            bkp = act_bytes(w.x, w.y, nb);
+            bkq = act_bytes(w.z, w.w, nb);
           }
         }
       }
@@ -673,25 +700,27 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       const bool hi4 = (g & 4u) != 0;
       const uint32_t sh = 8u * (g & 3u);
 #pragma unroll
-      for (int j = 0; j < P; ++j) k[j] = (int)__builtin_amdgcn_ubfe(hi4 ? kp[j][1] : kp[j][0], sh, 8);
-      if constexpr (EXT) kb = (int)__builtin_amdgcn_ubfe(hi4 ? bkp[1] : bkp[0], sh, 8);
-    } else if (dy.mode == CX_ACT_MAX) {
+      for (int j = 0; j < P; ++j) k[j] = (int)__builtin_amdgcn_ubfe(hi4 ? kq[j] : kp[j], sh, 8);
+      if constexpr (EXT) kb = (int)__builtin_amdgcn_ubfe(hi4 ? bkq : bkp, sh, 8);
+    } else if (flags & kMax) {
 #pragma unroll
       for (int j = 0; j < P; ++j) k[j] = n_levels + n_neg;
       kb = 2 * n_levels;
     } else {
+      // this step's bytes were asked for a step ago (the wait for them is then
+      // no wait for the records of this step); the next step's are asked for now
+#define CX_ASK(row)                                                                                    \
+  do {                                                                                                 \
+    _Pragma("unroll") for (int j = 0; j < P; ++j)                                                      \
+        k_in[j] = active && port[j] >= 0 ? (int)gl_at(row, act_bo + (uint32_t)port[j]) : 0;            \
+    if constexpr (EXT) kb_in = batt && active ? (int)gl_at(row, act_bo + (uint32_t)N) : 0;             \
+  } while (0)
+      if (t == 0) CX_ASK(ai_t);
 #pragma unroll
-      for (int j = 0; j < P; ++j) {
-        int v = 0;
-        if (active && port[j] >= 0)
-          v = ld_at(ai_t, act_bo + (uint32_t)port[j]);
-        k[j] = v > n_levels + n_neg ? n_levels + n_neg : v;
-      }
-      if constexpr (EXT) {
-        int v = 0;
-        if (batt && active) v = ld_at(ai_t, act_bo + (uint32_t)N);
-        kb = v > 2 * n_levels ? 2 * n_levels : v;
-      }
+      for (int j = 0; j < P; ++j) k[j] = min(k_in[j], n_levels + n_neg);
+      if constexpr (EXT) kb = min(kb_in, 2 * n_levels);
+      if (t + 1 < T) CX_ASK(ai_t + act_step);
+#undef CX_ASK
     }
 
     // ---- apply actions: clip by request, charge curve, battery room; a
@@ -700,17 +729,17 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
     float pw[P];
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-      const float req = (float)k[j] * C.inv_n_levels * pmax[j];
-      const float rhat = pmax[j] * fminf(1.0f, qf[j] * C.inv_1mtau);
-      const float room = qf[j] * cap[j] * C.inv_dt;
+      const float req = (float)k[j] * inv_n_levels * pmax[j];
+      const float rhat = pmax[j] * fminf(1.0f, qf[j] * inv_1mtau);
+      const float room = qf[j] * cap[j] * inv_dt;
       if constexpr (EXT) {
         const int lev = k[j] - n_neg;
         const float soc = (float)(1.0 - q[j]);
-        const float creq = (float)lev * C.inv_n_levels * pmax[j];
-        const float dreq = (float)(-lev) * C.inv_n_levels * pdis[j];
-        const float crate = rb[j] * fminf(1.0f, qf[j] * C.inv_1mtau);   // the car's curve
-        const float drate = rb[j] * fminf(1.0f, soc * C.inv_1mtau);
-        const float stored = soc * cap[j] * C.inv_dt;
+        const float creq = (float)lev * inv_n_levels * pmax[j];
+        const float dreq = (float)(-lev) * inv_n_levels * pdis[j];
+        const float crate = rb[j] * fminf(1.0f, qf[j] * inv_1mtau);   // the car's curve
+        const float drate = rb[j] * fminf(1.0f, soc * inv_1mtau);
+        const float stored = soc * cap[j] * inv_dt;
         const float p = lev >= 0 ? fminf(fminf(creq, crate), room) : -fminf(fminf(dreq, drate), stored);
         pw[j] = CX_OCCUPIED(j) ? p : 0.0f;
       } else {
@@ -735,11 +764,11 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
         F[j] = 1.0f;
       }
       auto check = [&](int k) {
-        if ((C.blk_mask >> k) & 1u) {  // a level of blocks of 2^k slots (wave-uniform)
+        if ((blk_mask >> k) & 1u) {  // a level of blocks of 2^k slots (wave-uniform)
           // a real (scalar) branch: most k have no level, and computing the
           // check for every k and selecting would cost more than it saves
           asm volatile("");
-          const float c = C.blk_cap[k];
+          const float c = blk_cap[k];
 #pragma unroll
           for (int j = 0; j < P; ++j) {
             const bool over = r[j] > c;
@@ -769,8 +798,8 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       const float f = over ? c_root * frcp(tot) : 1.0f;
 #pragma unroll
       for (int j = 0; j < P; ++j) pw[j] *= F[j] * f;
-      e_net = C.dt * (over ? c_root : tot);
-      e_grid = e_net * C.inv_eta_uniform;
+      e_net = dt * (over ? c_root : tot);
+      e_grid = e_net * inv_eta_u;
     } else {
 #pragma unroll
     for (int d = 0; d < kMaxLevels - 1; ++d) {
@@ -848,7 +877,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       const float f = over ? c_root * frcp(a) : 1.0f;
 #pragma unroll
       for (int j = 0; j < P; ++j) pw[j] *= f;
-      e_net = C.dt * (over ? copysignf(c_root, tot) : tot);
+      e_net = dt * (over ? copysignf(c_root, tot) : tot);
       // grid energy: charging ports draw e / eta, discharging ports return eta e
       float tg = 0.f, to = 0.f;
 #pragma unroll
@@ -856,8 +885,8 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
         tg += pw[j] > 0.f ? pw[j] * inv_eta[j] : pw[j] * eta[j];
         to += pw[j] < 0.f ? pw[j] * eta[j] : 0.f;
       }
-      e_grid = C.dt * station_sum<L>(tg);
-      if (C.alpha_dc != 0.0f) e_out = C.dt * station_sum<L>(to);
+      e_grid = dt * station_sum<L>(tg);
+      if (C.alpha_dc != 0.0f) e_out = dt * station_sum<L>(to);
     } else {
       float tot = 0.f;
 #pragma unroll
@@ -867,14 +896,14 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       const float f = over ? c_root * frcp(tot) : 1.0f;
 #pragma unroll
       for (int j = 0; j < P; ++j) pw[j] *= f;
-      e_net = C.dt * (over ? c_root : tot);
+      e_net = dt * (over ? c_root : tot);
       if (C.uniform_eta) {
-        e_grid = e_net * C.inv_eta_uniform;
+        e_grid = e_net * inv_eta_u;
       } else {
         float tg = 0.f;
 #pragma unroll
         for (int j = 0; j < P; ++j) tg += pw[j] * inv_eta[j];
-        e_grid = C.dt * station_sum<L>(tg);
+        e_grid = dt * station_sum<L>(tg);
       }
     }
     }  // projection of classes that are not SIMPLE
@@ -914,7 +943,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
 #pragma unroll
     for (int j = 0; j < P; ++j) {
       const bool occ = CX_OCCUPIED(j);              // pw = 0 and icap = 0 on empty slots
-      const float e = C.dt * pw[j];
+      const float e = dt * pw[j];
       const double nq = q[j] - (double)(e * icap[j]);
       q[j] = nq > 0.0 ? nq : 0.0;
       if constexpr (EXT) q[j] = q[j] < 1.0 ? q[j] : 1.0;  // discharging never below SoC 0
@@ -928,14 +957,14 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
           const bool csu = cs[j] != 0;
           dep = occ && (csu ? q[j] <= (double)u[j] : dw[j] == 0);
           dep0 = dep && !csu;
-          const float tl = (float)dw[j] * C.dt;
+          const float tl = (float)dw[j] * dt;
           csat1 += (dep && csu) ? fmaxf(0.0f, -tl) - C.beta_sat1 * fmaxf(0.0f, tl) : 0.0f;
           cs[j] = dep ? 0 : cs[j];
           dw[j] = dep ? 0 : dw[j];   // a charged user may leave with steps of its stay left
         }
         if (models) rb[j] = dep ? 0.f : rb[j];
       }
-      if (C.alpha_sat != 0.0f) {  // energy still wanted by a departing car (c_satisfaction,0)
+      if (flags & kSat) {  // energy still wanted by a departing car (c_satisfaction,0)
         const float miss = fmaxf(0.0f, (qf[j] - u[j]) * cap[j]);
         csat += dep0 ? miss : 0.0f;
       }
@@ -946,7 +975,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
       icap[j] = dep ? 0.f : icap[j];
       plast[j] = dep ? 0.f : plast[j];
     }
-    if (C.alpha_sat != 0.0f) csat = station_sum<L>(csat);
+    if (flags & kSat) csat = station_sum<L>(csat);
     if constexpr (EXT) {
       if (users && C.alpha_sat1 != 0.0f) csat1 = station_sum<L>(csat1);
     }
@@ -1007,7 +1036,7 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
             }
             s0 = C.soc_lo + C.soc_span * u24(b.y);
             tg = C.tgt_lo + C.tgt_span * u24(b.z);
-            dd = stay_len(tdw, tdw_lds, C.dwell_log2, b.w);
+            dd = stay_len(tdw, C.dwell_log2, b.w);
             if constexpr (EXT) {
               if (users) us = philox(env_id, g, (uint32_t)rank, kDomUser, k0, k1).x <= C.cs_thresh ? 1 : 0;
             }
@@ -1032,12 +1061,12 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
     float r;
     if constexpr (EXT) {
       const float e_gn = e_grid + e_b;
-      const float price = e_gn > 0.0f ? pbuy : C.p_sell_grid;
-      r = C.p_sell * e_net - price * e_gn - C.fixed_cost - C.alpha_sat * csat - C.alpha_dec * (float)rej -
+      const float price = e_gn > 0.0f ? pbuy : p_sell_grid;
+      r = p_sell * e_net - price * e_gn - fixed_cost - alpha_sat * csat - alpha_dec * (float)rej -
           C.alpha_db * fmaxf(0.0f, -e_b) + C.alpha_dc * e_out - C.alpha_sat1 * csat1;
     } else {
-      const float price = e_grid > 0.0f ? pbuy : C.p_sell_grid;
-      r = C.p_sell * e_net - price * e_grid - C.fixed_cost - C.alpha_sat * csat - C.alpha_dec * (float)rej;
+      const float price = e_grid > 0.0f ? pbuy : p_sell_grid;
+      r = p_sell * e_net - price * e_grid - fixed_cost - alpha_sat * csat - alpha_dec * (float)rej;
     }
     ret += (double)r;
 
@@ -1073,12 +1102,12 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
     uint32_t obs_bo_t = obs_bo, act_bo_t = act_bo, env_bo_t = env_bo;
     asm volatile("" : "+v"(obs_bo_t), "+v"(act_bo_t), "+v"(env_bo_t));
     // (the fused policy reads the stage from float 0: its records are 16-byte aligned)
-    const int pad = !POL && STAGE && w_obs
+    const int pad = !POL && STAGE && (flags & kWObs)
                         ? (int)((reinterpret_cast<uintptr_t>(ob_now + (int64_t)env_blk0 * obs_dim) >> 2) & 3u)
                         : 0;
     if (active) {
-      if (w_obs || POL) {
-        auto obs_record = [&](auto put) {
+      if (POL || (flags & kWObs)) {
+        auto obs_record = [&](auto put, auto put4) {
 #pragma unroll
           for (int j = 0; j < P; ++j) {
             if (NOPAD || port[j] >= 0) {
@@ -1087,8 +1116,8 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
               put(0u * 4u * N, o, occ ? 1.0f : 0.0f);
               put(1u * 4u * N, o, occ ? 1.0f - qf[j] : 0.0f);
               put(2u * 4u * N, o, occ ? qf[j] - u[j] : 0.0f);
-              put(3u * 4u * N, o, (float)dw[j] * C.inv_steps_ep);
-              float rh = fminf(1.0f, qf[j] * C.inv_1mtau);
+              put(3u * 4u * N, o, (float)dw[j] * inv_steps_ep);
+              float rh = fminf(1.0f, qf[j] * inv_1mtau);
               if constexpr (EXT) {
                 if (models) rh *= rb[j] * inv_pmax[j];  // the car's curve, as a share of the port maximum
               }
@@ -1099,13 +1128,13 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
               }
             }
           }
-          if (l < 4) {
+          if (l == 0) {  // the station's four: its first lane
             const int n_occ = done ? 0 : (N - n_free + acc);
-            float gv = l == 3 ? (float)n_occ * (1.0f / (float)N) : l == 0 ? gl_sin : l == 1 ? gl_cos : gl_price;
+            float price = gl.z;
             if constexpr (EXT) {
-              if (days && l == 2) gv = gld(C.price_days, dday * steps_ep + t_day);
+              if (days) price = gld(C.price_days, dday * steps_ep + t_day);
             }
-            put(4u * (uint32_t)(6 * N), 4u * (uint32_t)l, gv);
+            put4(4u * (uint32_t)(6 * N), gl.x, gl.y, price, (float)n_occ * (1.0f / (float)N));
           }
           if constexpr (EXT) {
             if (batt && l < 2) put(4u * (uint32_t)(6 * N + 4), 4u * (uint32_t)l, l == 0 ? (float)bsoc : bpw * C.b_inv_rate);
@@ -1113,59 +1142,58 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
               put(4u * (uint32_t)C.day_obs, 4u * (uint32_t)l, l == 0 ? (float)dday * C.inv_n_days : (dday % 7 >= 5 ? 1.0f : 0.0f));
           }
         };
-        if (POL && !w_obs) {
+        if (POL && !(flags & kWObs)) {
           // the fused policy without observation records: the values go to
           // the MLP's BF16 rows directly (their padding was zeroed by the
           // first conversion)
           typedef __attribute__((address_space(3))) uint16_t lds_u16;
           lds_u16 *xr = reinterpret_cast<lds_u16 *>(lds + pol->xb_off) + (env - env_blk0) * (kPolXbRow * 8);
-          obs_record([&](uint32_t fo, uint32_t lo, float v) { xr[(fo + lo) >> 2] = (uint16_t)pack2(v, 0.f); });
+          obs_record([&](uint32_t fo, uint32_t lo, float v) { xr[(fo + lo) >> 2] = (uint16_t)pack2(v, 0.f); },
+                     [&](uint32_t fo, float a, float b, float c, float d) {
+                       lds_u32 *x2 = reinterpret_cast<lds_u32 *>(xr) + (fo >> 3);  // (6 N is even)
+                       x2[0] = pack2(a, b);
+                       x2[1] = pack2(c, d);
+                     });
         } else if constexpr (STAGE) {
-          lds_float *sb = stage + (POL ? 0 : (t & 1) * stage_floats) + pad;
-          obs_record([&](uint32_t fo, uint32_t lo, float v) {
-            *reinterpret_cast<lds_float *>(reinterpret_cast<__attribute__((address_space(3))) char *>(sb) + stage_bo +
-                                           fo + lo) = v;
-          });
+          lds_char *sb = reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_floats) + pad) + stage_bo;
+          obs_record([&](uint32_t fo, uint32_t lo, float v) { *reinterpret_cast<lds_float *>(sb + fo + lo) = v; },
+                     [&](uint32_t fo, float a, float b, float c, float d) {
+                       *reinterpret_cast<lds_f32x4u *>(sb + fo) = f32x4{a, b, c, d};
+                     });
         } else {
           // the feature's offset goes on the wave-uniform base, the lane's on its
           // 32-bit offset
-          obs_record([&](uint32_t fo, uint32_t lo, float v) {
-            st_at((float *)((char *)ob_now + fo), obs_bo_t + lo, v);
-          });
+          obs_record([&](uint32_t fo, uint32_t lo, float v) { st_at((float *)((char *)ob_now + fo), obs_bo_t + lo, v); },
+                     [&](uint32_t fo, float a, float b, float c, float d) {
+                       st_at((f32x4u *)((char *)ob_now + fo), obs_bo_t, (f32x4u){a, b, c, d});
+                     });
         }
       }
-      if (w_act) {
-        uint8_t *ab = ab_t;
-        bool packed = false;
-        if constexpr (NOPAD) {
+      if (flags & kWAct) {
+        if (NOPAD && (flags & kActQuads)) {
           // four consecutive ports' bytes gathered into the first lane of each
           // quad and stored as one dword (an env's bytes start at a multiple of
-          // 4, N being one; the step's row too when its base is aligned)
-          if ((reinterpret_cast<uintptr_t>(ab) & 3u) == 0) {
-            packed = true;
+          // 4, N being one; every step's row too)
 #pragma unroll
-            for (int j = 0; j < P; ++j) {
-              const int b1 = __builtin_amdgcn_update_dpp(0, k[j], 0x55, 0xF, 0xF, false);  // quad lane 1
-              const int b2 = __builtin_amdgcn_update_dpp(0, k[j], 0xAA, 0xF, 0xF, false);  // quad lane 2
-              const int b3 = __builtin_amdgcn_update_dpp(0, k[j], 0xFF, 0xF, 0xF, false);  // quad lane 3
-              const uint32_t w4 =
-                  (uint32_t)k[j] | ((uint32_t)b1 << 8) | ((uint32_t)b2 << 16) | ((uint32_t)b3 << 24);
-              if ((l & 3) == 0) st_at((uint32_t *)ab, act_bo_t + (uint32_t)port[j], w4);
-            }
+          for (int j = 0; j < P; ++j) {
+            const int b1 = __builtin_amdgcn_update_dpp(0, k[j], 0x55, 0xF, 0xF, false);  // quad lane 1
+            const int b2 = __builtin_amdgcn_update_dpp(0, k[j], 0xAA, 0xF, 0xF, false);  // quad lane 2
+            const int b3 = __builtin_amdgcn_update_dpp(0, k[j], 0xFF, 0xF, 0xF, false);  // quad lane 3
+            const uint32_t w4 = (uint32_t)k[j] | ((uint32_t)b1 << 8) | ((uint32_t)b2 << 16) | ((uint32_t)b3 << 24);
+            if ((l & 3) == 0) st_at((uint32_t *)ab_t, act_bo_t + (uint32_t)port[j], w4);
           }
-        }
-        if (!packed) {
+        } else {
 #pragma unroll
           for (int j = 0; j < P; ++j)
-            if (NOPAD || port[j] >= 0) st_at(ab, act_bo_t + (uint32_t)port[j], (uint8_t)k[j]);
+            if (NOPAD || port[j] >= 0) st_at(ab_t, act_bo_t + (uint32_t)port[j], (uint8_t)k[j]);
         }
         if constexpr (EXT) {
-          if (batt && l == 0) st_at(ab, act_bo_t + (uint32_t)N, (uint8_t)kb);
+          if (batt && l == 0) st_at(ab_t, act_bo_t + (uint32_t)N, (uint8_t)kb);
         }
       }
       if (l == 0) {
-        if (w_rew) st_at(rw_t, 4u * env_bo_t, r);
-        if (w_done) st_at(dn_t, env_bo_t, (uint8_t)(done ? 1 : 0));
+        if (flags & kWRew) st_at(rw_t, 4u * env_bo_t, r);
+        if (flags & kWDone) st_at(dn_t, env_bo_t, (uint8_t)(done ? 1 : 0));
       }
     }
     ob_t += obs_step;
@@ -1180,38 +1208,39 @@ __device__ __forceinline__ void run_group(const SegDev &sg, const Dyn &dy, int g
     __syncthreads();
     // the stage of this step is complete: out to HBM (the next step fills the
     // other buffer; the barrier of that step keeps this one until it is read)
-    if (STAGE && w_obs && (!POL || wv < n_run))
+    if (STAGE && (flags & kWObs) && (!POL || wv < n_run))
       flush_stage(stage + (POL ? 0 : (t & 1) * stage_floats), ob_now + (int64_t)env_blk0 * obs_dim, pad, n_blk,
                   (group - g_blk0) * 64 + lane, n_run * 64);
     if constexpr (POL) {
       // the next step's levels (the phase's barriers keep the stage until the
       // flush above has read it)
       if (t + 1 < dy.T)
-        policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, (int)blk_envs, wv, env_id0, g + 1u, k0, k1,
+        policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g + 1u, k0, k1,
                                  w_obs);
     }
   }
 
-  // ---- state back to HBM
+  // ---- state back to HBM (its addresses read again, not held over the steps)
+  CX_KONST SegDev &so = *reload(sgp);
   if (active) {
 #pragma unroll
     for (int j = 0; j < P; ++j) {
       const int64_t i = sofs + j * L + l;
-      sg.q[i] = q[j];
-      sg.u[i] = u[j];
-      sg.cap[i] = cap[j];
-      sg.p_last[i] = plast[j];
-      sg.dwell[i] = (int16_t)dw[j];
+      gst(so.q, i, q[j]);
+      gst(so.u, i, u[j]);
+      gst(so.cap, i, cap[j]);
+      gst(so.p_last, i, plast[j]);
+      gst(so.dwell, i, (int16_t)dw[j]);
       if constexpr (EXT) {
-        if (users) sg.utype[i] = (uint8_t)cs[j];
-        if (models) sg.rbar[i] = rb[j];
+        if (users) gst(so.utype, i, (uint8_t)cs[j]);
+        if (models) gst(so.rbar, i, rb[j]);
       }
     }
-    if (l == 0) sg.ret[env] = ret;
+    if (l == 0) gst(so.ret, env, ret);
     if constexpr (EXT) {
       if (batt && l == 0) {
-        sg.bsoc[env] = bsoc;
-        sg.bp[env] = bpw;
+        gst(so.bsoc, env, bsoc);
+        gst(so.bp, env, bpw);
       }
     }
   }
@@ -1245,7 +1274,9 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   }
   // the segment is block-uniform: say so, so its fields come in scalar loads
   lo = __builtin_amdgcn_readfirstlane(lo);
-  const SegDev sg = a.segs[lo];
+  CX_KONST SegDev *const sgp = konst(a.segs) + lo;
+  CX_KONST SegDev &sg = *sgp;
+  CX_KONST ClassDev &C = *konst((const ClassDev *)sg.cls);
   Dyn dy;
   if (a.per_segment) {
     dy = Dyn{sg.T, sg.t_day0, sg.g0, sg.mode, sg.out_mode, sg.obs, sg.act, sg.reward, sg.done, sg.act_in,
@@ -1256,44 +1287,36 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   }
   // stay-length thresholds in LDS (every wave of the block helps load them
   // before any wave may leave)
-  const uint32_t *tdw = sg.cls->tdwell;
-  const bool tdw_lds = a.lds_tdwell != 0;
   const lds_u32x4 *exo_tp = nullptr;
   const lds_float *exo_pr = nullptr;
-  if (tdw_lds) {
-    const int n = 1 << sg.cls->dwell_log2;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) lds_tdwell[i] = gld(tdw, i);
-    // the day's per-step tables after the (16-byte aligned) stay table, for
-    // launches long enough to repay copying them (short ones read them from
-    // device memory)
-    const int steps = sg.cls->steps_ep;
-    if (!POL && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
-      __attribute__((address_space(3))) char *base =
-          (__attribute__((address_space(3))) char *)lds_tdwell + ((4 * n + 15) & ~15);
-      lds_u32x4 *tp = (lds_u32x4 *)base;
-      lds_float *pr = (lds_float *)(base + 16 * kLdsExoSteps);
-      const uint32_t *tpois = sg.cls->tpois;
-      const float *glob = sg.cls->glob;
-      for (int i = threadIdx.x; i < steps; i += blockDim.x) {
-        tp[i] = gld(reinterpret_cast<const u32x4 *>(tpois + (int64_t)i * kPoisStride), 0);
-        pr[i] = gld(glob, 4 * i + 2);
-      }
-      exo_tp = tp;
-      exo_pr = pr;
+  const int n_stay = 1 << C.dwell_log2;
+  for (int i = threadIdx.x; i < n_stay; i += blockDim.x) lds_tdwell[i] = gld(C.tdwell, i);
+  // the day's per-step tables after the (16-byte aligned) stay table, for
+  // launches long enough to repay copying them (short ones read them from
+  // device memory)
+  const int steps = C.steps_ep;
+  if (!POL && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
+    lds_char *base = (lds_char *)lds_tdwell + ((4 * n_stay + 15) & ~15);
+    lds_u32x4 *tp = (lds_u32x4 *)base;
+    lds_float *pr = (lds_float *)(base + 16 * kLdsExoSteps);
+    for (int i = threadIdx.x; i < steps; i += blockDim.x) {
+      tp[i] = gld(reinterpret_cast<const u32x4 *>(C.tpois + (int64_t)i * kPoisStride), 0);
+      pr[i] = gld(C.glob, 4 * i + 2);
     }
-    __syncthreads();
-    tdw = lds_tdwell;
+    exo_tp = tp;
+    exo_pr = pr;
   }
+  __syncthreads();
   const int W = blockDim.x >> 6;
   const int g_blk0 = (b - sg.block_begin) * W;  // the block's first group
-  const int group = __builtin_amdgcn_readfirstlane(g_blk0 + (int)(threadIdx.x >> 6));
+  const int group = uni(g_blk0 + (int)(threadIdx.x >> 6));
   // (the fused policy keeps every wave: all take part in the MLP)
-  if (!POL && group >= sg.n_groups) return;
-  const int n_run = min(W, sg.n_groups - g_blk0);  // waves of the block that run
-  lds_float *stage =
-      a.stage_floats > 0 ? (lds_float *)((__attribute__((address_space(3))) char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, POL>(sg, dy, group, tdw, tdw_lds, exo_tp, exo_pr, stage, a.stage_floats,
-                                           g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
+  const int n_groups = sg.n_groups;
+  if (!POL && group >= n_groups) return;
+  const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
+  lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
+  run_group<L, P, SIMPLE, EXT, STAGE, POL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, stage,
+                                           a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
 }
 
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
