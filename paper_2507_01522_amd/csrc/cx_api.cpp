@@ -212,11 +212,12 @@ void build_groups(const std::vector<SegDev> &in, const std::vector<int> &log2_dw
       g.max_dwell_log2 = std::max(g.max_dwell_log2, log2_dwell[i]);
       g.max_T = std::max(g.max_T, in[i].T);
       g.max_obs_dim = std::max(g.max_obs_dim, in[i].obs_dim);
+      if (in[i].steps_ep <= kLdsExoSteps) g.max_day_steps = std::max(g.max_day_steps, in[i].steps_ep);
     }
     // fewer waves per block where the observation stages would not fit
     g.wpb = wpb;
     while (group_stages(g.kind, g.pack) && g.wpb > 1 &&
-           group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, nullptr, nullptr) > kMaxBlockLds)
+           group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, nullptr, nullptr) > kMaxBlockLds)
       g.wpb >>= 1;
     int blocks = 0;
     for (size_t i = 0; i < in.size(); ++i) {
@@ -248,6 +249,7 @@ void class_segments(const cx_ctx *ctx, const ClassRt &c, int L, int P, std::vect
     sg.n_groups = (int32_t)((n + spw - 1) / spw);
     sg.pack = pack_id(L, P);
     sg.obs_dim = c.comp.obs_dim;
+    sg.steps_ep = ctx->steps_ep;
     sg.seed = ctx->seed;
     const int64_t so = c.slot_off + e0 * c.comp.S;
     sg.q = ctx->q + so;

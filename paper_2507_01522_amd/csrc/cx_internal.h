@@ -125,7 +125,8 @@ struct SegDev {
   // dynamic (per-segment launches only)
   int32_t T, t_day0;
   uint32_t g0;
-  int32_t mode, out_mode, pad2;
+  int32_t mode, out_mode;
+  int32_t steps_ep;     // steps per day of its class (sizes the LDS day tables of its launch)
   float *obs;
   uint8_t *act;
   float *reward;
@@ -187,6 +188,7 @@ struct LaunchGroup {
   int n_segs = 0;
   int n_blocks = 0;
   int max_dwell_log2 = 1;  // largest stay table among its classes (LDS bytes = 4 << this)
+  int max_day_steps = 0;   // longest day among its classes whose day tables go to LDS
   int max_T = 0;           // per-segment launches: the longest horizon among its segments
   int max_obs_dim = 0;     // largest observation among its classes (floats)
   int wpb = 1;             // waves per block: the context's choice, halved until the LDS fits
@@ -208,17 +210,17 @@ constexpr int kLdsExoSteps = 512;
 constexpr int kLdsExoMinT = 32;   // ... in launches of at least this many steps
 
 // LDS layout of a launch group's blocks: the stay table (4 << dwell_log2
-// bytes), the per-step tables (kLdsExoSteps x 20 bytes), then two observation
+// bytes), the day's tables (16 bytes a step, then 4), then two observation
 // stages of waves x stations per wave x the largest observation floats, plus 3
 // floats to align them with HBM (rounded to 16 bytes).
-inline size_t group_table_bytes(int dwell_log2) {
-  return ((((size_t)4 << dwell_log2) + 15) & ~(size_t)15) + (size_t)kLdsExoSteps * 20;
+inline size_t group_table_bytes(int dwell_log2, int day_steps) {
+  return ((((size_t)4 << dwell_log2) + 15) & ~(size_t)15) + (((size_t)day_steps * 20 + 15) & ~(size_t)15);
 }
 // Bytes with the stages; *stage_off / *stage_floats: where the stages begin
 // and floats per stage.
-inline size_t group_lds_bytes(int wpb, int pack, int max_obs_dim, int dwell_log2, int32_t *stage_off,
+inline size_t group_lds_bytes(int wpb, int pack, int max_obs_dim, int dwell_log2, int day_steps, int32_t *stage_off,
                               int32_t *stage_floats) {
-  const size_t off = group_table_bytes(dwell_log2);
+  const size_t off = group_table_bytes(dwell_log2, day_steps);
   const size_t floats =
       ((size_t)wpb * (size_t)(64 / pack_lanes(pack)) * (size_t)max_obs_dim + 3 + 3) & ~(size_t)3;
   if (stage_off) *stage_off = (int32_t)off;

@@ -156,6 +156,9 @@ __device__ __forceinline__ float block_sum_lanes(float v, int lb) {
   return v;
 }
 
+// The lanes of the wave in which b holds (a comparison's own result mask).
+__device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Four random action bytes from two Philox words: each 16-bit half h (low
@@ -222,22 +225,32 @@ typedef __attribute__((address_space(3))) f32x4u lds_f32x4u;
 // the whole chunks go out as one 16-byte buffer store each (a resource over the
 // 16-byte-aligned address dst - pad, offset 16 c for chunk c, non-temporal),
 // the at most 3 floats before the first and after the last whole chunk one by
-// one.  tid / nthreads: this lane among the block's running lanes.
+// one.  Lane 0 starts at the 128-byte line that holds dst (the chunks before
+// dst, at most 7, are skipped), so that every wave's store covers whole lines:
+// starting at dst itself, each 1 KiB store begins and ends inside a line, and
+// HBM takes the two halves of a line from two non-temporal stores as two partial
+// writes.  The mixture's record stream alone (five classes of 6.2-12.4 KB runs, 13.7 GB):
+// 3.25 ms from dst, 2.86 from the line's start, 2.60 if every run were whole lines.
+// tid / nthreads: this lane among the block's running lanes.
 __device__ __forceinline__ void flush_stage(const lds_float *sb, float *dst, int pad, int n, int tid,
                                             int nthreads) {
-  const int c_end = (pad + n) >> 2;  // whole chunks: [pad ? 1 : 0, c_end)
-  // raw buffer: stride 0, range 2^31 - 1 bytes (offsets stay below 16 n + 64),
+  // chunk k counts from that line; [k_beg, k_end) are the whole chunks of the run
+  const int phase = (int)((reinterpret_cast<uintptr_t>(dst) >> 4) & 7u);
+  const int k_beg = phase + (pad ? 1 : 0), k_end = phase + ((pad + n) >> 2);
+  // raw buffer: stride 0, range 2^31 - 1 bytes (offsets stay below 16 n + 192),
   // format word of a plain 32-bit buffer on gfx9-family GPUs
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(dst) - 4 * pad, (short)0, 0x7fffffff, 0x00020000);
-  for (int c = (pad ? 1 : 0) + tid; c < c_end; c += nthreads) {
-    const f32x4 v = *reinterpret_cast<const lds_f32x4 *>(sb + 4 * c);
-    __builtin_amdgcn_raw_buffer_store_b128(v, rs, 16 * c, 0, 2 /* nt */);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      reinterpret_cast<char *>(dst) - 4 * pad - 16 * phase, (short)0, 0x7fffffff, 0x00020000);
+  const lds_float *line = sb - 4 * phase;  // (chunks below k_beg are not read)
+  for (int k = tid; k < k_end; k += nthreads) {
+    if (k < k_beg) continue;
+    const f32x4 v = *reinterpret_cast<const lds_f32x4 *>(line + 4 * k);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rs, 16 * k, 0, 2 /* nt */);
   }
   if (pad != 0 || ((pad + n) & 3) != 0) {  // the same in every lane
     const int head = (4 - pad) & 3;         // floats before the first whole chunk
     if (tid < head && tid < n) st_at(dst, 4u * (uint32_t)tid, (float)sb[pad + tid]);
-    const int i = 4 * c_end - pad + (tid - 4);  // lanes 4..7: the floats after the last whole chunk
+    const int i = 4 * (k_end - phase) - pad + (tid - 4);  // lanes 4..7: the floats after the last whole chunk
     if (tid >= 4 && tid < 8 && i >= head && i < n) st_at(dst, 4u * (uint32_t)i, (float)sb[pad + i]);
   }
 }
@@ -650,7 +663,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
         if (users) bus = philox(env_id, gl, 0u, kDomUser, k0, k1).x <= C.cs_thresh ? 1 : 0;
       }
       if constexpr (AHEAD2) {
-        if (__ballot(bM >= 2)) {  // some step ahead brings a second car
+        if (ballot(bM >= 2)) {  // some step ahead brings a second car
           const U4 b1 = philox(env_id, gl, 1u, kDomCar, k0, k1);
           bcp1 = C.cap_lo + C.cap_span * u24(b1.x);
           bs01 = C.soc_lo + C.soc_span * u24(b1.y);
@@ -942,7 +955,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     float csat = 0.f, csat1 = 0.f;
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-      const bool occ = CX_OCCUPIED(j);              // pw = 0 and icap = 0 on empty slots
+      const bool occ = CX_OCCUPIED(j);              // (pw = 0 on empty slots)
       const float e = dt * pw[j];
       const double nq = q[j] - (double)(e * icap[j]);
       q[j] = nq > 0.0 ? nq : 0.0;
@@ -962,18 +975,14 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           cs[j] = dep ? 0 : cs[j];
           dw[j] = dep ? 0 : dw[j];   // a charged user may leave with steps of its stay left
         }
-        if (models) rb[j] = dep ? 0.f : rb[j];
       }
       if (flags & kSat) {  // energy still wanted by a departing car (c_satisfaction,0)
         const float miss = fmaxf(0.0f, (qf[j] - u[j]) * cap[j]);
         csat += dep0 ? miss : 0.0f;
       }
-      q[j] = dep ? 0.0 : q[j];
-      qf[j] = dep ? 0.0f : qf[j];
-      u[j] = dep ? 0.f : u[j];
-      cap[j] = dep ? 0.f : cap[j];
-      icap[j] = dep ? 0.f : icap[j];
-      plast[j] = dep ? 0.f : plast[j];
+      // (an empty slot keeps its last car's values: its power and every feature
+      // are masked by its being empty, an arrival overwrites them, and the state
+      // goes back to HBM as zeros)
     }
     if (flags & kSat) csat = station_sum<L>(csat);
     if constexpr (EXT) {
@@ -981,20 +990,21 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     }
 
     // ---- arrivals: first free ports in port order take the accepted cars
-    int cnt[P], below[P];
-    bool fr[P];
-    int n_free = 0;
+    int rej = 0;
+    if (ballot(M > 0)) {
+      int cnt[P], below[P];
+      bool fr[P];
+      int n_free = 0;
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-      fr[j] = (EXT ? !CX_OCCUPIED(j) : dw[j] == 0) && (NOPAD || port[j] >= 0);
-      const uint64_t m = __ballot(fr[j]) & smask;
-      cnt[j] = __popcll(m);
-      below[j] = __popcll(m & below_mask);
-      n_free += cnt[j];
-    }
-    const int acc = M < n_free ? M : n_free;
-    const int rej = M - acc;
-    if (__ballot(acc > 0)) {
+      for (int j = 0; j < P; ++j) {
+        fr[j] = (EXT ? !CX_OCCUPIED(j) : dw[j] == 0) && (NOPAD || port[j] >= 0);
+        const uint64_t m = ballot(fr[j]) & smask;
+        cnt[j] = __popcll(m);
+        below[j] = __popcll(m & below_mask);
+        n_free += cnt[j];
+      }
+      const int acc = M < n_free ? M : n_free;
+      rej = M - acc;
       // the first car's profile was drawn ahead by lane tb of the station
       const float f_cp = bcastf<L>(bcp, tb), f_s0 = bcastf<L>(bs0, tb), f_tg = bcastf<L>(btg, tb);
       const int f_dw = bcast<L>(bdw, tb);
@@ -1004,7 +1014,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       float f_cp1 = 0.f, f_s01 = 0.f, f_tg1 = 0.f;
       int f_dw1 = 1;
       if constexpr (AHEAD2) {
-        if (__ballot(acc > 1)) {
+        if (ballot(acc > 1)) {
           f_cp1 = bcastf<L>(bcp1, tb);
           f_s01 = bcastf<L>(bs01, tb);
           f_tg1 = bcastf<L>(btg1, tb);
@@ -1077,11 +1087,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       t_day = 0;
 #pragma unroll
       for (int j = 0; j < P; ++j) {
-        dw[j] = 0; q[j] = 0.0; qf[j] = 0.f; u[j] = 0.f; cap[j] = 0.f; icap[j] = 0.f; plast[j] = 0.f;
-        if constexpr (EXT) {
-          cs[j] = 0;
-          if (models) rb[j] = 0.f;
-        }
+        dw[j] = 0;
+        if constexpr (EXT) cs[j] = 0;
       }
       if constexpr (EXT) {
         if (days) dday = episode_day(env_id, g + 1u, k0, k1, n_days);  // the next episode begins
@@ -1107,6 +1114,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
                         : 0;
     if (active) {
       if (POL || (flags & kWObs)) {
+        int n_occ = 0;
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+          n_occ += __popcll(ballot(CX_OCCUPIED(j) && (NOPAD || port[j] >= 0)) & smask);
         auto obs_record = [&](auto put, auto put4) {
 #pragma unroll
           for (int j = 0; j < P; ++j) {
@@ -1122,14 +1133,13 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
                 if (models) rh *= rb[j] * inv_pmax[j];  // the car's curve, as a share of the port maximum
               }
               put(4u * 4u * N, o, occ ? rh : 0.0f);
-              put(5u * 4u * N, o, plast[j] * inv_pmax[j]);
+              put(5u * 4u * N, o, occ ? plast[j] * inv_pmax[j] : 0.0f);
               if constexpr (EXT) {
                 if (users) put(4u * (uint32_t)C.user_obs, 4u * (uint32_t)port[j], cs[j] ? 1.0f : 0.0f);
               }
             }
           }
           if (l == 0) {  // the station's four: its first lane
-            const int n_occ = done ? 0 : (N - n_free + acc);
             float price = gl.z;
             if constexpr (EXT) {
               if (days) price = gld(C.price_days, dday * steps_ep + t_day);
@@ -1172,14 +1182,15 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       if (flags & kWAct) {
         if (NOPAD && (flags & kActQuads)) {
           // four consecutive ports' bytes gathered into the first lane of each
-          // quad and stored as one dword (an env's bytes start at a multiple of
-          // 4, N being one; every step's row too)
+          // quad (the pair's second byte, then the second pair, each moved and
+          // shifted by one 24-bit multiply) and stored as one dword (an env's
+          // bytes start at a multiple of 4, N being one; every step's row too)
 #pragma unroll
           for (int j = 0; j < P; ++j) {
-            const int b1 = __builtin_amdgcn_update_dpp(0, k[j], 0x55, 0xF, 0xF, false);  // quad lane 1
-            const int b2 = __builtin_amdgcn_update_dpp(0, k[j], 0xAA, 0xF, 0xF, false);  // quad lane 2
-            const int b3 = __builtin_amdgcn_update_dpp(0, k[j], 0xFF, 0xF, 0xF, false);  // quad lane 3
-            const uint32_t w4 = (uint32_t)k[j] | ((uint32_t)b1 << 8) | ((uint32_t)b2 << 16) | ((uint32_t)b3 << 24);
+            const uint32_t b1 = (uint32_t)__builtin_amdgcn_update_dpp(0, k[j], 0xF5, 0xF, 0xF, true);  // lanes 1, 1, 3, 3
+            const uint32_t w2 = (uint32_t)k[j] | __umul24(b1, 1u << 8);
+            const uint32_t b2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w2, 0xAA, 0xF, 0xF, true);  // lane 2
+            const uint32_t w4 = w2 | __umul24(b2, 1u << 16);
             if ((l & 3) == 0) st_at((uint32_t *)ab_t, act_bo_t + (uint32_t)port[j], w4);
           }
         } else {
@@ -1205,7 +1216,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // are then adjacent envs' blocks written together, which HBM takes
     // noticeably faster (better row locality) than the same bytes spread over
     // many steps.  Waves that left early (past the last env) do not count.
-    __syncthreads();
+    // (Rewards and done flags alone are too few bytes for that.)
+    if (POL || (flags & (kWObs | kWAct))) __syncthreads();
     // the stage of this step is complete: out to HBM (the next step fills the
     // other buffer; the barrier of that step keeps this one until it is read)
     if (STAGE && (flags & kWObs) && (!POL || wv < n_run))
@@ -1226,14 +1238,15 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
 #pragma unroll
     for (int j = 0; j < P; ++j) {
       const int64_t i = sofs + j * L + l;
-      gst(so.q, i, q[j]);
-      gst(so.u, i, u[j]);
-      gst(so.cap, i, cap[j]);
-      gst(so.p_last, i, plast[j]);
+      const bool occ = CX_OCCUPIED(j);
+      gst(so.q, i, occ ? q[j] : 0.0);
+      gst(so.u, i, occ ? u[j] : 0.f);
+      gst(so.cap, i, occ ? cap[j] : 0.f);
+      gst(so.p_last, i, occ ? plast[j] : 0.f);
       gst(so.dwell, i, (int16_t)dw[j]);
       if constexpr (EXT) {
         if (users) gst(so.utype, i, (uint8_t)cs[j]);
-        if (models) gst(so.rbar, i, rb[j]);
+        if (models) gst(so.rbar, i, occ ? rb[j] : 0.f);
       }
     }
     if (l == 0) gst(so.ret, env, ret);
@@ -1298,7 +1311,7 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   if (!POL && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
     lds_char *base = (lds_char *)lds_tdwell + ((4 * n_stay + 15) & ~15);
     lds_u32x4 *tp = (lds_u32x4 *)base;
-    lds_float *pr = (lds_float *)(base + 16 * kLdsExoSteps);
+    lds_float *pr = (lds_float *)(base + 16 * steps);
     for (int i = threadIdx.x; i < steps; i += blockDim.x) {
       tp[i] = gld(reinterpret_cast<const u32x4 *>(C.tpois + (int64_t)i * kPoisStride), 0);
       pr[i] = gld(C.glob, 4 * i + 2);
@@ -1402,13 +1415,13 @@ LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, size_t *lds) {
                      // bisection even for one-step launches
   const bool records =
       group_stages(g.kind, g.pack) && (a.per_segment || (a.out_mode == CX_OUT_FULL && a.obs != nullptr));
-  const size_t with_stages = group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, &b.stage_off,
-                                             &b.stage_floats);
+  const size_t with_stages = group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps,
+                                             &b.stage_off, &b.stage_floats);
   if (records) {
     *lds = with_stages;
   } else {
     b.stage_floats = 0;
-    *lds = group_table_bytes(g.max_dwell_log2);
+    *lds = group_table_bytes(g.max_dwell_log2, g.max_day_steps);
   }
   return b;
 }

@@ -315,6 +315,7 @@ bool launch(cx_server *s) {
     sg.n_groups = (int32_t)((E + spw - 1) / spw);
     sg.pack = pack_id(L, P);
     sg.obs_dim = (int32_t)od;
+    sg.steps_ep = r.spec.s.steps_per_episode;
     sg.seed = r.seed;
     if (b) {
       sg.q = reinterpret_cast<double *>(b + r.off_q);
