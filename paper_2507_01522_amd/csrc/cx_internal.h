@@ -173,7 +173,7 @@ struct LaunchArgs {
     const u32x4 *w1f;     // [16][8][64] fragments of W1^T
     const float *b1;      // [256]
     const u32x4 *w2f;     // [G][3][8][64] fragments of W2^T
-    const float *b2f;     // [G][3][16]
+    const float *b2f;     // [G][3][16]; -inf for levels past the class's
     int32_t in_dim, K1, HP, R, G, L1;
     int32_t hb_off, xb_off, act_off;  // LDS byte offsets
   } pol;
@@ -240,7 +240,7 @@ inline size_t policy_rollout_lds(int dwell_log2, int obs_dim, int N, int32_t *st
                                  int32_t *stage_floats, int32_t *hb_off, int32_t *xb_off, int32_t *act_off) {
   auto a16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
   const size_t off = a16((size_t)4 << dwell_log2);  // the stay table only (no per-step tables)
-  const size_t floats = ((size_t)kPolRolloutEnvs * obs_dim + 3) & ~(size_t)3;
+  const size_t floats = ((size_t)kPolRolloutEnvs * obs_dim + 3 + 3) & ~(size_t)3;  // 3: alignment with HBM
   const size_t region = a16(std::max(4 * floats, (size_t)8 * (kPolRolloutEnvs / 16) * 64 * 16));
   const size_t xb = off + region;
   const size_t act = xb + (size_t)kPolRolloutEnvs * 16 * kPolXbRow;
@@ -270,10 +270,12 @@ struct PolicyArgs {
   int64_t n;
   int32_t in_dim, K1, HP, R, G, N, L1;
   uint32_t g;        // global step of the draws
-  const u32x4 *w1f;  // [2 HP][K1][64] fragments of W1^T
-  const float *b1;   // [32 HP]
-  const u32x4 *w2f;  // [G][R][HP][64] fragments of W2^T
-  const float *b2f;  // [G][R][16]
+  // fragments padded to the largest sizes (as for the fused rollout)
+  const u32x4 *w1f;  // [16][8][64] fragments of W1^T
+  const float *b1;   // [256]
+  const u32x4 *w2f;  // [G][3][8][64] fragments of W2^T
+  const float *b2f;  // [G][3][16]; -inf for levels past the class's
+  // what the launch writes: one of the two
   uint8_t *act;      // [n][N] or NULL
   float *logits;     // [n][N * L1] or NULL
   uint64_t seed;
@@ -283,7 +285,8 @@ struct PolicyArgs {
 // Host-side launchers (defined in cx_kernels.hip).  `a.segs` is the base of
 // the device segment table; each group launches with its own slice.
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st);
-hipError_t launch_policy_rollout(const LaunchArgs &a, int per_lane, int n_blocks, size_t lds, hipStream_t st);
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int per_lane, int hp, int n_blocks, size_t lds,
+                                 hipStream_t st);
 hipError_t graph_rollout(RolloutGraph &g, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st);
 void graph_destroy(RolloutGraph &g);

@@ -265,7 +265,6 @@ __device__ __forceinline__ void flush_stage(const lds_float *sb, float *dst, int
 // context asks for it): stage / stage_floats are the two
 // stage buffers and floats per buffer, g_blk0 the block's first group and
 // n_run the number of its waves that run.
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -274,42 +273,41 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 // (E = 32 envs, row stride obs_dim floats) go through the MLP on the matrix
 // cores and each port gets its level for the next step, in LDS.  The products
 // are those of the standalone policy kernel, K-step by K-step in the same
-// order, so logits and levels are the same: here the block's 4 waves split the
+// order, so logits and levels are the same: the block's 4 waves split the
 // hidden units (first product) and the port groups (second) among them, and
 // each wave reads its weight fragments from device memory (L2) straight into
-// the matrix-core operands.  The K-step loops have compile-time bounds (K1, the
-// class's K-steps of 32 features; 8 x 32 hidden units and 3 level tiles, the
-// largest, over weights padded with zeros -- such steps add exact zeros), so
-// that they are straight-line code whose loads are all issued ahead of the
-// matrix-core work.  LDS: hb (8 x 2 hidden-unit fragments, over the stage once
-// it has been read), xb (the observations in BF16, 256 features per env, zero
-// past in_dim, rows 33 fragments apart so that the 16 envs of a tile fall in
-// different banks) and act (a level byte per port and env).  wv: this wave in
-// the block; convert: the step left its observations in the FP32 stage.
-template <int K1>
+// the matrix-core operands.  K1 (K-steps of 32 features) and HP (K-steps of 32
+// hidden units: 2, 4 or 8) are the class's and the policy's sizes rounded up;
+// the weights are padded with zeros, so such steps add exact zeros.
+// LDS: hb (HP x 2 hidden-unit fragments, over the stage once it has been
+// read), xb (the observations in BF16, 256 features per env, zero past in_dim,
+// rows 33 fragments apart so that the 16 envs of a tile fall in different
+// banks) and act (a level byte per port and env).  wv: this wave in the block;
+// convert: the step left its observations in the FP32 stage; hid: the first
+// product, its first fragments already asked for.
+template <int K1, int HP>
 __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const lds_float *stage, lds_char *lds,
                                              int obs_dim, int N, int blk_envs, int wv, uint32_t env_id0,
-                                             uint32_t g, uint32_t k0, uint32_t k1, bool convert) {
+                                             uint32_t g, uint32_t k0, uint32_t k1, bool convert,
+                                             HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, K1, HP> &hid) {
   constexpr int W = kPolRolloutWaves, NT = kPolRolloutEnvs / 16, CPR = 4 * K1;  // chunks of 8 per row
   const int lane = __lane_id(), col = lane & 15, lg = lane >> 4, tid = wv * 64 + lane;
-  const int in_dim = pl.in_dim, R = pl.R, G = pl.G, L1 = pl.L1;
+  const int in_dim = pl.in_dim, G = pl.G, L1 = pl.L1;
   lds_u32x4 *xb = reinterpret_cast<lds_u32x4 *>(lds + pl.xb_off);
   lds_u32x4 *hb = reinterpret_cast<lds_u32x4 *>(lds + pl.hb_off);
   lds_u8 *act = reinterpret_cast<lds_u8 *>(lds + pl.act_off);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  // observations -> BF16 (features past in_dim and envs past the block's: 0);
-  // a row of the stage starts 16-byte aligned (obs_dim is a multiple of 4).
+  // observations -> BF16 (features past in_dim and envs past the block's: 0).
   // Without observation records the step wrote its values straight into xb
   // (convert = false), whose padding the first conversion zeroed.
   if (convert) {
     for (int c = tid; c < kPolRolloutEnvs * CPR; c += 64 * W) {
       const int e = c / CPR, k = c % CPR, f = 8 * k;
       const lds_float *row = stage + e * obs_dim + f;
-      u32x4 v = zero;
+      u32x4 v = {0u, 0u, 0u, 0u};
       if (e < blk_envs) {
         if (f + 8 <= in_dim) {
-          const f32x4 x = *reinterpret_cast<const lds_f32x4 *>(row);
-          const f32x4 y = *reinterpret_cast<const lds_f32x4 *>(row + 4);
+          const f32x4u x = *reinterpret_cast<const lds_f32x4u *>(row);
+          const f32x4u y = *reinterpret_cast<const lds_f32x4u *>(row + 4);
           v = u32x4{pack2(x.x, x.y), pack2(x.z, x.w), pack2(y.x, y.y), pack2(y.z, y.w)};
         } else if (f < in_dim) {
           float x[8];
@@ -322,91 +320,27 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
     }
     __syncthreads();
   }
-  // first product: this wave's pairs of 16-unit hidden tiles, both pairs per
-  // K-step so that each observation fragment is read once.  Weight fragments
-  // come in buffer loads: one resource per matrix, the fragment's offset a
-  // scalar, the lane's 16 bytes the vector offset (no 64-bit addresses).
-  constexpr int NI = kPolHP / W;
-  // vector offsets: the lane's 16 bytes, plus 4 KiB for K-steps 4..7; the
-  // step's KiB within them goes in the instruction's offset field
-  const uint32_t vo[2] = {16u * (uint32_t)lane, 16u * (uint32_t)lane + 4096u};
-  const __amdgpu_buffer_rsrc_t w1 =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(pl.w1f), (short)0, 2 * kPolHP * kPolK1 * 1024, 0x00020000);
-  const __amdgpu_buffer_rsrc_t w2 =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(pl.w2f), (short)0, G * kPolR * kPolHP * 1024, 0x00020000);
-  f32x4 c0[NI][NT], c1[NI][NT];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int n = 0; n < NT; ++n) c0[i][n] = c1[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < K1; ++s) {
-    u32x4 a0[NI], a1[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int m = 2 * (wv + W * i);  // the pair's first tile
-      const uint32_t v = vo[s >> 2] + 1024u * (uint32_t)(s & 3);
-      a0[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w1, v, m * kPolK1 * 1024, 0));
-      a1[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w1, v, (m + 1) * kPolK1 * 1024, 0));
-    }
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      const u32x4 b = xb[(16 * n + col) * kPolXbRow + 4 * s + lg];
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        c0[i][n] = mfma_bf16(a0[i], b, c0[i][n]);
-        c1[i][n] = mfma_bf16(a1[i], b, c1[i][n]);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int mp = wv + W * i;
-    const f32x4 bA = gld(reinterpret_cast<const f32x4 *>(pl.b1 + 32 * mp + 4 * lg), 0);
-    const f32x4 bB = gld(reinterpret_cast<const f32x4 *>(pl.b1 + 32 * mp + 16 + 4 * lg), 0);
-#pragma unroll
-    for (int n = 0; n < NT; ++n) hb[(mp * NT + n) * 64 + lane] = hidden_frag(c0[i][n], c1[i][n], bA, bB);
-  }
-  __syncthreads();
-  // second product and the draw, per group of 4 ports.  The lane's ports are
-  // 4 wv + lg + 16 i (group wv + 4 i): one Philox call per env serves them all
+  hid.run(frag_rsrc(pl.w1f, 2 * kPolHP * kPolK1), pl.b1, xb, kPolXbRow, hb, wv);
+  const __amdgpu_buffer_rsrc_t w2 = frag_rsrc(pl.w2f, G * kPolR * kPolHP);
+  LogitLayer<NT, HP> logit;
+  logit.start(w2, min(wv, G - 1));
+  // the lane's ports are 4 wv + lg + 16 i (group wv + 4 i): one Philox call per
+  // env serves them all
   U4 dw[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n)
     dw[n] = philox(env_id0 + (uint32_t)(16 * n + col), g, draw_index(4 * wv + lg), kDomGum, k0, k1);
+  __syncthreads();
   for (int grp = wv; grp < G; grp += W) {
     const int port = 4 * grp + lg;
-    float ud[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) ud[n] = draw_uniform(draw_word(dw[n], port));
     f32x4 c[kPolR][NT];
-#pragma unroll
-    for (int r = 0; r < kPolR; ++r) {
-      const f32x4 b = gld(reinterpret_cast<const f32x4 *>(pl.b2f + (int64_t)(grp * kPolR + r) * 16 + 4 * lg), 0);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) c[r][n] = b;
-    }
-#pragma unroll
-    for (int s = 0; s < kPolHP; ++s) {
-      u32x4 hv[NT];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) hv[n] = hb[(s * NT + n) * 64 + lane];
-#pragma unroll
-      for (int r = 0; r < kPolR; ++r) {
-        const u32x4 wf = __builtin_bit_cast(
-            u32x4, __builtin_amdgcn_raw_buffer_load_b128(w2, vo[s >> 2] + 1024u * (uint32_t)(s & 3),
-                                                         (grp * kPolR + r) * kPolHP * 1024, 0));
-#pragma unroll
-        for (int n = 0; n < NT; ++n) c[r][n] = mfma_bf16(wf, hv[n], c[r][n]);
-      }
-    }
+    logit.run(w2, pl.b2f, hb, grp, min(grp + W, G - 1), c);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const int e = 16 * n + col;
-      if (port < N && e < blk_envs) {
-        const f32x4 cn[kPolR] = {c[0][n], c[1][n], c[2][n]};
-        act[e * N + port] = (uint8_t)sample_level(cn, R, L1, ud[n]);
-      }
+      const f32x4 cn[kPolR] = {c[0][n], c[1][n], c[2][n]};
+      const int lev = sample_level(cn, L1, draw_uniform(draw_word(dw[n], port)));
+      if (port < N && e < blk_envs) act[e * N + port] = (uint8_t)lev;
     }
   }
   __syncthreads();
@@ -417,7 +351,8 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 // tdw: the block's LDS copy of the stay thresholds; exo_tp / exo_pr: its LDS
 // copies of the first four arrival thresholds and the base price of every step
 // of the day (NULL: read device memory).
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, bool POL = false>
+// HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units.
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL = 0>
 __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, int group, const lds_u32 *tdw,
                                           const lds_u32x4 *exo_tp, const lds_float *exo_pr, lds_float *stage,
                                           int stage_floats, int g_blk0, int n_run,
@@ -425,6 +360,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   constexpr int SPW = 64 / L;
   constexpr int LOGL = (L == 4) ? 2 : (L == 8) ? 3 : (L == 16) ? 4 : (L == 32) ? 5 : 6;
   constexpr bool NOPAD = SIMPLE;  // every slot holds a port: slot s = port s
+  constexpr bool POL = HPOL > 0;
   CX_KONST SegDev &sg = *sgp;
   CX_KONST ClassDev *const cls = konst((const ClassDev *)sg.cls);
   CX_KONST ClassDev &C = *cls;
@@ -602,14 +538,17 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   // observation the rollout starts from, put in the stage
   [[maybe_unused]] const int wv = group - g_blk0;
   [[maybe_unused]] const uint32_t env_id0 = (uint32_t)(sg.env0 + env_blk0);
-  // K-steps of 32 features of the first product: the observation of a SIMPLE
-  // class has 6 L P + 4 features
+  // K-steps of 32 features of the first product (a class of L P slots has at most
+  // 6 L P + 4 features)
   constexpr int kPolSteps1 = (6 * L * P + 4 + 31) / 32;
+  [[maybe_unused]] const auto w1_rsrc = [&] { return frag_rsrc(pol->w1f, 2 * kPolHP * kPolK1); };
   if constexpr (POL) {
     const float *src = pol->obs0 + sg.obs_off + (int64_t)env_blk0 * obs_dim;
     for (int i = wv * 64 + lane; i < n_blk; i += kPolRolloutWaves * 64) stage[i] = gld(src, i);
+    HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, kPolSteps1, HPOL> hid;
+    hid.start(w1_rsrc(), wv);
     __syncthreads();
-    policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true);
+    policy_phase<kPolSteps1, HPOL>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true, hid);
   }
 
   [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
@@ -686,7 +625,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     if constexpr (POL) {  // the levels the policy drew after the last step
       const lds_u8 *lv = reinterpret_cast<const lds_u8 *>(lds + pol->act_off) + (env - env_blk0) * N;
 #pragma unroll
-      for (int j = 0; j < P; ++j) k[j] = active ? (int)lv[port[j]] : 0;
+      for (int j = 0; j < P; ++j) k[j] = active && (NOPAD || port[j] >= 0) ? (int)lv[port[j]] : 0;
     } else if (flags & kRandom) {
       if (t == 0 || (g & 7u) == 0) {
         // one Philox call gives the 8 steps' bytes: its 16-bit halves (low
@@ -760,6 +699,25 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       }
     }
 
+    // Sum over the station of one value per slot.  The fused policy of a class
+    // that is not SIMPLE adds lanes first, then registers: the order of the
+    // packing with one slot per lane that such a class runs in by default, so
+    // that its records are those of the two-kernel path bit for bit.
+    auto station_total = [&](const float (&v)[P]) {
+      if constexpr (POL && !SIMPLE && P > 1) {
+        float r[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) r[j] = station_sum<L>(v[j]);
+        if constexpr (P == 2) return r[0] + r[1];
+        else return (r[0] + r[1]) + (r[2] + r[3]);
+      } else {
+        float a = v[0];
+#pragma unroll
+        for (int j = 1; j < P; ++j) a += v[j];
+        return station_sum<L>(a);
+      }
+    };
+
     // ---- projection onto the capacity tree (Eq. ArchConst), deepest level
     // first; the root (level D-1) holds the whole station
     float e_net, e_grid, e_out = 0.f;
@@ -829,10 +787,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           for (int m = 0; m < 4; ++m) {
             if (m < nd) {
               const uint32_t code = 0x80u | (uint32_t)m;
-              float acc = 0.f;
+              float in[P];
 #pragma unroll
-              for (int j = 0; j < P; ++j) acc += ((lbp[j] >> (8 * d)) & 0xFFu) == code ? pw[j] : 0.f;
-              acc = station_sum<L>(acc);
+              for (int j = 0; j < P; ++j) in[j] = ((lbp[j] >> (8 * d)) & 0xFFu) == code ? pw[j] : 0.f;
+              const float acc = station_total(in);
 #pragma unroll
               for (int j = 0; j < P; ++j) s[j] = ((lbp[j] >> (8 * d)) & 0xFFu) == code ? acc : s[j];
             }
@@ -901,10 +859,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       e_grid = dt * station_sum<L>(tg);
       if (C.alpha_dc != 0.0f) e_out = dt * station_sum<L>(to);
     } else {
-      float tot = 0.f;
-#pragma unroll
-      for (int j = 0; j < P; ++j) tot += pw[j];
-      tot = station_sum<L>(tot);
+      const float tot = station_total(pw);
       const bool over = tot > c_root;
       const float f = over ? c_root * frcp(tot) : 1.0f;
 #pragma unroll
@@ -913,10 +868,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       if (C.uniform_eta) {
         e_grid = e_net * inv_eta_u;
       } else {
-        float tg = 0.f;
+        float tg[P];
 #pragma unroll
-        for (int j = 0; j < P; ++j) tg += pw[j] * inv_eta[j];
-        e_grid = dt * station_sum<L>(tg);
+        for (int j = 0; j < P; ++j) tg[j] = pw[j] * inv_eta[j];
+        e_grid = dt * station_total(tg);
       }
     }
     }  // projection of classes that are not SIMPLE
@@ -953,6 +908,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // charge-sensitive one (EXT) when no energy is wanted any more
     // (c_satisfaction,1: hours overstayed - beta x hours left early)
     float csat = 0.f, csat1 = 0.f;
+    float missed[P] = {};
 #pragma unroll
     for (int j = 0; j < P; ++j) {
       const bool occ = CX_OCCUPIED(j);              // (pw = 0 on empty slots)
@@ -978,13 +934,13 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       }
       if (flags & kSat) {  // energy still wanted by a departing car (c_satisfaction,0)
         const float miss = fmaxf(0.0f, (qf[j] - u[j]) * cap[j]);
-        csat += dep0 ? miss : 0.0f;
+        missed[j] = dep0 ? miss : 0.0f;
       }
       // (an empty slot keeps its last car's values: its power and every feature
       // are masked by its being empty, an arrival overwrites them, and the state
       // goes back to HBM as zeros)
     }
-    if (flags & kSat) csat = station_sum<L>(csat);
+    if (flags & kSat) csat = station_total(missed);
     if constexpr (EXT) {
       if (users && C.alpha_sat1 != 0.0f) csat1 = station_sum<L>(csat1);
     }
@@ -1108,8 +1064,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // each store the compiler emits the scalar-base form (no 64-bit lane address)
     uint32_t obs_bo_t = obs_bo, act_bo_t = act_bo, env_bo_t = env_bo;
     asm volatile("" : "+v"(obs_bo_t), "+v"(act_bo_t), "+v"(env_bo_t));
-    // (the fused policy reads the stage from float 0: its records are 16-byte aligned)
-    const int pad = !POL && STAGE && (flags & kWObs)
+    // (the fused policy's records of a SIMPLE class are always 16-byte aligned)
+    const int pad = !(POL && SIMPLE) && STAGE && (flags & kWObs)
                         ? (int)((reinterpret_cast<uintptr_t>(ob_now + (int64_t)env_blk0 * obs_dim) >> 2) & 3u)
                         : 0;
     if (active) {
@@ -1226,9 +1182,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     if constexpr (POL) {
       // the next step's levels (the phase's barriers keep the stage until the
       // flush above has read it)
-      if (t + 1 < dy.T)
-        policy_phase<kPolSteps1>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g + 1u, k0, k1,
-                                 w_obs);
+      if (t + 1 < T) {
+        HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, kPolSteps1, HPOL> hid;
+        hid.start(w1_rsrc(), wv);
+        policy_phase<kPolSteps1, HPOL>(*pol, stage + pad, lds, obs_dim, N, blk_envs, wv, env_id0, g + 1u, k0, k1,
+                                       w_obs, hid);
+      }
     }
   }
 
@@ -1274,8 +1233,9 @@ __device__ __forceinline__ int xcd_block() {
 // One kernel per packing (lanes per station L, slots per lane P) and class
 // kind (general, SIMPLE, bidirectional), so that each keeps its own register
 // budget; the entry points below add the launch bounds of each kind.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, bool POL>
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL>
 __device__ __forceinline__ void rollout_body(LaunchArgs a) {
+  constexpr bool POL = HPOL > 0;
   extern __shared__ uint32_t lds_tdwell[];
   // (the staged kernels, whose blocks write whole runs of adjacent envs)
   const int b = STAGE ? __builtin_amdgcn_readfirstlane(xcd_block()) : (int)blockIdx.x;
@@ -1328,13 +1288,13 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   if (!POL && group >= n_groups) return;
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
   lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, POL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, stage,
+  run_group<L, P, SIMPLE, EXT, STAGE, HPOL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, stage,
                                            a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
 }
 
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
 __global__ __launch_bounds__(512) void k_rollout(LaunchArgs a) {
-  rollout_body<L, P, SIMPLE, EXT, STAGE, false>(a);
+  rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a);
 }
 
 // SIMPLE classes of 1 or 2 slots per lane: the kernel held to CX_SIMPLE_WAVES
@@ -1346,14 +1306,21 @@ __global__ __launch_bounds__(512) void k_rollout(LaunchArgs a) {
 template <int L, int P, bool STAGE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CX_SIMPLE_WAVES))) void k_rollout_simple(
     LaunchArgs a) {
-  rollout_body<L, P, true, false, STAGE, false>(a);
+  rollout_body<L, P, true, false, STAGE, 0>(a);
 }
 
 // The fused policy rollout (4 waves per block): three blocks per CU, so that
 // one block's matrix-core work and memory waits overlap the others' steps.
-template <int L, int P>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_rollout_policy(LaunchArgs a) {
-  rollout_body<L, P, true, false, true, true>(a);
+template <int L, int P, int HP>
+__global__ __launch_bounds__(64 * kPolRolloutWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_rollout_policy(LaunchArgs a) {
+  rollout_body<L, P, true, false, true, HP>(a);
+}
+// ... of classes that are not SIMPLE (padding slots, port maxima or limits that
+// differ, the dense layout): a policy rollout of the 10 DC + 6 AC station used to
+// take two launches a step.
+template <int L, int P, int HP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
+  rollout_body<L, P, false, false, true, HP>(a);
 }
 
 // Observation of empty stations at t_day = 0 for every env of one segment
@@ -1442,15 +1409,20 @@ hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_g
   return hipSuccess;
 }
 
-// The fused policy rollout of one SIMPLE class: stations of 8 lanes (8, 16 or
-// 32 slots), 4 waves per block (32 stations, two 16-env tiles of the MLP).
-hipError_t launch_policy_rollout(const LaunchArgs &a, int per_lane, int n_blocks, size_t lds, hipStream_t st) {
+// The fused policy rollout of one class: stations of 8 lanes (8, 16 or 32
+// slots), 4 waves per block (32 stations, two 16-env tiles of the MLP).  hp:
+// K-steps of 32 hidden units; the kernels are built for 2, 4 and 8 (a policy
+// of 64 hidden units does a quarter of the matrix work of one of 256).
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int per_lane, int hp, int n_blocks, size_t lds,
+                                 hipStream_t st) {
   if (n_blocks <= 0) return hipSuccess;
-  KernelFn f = per_lane == 1   ? &k_rollout_policy<8, 1>
-               : per_lane == 2 ? &k_rollout_policy<8, 2>
-               : per_lane == 4 ? &k_rollout_policy<8, 4>
-                               : nullptr;
-  if (!f) return hipErrorInvalidValue;
+#define CX_POL(K, P) {&K<8, P, 2>, &K<8, P, 4>, &K<8, P, 8>}
+  static const KernelFn kPol[2][3][3] = {
+      {CX_POL(k_rollout_policy_general, 1), CX_POL(k_rollout_policy_general, 2), CX_POL(k_rollout_policy_general, 4)},
+      {CX_POL(k_rollout_policy, 1), CX_POL(k_rollout_policy, 2), CX_POL(k_rollout_policy, 4)}};
+#undef CX_POL
+  if ((per_lane != 1 && per_lane != 2 && per_lane != 4) || hp < 1 || hp > 8) return hipErrorInvalidValue;
+  const KernelFn f = kPol[simple ? 1 : 0][per_lane == 4 ? 2 : per_lane - 1][hp <= 2 ? 0 : hp <= 4 ? 1 : 2];
   LaunchArgs b = a;
   void *params[1] = {&b};
   return hipLaunchKernel(reinterpret_cast<const void *>(f), dim3(n_blocks), dim3(64 * kPolRolloutWaves), params, lds,

@@ -69,36 +69,167 @@ __device__ __forceinline__ uint32_t draw_word(U4 w, int port) {
 }
 
 // The level drawn from softmax of a port's logits (level 4 r + i in c[r][i],
-// r < R, L1 levels): the first level whose cumulative softmax weight exceeds
-// u times the total, i.e. the inverse of the distribution function at u.  The
-// weights are 2^(z log2 e - zmax log2 e) (one fused multiply-add each); the
-// running sums kept as they are formed are the cumulative weights.
-__device__ __forceinline__ int sample_level(const f32x4 (&c)[kPolR], int R, int L1, float u) {
+// L1 levels; the levels past them have bias -inf and weights 0, so their
+// logits are -inf and their softmax weights exactly 0): the first level whose
+// cumulative softmax weight exceeds u times the total, i.e. the inverse of the
+// distribution function at u.  The weights are 2^(z log2 e - zmax log2 e) (one
+// fused multiply-add each); the running sums kept as they are formed are the
+// cumulative weights.  Straight-line code, no test per level: with the levels
+// in use selected one by one the draw took 110 vector and 35 scalar
+// instructions, now 63 vector ones.
+__device__ __forceinline__ int sample_level(const f32x4 (&c)[kPolR], int L1, float u) {
   constexpr float kLog2e = 1.44269504088896341f;
-  float zmax = c[0][0];  // level 0 always exists
+  float zmax = c[0][0];
 #pragma unroll
   for (int r = 0; r < kPolR; ++r)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (r < R && 4 * r + i < L1) zmax = c[r][i] > zmax ? c[r][i] : zmax;
+    for (int i = 0; i < 4; ++i) zmax = __builtin_elementwise_maximum(zmax, (float)c[r][i]);
   const float zs = zmax * kLog2e;
-  float cum[kPolR][4], tot = 0.f;
+  float cum[4 * kPolR];
 #pragma unroll
-  for (int r = 0; r < kPolR; ++r)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool in = r < R && 4 * r + i < L1;
-      tot += in ? __builtin_amdgcn_exp2f(__builtin_fmaf(c[r][i], kLog2e, -zs)) : 0.f;
-      cum[r][i] = tot;
-    }
-  const float target = u * tot;
+  for (int l = 0; l < 4 * kPolR; ++l) {
+    const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(c[l >> 2][l & 3], kLog2e, -zs));
+    cum[l] = l ? cum[l - 1] + w : w;
+  }
+  const float target = u * cum[4 * kPolR - 1];
   int lev = 0;
 #pragma unroll
-  for (int r = 0; r < kPolR; ++r)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) lev += (r < R && 4 * r + i < L1 - 1 && cum[r][i] <= target) ? 1 : 0;
-  return lev;
+  for (int l = 0; l < 4 * kPolR; ++l) lev += cum[l] <= target ? 1 : 0;
+  return min(lev, L1 - 1);  // (u times the total may round to the total)
 }
+
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+
+// Weight fragments come in buffer loads: one resource per matrix, the
+// fragment's offset a scalar, the lane's 16 bytes the vector offset (no 64-bit
+// addresses).  Fragments are 1 KiB and padded to the largest sizes: W1^T
+// [16 tiles][8 K-steps], W2^T [G][3 tiles][8 K-steps].
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t frag_rsrc(const u32x4 *w, int n_frags) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(w), (short)0, n_frags * 1024, 0x00020000);
+}
+// Fragment i (wave-uniform).
+__device__ __forceinline__ u32x4 frag(__amdgpu_buffer_rsrc_t w, int i) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w, 16u * (uint32_t)__lane_id(), i * 1024, 0));
+}
+
+// Both products read their weight fragments through a ring of registers two
+// K-steps deep: while step s is multiplied step s + 1 is in flight, and the ring
+// is filled before the barrier or the draw that comes first.  The scheduling
+// barriers keep the loads where they are written: left alone, the compiler
+// sinks each load to its use to save registers, and every fragment then costs
+// the L2's whole latency.  32-port stations, 262,144 x 288 steps: 39.5 ms a
+// rollout so, 34.4 ms with the ring; 35.4 at depths 1 and 2, 37.5 at 3 and 4
+// (spilled registers), 41.9 at 3 and 4 with two waves per SIMD and no spills.
+constexpr int kRing = 2;
+constexpr int ring_depth(int steps, int want) { return steps < want ? steps : want; }
+__device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
+
+// The first product of a block of W waves and 16 NT envs, with the tanh: wave wv
+// computes its pairs of 16-unit hidden tiles (HP pairs in all; with fewer pairs
+// than waves, waves share a pair and split its env tiles) from the BF16
+// observations xb (xrow fragments an env) into the hidden-unit fragments hb
+// [HP][NT][64].  K1 K-steps of 32 features.
+template <int W, int NT, int K1, int HP>
+struct HiddenLayer {
+  static constexpr int NI = HP >= W ? HP / W : 1;   // pairs of this wave
+  static constexpr int SH = HP >= W ? 1 : W / HP;   // waves that share a pair
+  static constexpr int NN = SH <= NT ? NT / SH : 1; // env tiles of this wave
+  static constexpr int D = ring_depth(K1, kRing);
+  u32x4 a[D][NI][2];
+
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t w1, int wv, int s) {
+    const int mp0 = SH == 1 ? wv : wv % HP;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) a[s % D][i][h] = frag(w1, (2 * (mp0 + W * i) + h) * kPolK1 + s);
+  }
+  // the first K-steps' fragments, ahead of run()
+  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w1, int wv) {
+    pin();
+#pragma unroll
+    for (int s = 0; s < D; ++s) load(w1, wv, s);
+    pin();
+  }
+  __device__ __forceinline__ void run(__amdgpu_buffer_rsrc_t w1, const float *b1, const lds_u32x4 *xb, int xrow,
+                                      lds_u32x4 *hb, int wv) {
+    const int lane = __lane_id(), col = lane & 15, lg = lane >> 4;
+    const int mp0 = SH == 1 ? wv : wv % HP, n0 = SH == 1 ? 0 : (wv / HP) * NN;
+    if (n0 >= NT) return;
+    f32x4 c[NI][2][NN];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int n = 0; n < NN; ++n) c[i][0][n] = c[i][1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < K1; ++s) {
+#pragma unroll
+      for (int n = 0; n < NN; ++n) {
+        const u32x4 b = xb[(16 * (n0 + n) + col) * xrow + 4 * s + lg];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          c[i][0][n] = mfma_bf16(a[s % D][i][0], b, c[i][0][n]);
+          c[i][1][n] = mfma_bf16(a[s % D][i][1], b, c[i][1][n]);
+        }
+      }
+      pin();
+      if (s + D < K1) load(w1, wv, s + D);
+      pin();
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int mp = mp0 + W * i;
+      const f32x4 bA = gld(reinterpret_cast<const f32x4 *>(b1 + 32 * mp + 4 * lg), 0);
+      const f32x4 bB = gld(reinterpret_cast<const f32x4 *>(b1 + 32 * mp + 16 + 4 * lg), 0);
+#pragma unroll
+      for (int n = 0; n < NN; ++n) hb[(mp * NT + n0 + n) * 64 + lane] = hidden_frag(c[i][0][n], c[i][1][n], bA, bB);
+    }
+  }
+};
+
+// The logits of port groups grp (4 ports) for 16 NT envs: c[r][n] holds levels
+// 4 r .. 4 r + 3 of port 4 grp + lane / 16 of env 16 n + lane % 16.  run()
+// leaves the first K-steps of group `next` in flight.
+template <int NT, int HP>
+struct LogitLayer {
+  static constexpr int D = ring_depth(HP, kRing);   // divides HP
+  u32x4 w[D][kPolR];
+
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t w2, int grp, int s) {
+#pragma unroll
+    for (int r = 0; r < kPolR; ++r) w[s % D][r] = frag(w2, (grp * kPolR + r) * kPolHP + s);
+  }
+  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w2, int grp) {
+    pin();
+#pragma unroll
+    for (int s = 0; s < D; ++s) load(w2, grp, s);
+    pin();
+  }
+  __device__ __forceinline__ void run(__amdgpu_buffer_rsrc_t w2, const float *b2f, const lds_u32x4 *hb, int grp, int next,
+                                      f32x4 (&c)[kPolR][NT]) {
+    const int lane = __lane_id(), lg = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < kPolR; ++r) {
+      const f32x4 b = gld(reinterpret_cast<const f32x4 *>(b2f + (int64_t)(grp * kPolR + r) * 16 + 4 * lg), 0);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) c[r][n] = b;
+    }
+#pragma unroll
+    for (int s = 0; s < HP; ++s) {
+      u32x4 hv[NT];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) hv[n] = hb[(s * NT + n) * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < kPolR; ++r)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) c[r][n] = mfma_bf16(w[s % D][r], hv[n], c[r][n]);
+      pin();
+      if (s + D < HP) load(w2, grp, s + D);
+      else load(w2, next, s + D - HP);
+      pin();
+    }
+  }
+};
 
 }  // namespace
 }  // namespace cx

@@ -2,7 +2,7 @@
 //   k_policy  obs -> BF16 -> W1 (tanh) -> W2 -> logits on the matrix cores
 //             (v_mfma_f32_16x16x32_bf16, FP32 accumulation), then per port a
 //             level drawn from softmax of its logits with one Philox uniform.
-// A rollout of a SIMPLE class of 8, 16 or 32 slots is one launch of the fused
+// A rollout of a class of 8, 16 or 32 slots is one launch of the fused
 // persistent kernel (the rollout kernel with this MLP between its steps,
 // cx_kernels.hip): state in registers, observations only in LDS.  Other
 // classes, and the rollout that allocates nothing, run two kernels per step:
@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <vector>
 
@@ -25,20 +26,13 @@
 
 namespace cx {
 
-constexpr int kPolNT = 2;  // 16-env column tiles per wave
-constexpr int kPolWaves = 8;  // waves per block sharing each staged weight chunk
-
 struct PolicyRt {
   int hidden = 0, in_dim = 0, N = 0, L1 = 0;
   int K1 = 0, HP = 0, R = 0, G = 0;
-  void *mem = nullptr;  // weights in fragment order + FP32 biases
-  const u32x4 *w1f = nullptr;
-  const float *b1 = nullptr;
-  const u32x4 *w2f = nullptr;
-  const float *b2f = nullptr;
-  // the same weights padded to the largest sizes (zeros), for the fused
-  // rollout: W1^T [16 tiles][8 K-steps][64], b1 [256], W2^T [G][3][8][64],
-  // b2 [G][3][16]
+  // weights in fragment order and FP32 biases, padded to the largest sizes
+  // (zeros; -inf for the biases of levels past the class's): W1^T [16 tiles][8
+  // K-steps][64], b1 [256], W2^T [G][3][8][64], b2 [G][3][16]
+  void *mem = nullptr;
   const u32x4 *w1p = nullptr;
   const float *b1p = nullptr;
   const u32x4 *w2p = nullptr;
@@ -53,178 +47,136 @@ struct PolicyRt {
 
 namespace {
 
-// Weight chunks pass through LDS, double-buffered: chunk c < HP holds the two
-// W1^T tiles of hidden units 32c..32c+31 (all K-steps), chunk HP + g the R
-// tiles of W2^T of port group g.  Every wave of the block reads each chunk, so
-// a weight byte leaves L2 once per 16 * kPolNT * kPolWaves envs.
-constexpr int kChunkMax = 3 * kPolHP * 64;  // u32x4 per chunk (R * HP or 2 * K1 tiles of 64 lanes)
-constexpr int kPerThread = kChunkMax / (64 * kPolWaves);
-
-__device__ __forceinline__ void chunk_src(const PolicyArgs &a, int c, const u32x4 *&src, int &cnt) {
-  if (c < a.HP) {
-    src = a.w1f + (int64_t)(2 * c) * a.K1 * 64;
-    cnt = 2 * a.K1 * 64;
-  } else {
-    src = a.w2f + (int64_t)(c - a.HP) * a.R * a.HP * 64;
-    cnt = a.R * a.HP * 64;
-  }
-}
-
-__device__ __forceinline__ void fetch_chunk(const PolicyArgs &a, int c, u32x4 (&r)[kPerThread]) {
-  const u32x4 *src;
-  int cnt;
-  chunk_src(a, c, src, cnt);
-#pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {
-    const int idx = (int)threadIdx.x + i * 64 * kPolWaves;
-    if (idx < cnt) r[i] = gld(src, idx);
-  }
-}
-
-__device__ __forceinline__ void put_chunk(const PolicyArgs &a, int c, const u32x4 (&r)[kPerThread], u32x4 *buf) {
-  const u32x4 *src;
-  int cnt;
-  chunk_src(a, c, src, cnt);
-#pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {
-    const int idx = (int)threadIdx.x + i * 64 * kPolWaves;
-    if (idx < cnt) buf[idx] = r[i];
-  }
-}
-
-__global__ __launch_bounds__(64 * kPolWaves) void k_policy(PolicyArgs a) {
-  __shared__ u32x4 wbuf[2][kChunkMax];
-  const int lane = __lane_id();
+// One block of the standalone policy kernel: W waves, E = 16 NT observations.
+// They are converted to BF16 fragments in LDS; the waves split the hidden units,
+// then the port groups, as in the fused rollout, and read their weight
+// fragments from L2 straight into the matrix-core operands.
+template <int W, int NT, int K1, int HP>
+__device__ __forceinline__ void policy_block(const PolicyArgs &a, lds_u32x4 *xb, lds_u32x4 *hb) {
+  constexpr int E = 16 * NT, CPR = 4 * K1, XR = kPolXbRow;
+  const int tid = threadIdx.x, lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, lg = lane >> 4;
-  const int64_t wave = (int64_t)blockIdx.x * kPolWaves + (threadIdx.x >> 6);
-  const int64_t e_base = wave * 16 * kPolNT;  // waves past the end still take part in the barriers
-  const int n_chunks = a.HP + a.G;
-  u32x4 pf[kPerThread];
-  fetch_chunk(a, 0, pf);
-  put_chunk(a, 0, pf, wbuf[0]);
-
-  // ---- B operand of the first product: 8 consecutive features of one env
-  u32x4 ob[kPolK1][kPolNT];
-#pragma unroll
-  for (int s = 0; s < kPolK1; ++s) {
-#pragma unroll
-    for (int n = 0; n < kPolNT; ++n) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      const int64_t e = e_base + 16 * n + col;
-      const int f = 32 * s + 8 * lg;
-      if (s < a.K1 && e < a.n && f < a.in_dim) {
-        const float *row = a.obs + e * a.in_dim + f;
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 x = gld(reinterpret_cast<const f4 *>(row), 0);
-        f4 y = {0.f, 0.f, 0.f, 0.f};
-        if (f + 4 < a.in_dim) y = gld(reinterpret_cast<const f4 *>(row + 4), 0);
+  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int n_e = (int)(a.n - e0 < E ? a.n - e0 : E);
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  const __amdgpu_buffer_rsrc_t w1 = frag_rsrc(a.w1f, 2 * kPolHP * kPolK1);
+  HiddenLayer<W, NT, K1, HP> hid;
+  hid.start(w1, wv);
+  const float *obs = a.obs + e0 * a.in_dim;
+  for (int c = tid; c < E * CPR; c += 64 * W) {
+    const int e = c / CPR, k = c % CPR, f = 8 * k;
+    const float *row = obs + (int64_t)e * a.in_dim + f;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (e < n_e) {
+      if (f + 8 <= a.in_dim) {
+        const f4u x = gld(reinterpret_cast<const f4u *>(row), 0), y = gld(reinterpret_cast<const f4u *>(row + 4), 0);
         v = u32x4{pack2(x.x, x.y), pack2(x.z, x.w), pack2(y.x, y.y), pack2(y.z, y.w)};
+      } else if (f < a.in_dim) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = f + j < a.in_dim ? gld(row, j) : 0.f;
+        v = u32x4{pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7])};
       }
-      ob[s][n] = v;
     }
+    xb[e * XR + k] = v;
   }
   __syncthreads();
-
-  // ---- first product, 32 hidden units (two 16-row tiles, one chunk) at a time
-  u32x4 h[kPolHP][kPolNT];
+  hid.run(w1, a.b1, xb, XR, hb, wv);
+  const __amdgpu_buffer_rsrc_t w2 = frag_rsrc(a.w2f, a.G * kPolR * kPolHP);
+  LogitLayer<NT, HP> logit;
+  logit.start(w2, min(wv, a.G - 1));
+  // the lane's ports are 4 wv + lg + 4 W i, a multiple of 16 apart: one Philox
+  // call per observation serves them all
+  U4 dw[NT];
+  if (a.act) {
 #pragma unroll
-  for (int mp = 0; mp < kPolHP; ++mp) {
-#pragma unroll
-    for (int n = 0; n < kPolNT; ++n) h[mp][n] = u32x4{0u, 0u, 0u, 0u};
-    if (mp < a.HP) {
-      if (mp + 1 < n_chunks) fetch_chunk(a, mp + 1, pf);
-      const u32x4 *w = wbuf[mp & 1];
-      f32x4 c0[kPolNT], c1[kPolNT];
-#pragma unroll
-      for (int n = 0; n < kPolNT; ++n) {
-        c0[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        c1[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-      for (int s = 0; s < kPolK1; ++s) {
-        if (s < a.K1) {
-          const u32x4 a0 = w[s * 64 + lane];
-          const u32x4 a1 = w[(a.K1 + s) * 64 + lane];
-#pragma unroll
-          for (int n = 0; n < kPolNT; ++n) {
-            c0[n] = mfma_bf16(a0, ob[s][n], c0[n]);
-            c1[n] = mfma_bf16(a1, ob[s][n], c1[n]);
-          }
-        }
-      }
-      if (mp + 1 < n_chunks) put_chunk(a, mp + 1, pf, wbuf[(mp + 1) & 1]);
-      const f32x4 bA = gld(reinterpret_cast<const f32x4 *>(a.b1 + 32 * mp + 4 * lg), 0);
-      const f32x4 bB = gld(reinterpret_cast<const f32x4 *>(a.b1 + 32 * mp + 16 + 4 * lg), 0);
-#pragma unroll
-      for (int n = 0; n < kPolNT; ++n) h[mp][n] = hidden_frag(c0[n], c1[n], bA, bB);
-      __syncthreads();
-    }
+    for (int n = 0; n < NT; ++n)
+      dw[n] = philox((uint32_t)(a.env0 + e0 + 16 * n + col), a.g, draw_index(4 * wv + lg), kDomGum, (uint32_t)a.seed,
+                     (uint32_t)(a.seed >> 32));
   }
-
-  // ---- second product per group of 4 ports (one chunk each), then a level
-  // per port drawn from softmax of its logits
-  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  const int out_dim = a.N * a.L1;
-  for (int grp = 0; grp < a.G; ++grp) {
-    const int cidx = a.HP + grp;
-    const int port = 4 * grp + lg;
-    if (cidx + 1 < n_chunks) fetch_chunk(a, cidx + 1, pf);
-    // the uniform of this port's draw: independent of the products, so it is
-    // computed in the same straight-line block as the matrix-core work and the
-    // two overlap (lanes past the last env or port compute unused draws)
-    float ud[kPolNT];
+  __syncthreads();
+  // Levels and logits gather in LDS, over the observations, which are no longer
+  // needed.  The levels leave as one contiguous run at the end; the logits of one
+  // tile (16 observations) and W port groups leave together, each observation's
+  // 4 W L1 floats (704 bytes at W = 4 and 11 levels) by one wave in 16-byte
+  // stores: stored from the lanes that hold them, 44 bytes a lane at that
+  // stride, 65,537 x 352 logits took 72 us a call, of which 29 the stores.
+  __attribute__((address_space(3))) uint8_t *lev = (__attribute__((address_space(3))) uint8_t *)xb;
+  __attribute__((address_space(3))) float *zs = (__attribute__((address_space(3))) float *)xb;
+  constexpr int ZR = 4 * W * 4 * kPolR + 4;   // floats per observation's row
+  static_assert(16 * ZR * 4 <= E * XR * 16, "the logits of a tile fit over the observations");
+  for (int g0 = 0; g0 < a.G; g0 += W) {
+    const int grp = min(g0 + wv, a.G - 1), port = 4 * (g0 + wv) + lg;
+    f32x4 c[kPolR][NT];
+    logit.run(w2, a.b2f, hb, grp, min(g0 + W + wv, a.G - 1), c);
+    if (a.logits) {
+      const int n_z = min(4 * W, a.N - 4 * g0) * a.L1;   // floats per observation of these groups
 #pragma unroll
-    for (int n = 0; n < kPolNT; ++n) {
-      const uint32_t env_id = (uint32_t)(a.env0 + e_base + 16 * n + col);
-      const U4 w = philox(env_id, a.g, draw_index(port), kDomGum, k0, k1);
-      ud[n] = draw_uniform(draw_word(w, port));
-    }
-    const u32x4 *w = wbuf[cidx & 1];
-    f32x4 c[kPolR][kPolNT];
+      for (int n = 0; n < NT; ++n) {
+        if (port < a.N) {
+          __attribute__((address_space(3))) float *z = zs + col * ZR + (4 * wv + lg) * a.L1;
 #pragma unroll
-    for (int r = 0; r < kPolR; ++r) {
-      f32x4 b = {0.f, 0.f, 0.f, 0.f};
-      if (r < a.R) b = gld(reinterpret_cast<const f32x4 *>(a.b2f + (int64_t)(grp * a.R + r) * 16 + 4 * lg), 0);
-#pragma unroll
-      for (int n = 0; n < kPolNT; ++n) c[r][n] = b;
-    }
-#pragma unroll
-    for (int s = 0; s < kPolHP; ++s) {
-      if (s < a.HP) {
-#pragma unroll
-        for (int r = 0; r < kPolR; ++r) {
-          if (r < a.R) {
-            const u32x4 wf = w[(r * a.HP + s) * 64 + lane];
-#pragma unroll
-            for (int n = 0; n < kPolNT; ++n) c[r][n] = mfma_bf16(wf, h[s][n], c[r][n]);
-          }
+          for (int l = 0; l < 4 * kPolR; ++l)
+            if (l < a.L1) z[l] = c[l >> 2][n][l & 3];
         }
+        __syncthreads();
+        for (int r = wv; r < 16 && 16 * n + r < n_e; r += W) {
+          float *out = a.logits + (e0 + 16 * n + r) * ((int64_t)a.N * a.L1) + (int64_t)4 * g0 * a.L1;
+          const __attribute__((address_space(3))) float *row = zs + r * ZR;
+          for (int i = 4 * lane; i + 4 <= n_z; i += 256)
+            gst(reinterpret_cast<f4u *>(out + i), 0, (f4u){row[i], row[i + 1], row[i + 2], row[i + 3]});
+          const int i = (n_z & ~3) + lane;
+          if (i < n_z) gst(out, i, (float)row[i]);
+        }
+        __syncthreads();
       }
     }
-    if (cidx + 1 < n_chunks) put_chunk(a, cidx + 1, pf, wbuf[(cidx + 1) & 1]);
-    __syncthreads();
+    if (a.act && port < a.N) {
 #pragma unroll
-    for (int n = 0; n < kPolNT; ++n) {
-      const int64_t e = e_base + 16 * n + col;
-      if (port >= a.N || e >= a.n) continue;
-      if (a.logits) {
-        float *z = a.logits + e * out_dim + (int64_t)port * a.L1;
-#pragma unroll
-        for (int r = 0; r < kPolR; ++r) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int lev = 4 * r + i;
-            if (r < a.R && lev < a.L1) z[lev] = c[r][n][i];
-          }
-        }
-      }
-      if (a.act) {
+      for (int n = 0; n < NT; ++n) {
         const f32x4 cn[kPolR] = {c[0][n], c[1][n], c[2][n]};
-        const int lev = sample_level(cn, a.R, a.L1, ud[n]);
-        a.act[e * a.N + port] = (uint8_t)lev;
+        lev[(16 * n + col) * a.N + port] = (uint8_t)sample_level(cn, a.L1, draw_uniform(draw_word(dw[n], port)));
       }
     }
   }
+  if (!a.act) return;
+  __syncthreads();
+  uint8_t *out = a.act + e0 * a.N;
+  const int bytes = n_e * a.N;
+  if ((reinterpret_cast<uintptr_t>(out) & 3u) == 0) {
+    for (int i = tid; i < bytes >> 2; i += 64 * W)
+      gst(reinterpret_cast<uint32_t *>(out), i, *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(lev + 4 * i));
+    const int i = (bytes & ~3) + tid;
+    if (i < bytes) gst(out, i, (uint8_t)lev[i]);
+  } else {
+    for (int i = tid; i < bytes; i += 64 * W) gst(out, i, (uint8_t)lev[i]);
+  }
+}
+
+template <int W, int NT>
+__device__ __forceinline__ void policy_sizes(const PolicyArgs &a, lds_u32x4 *xb, lds_u32x4 *hb) {
+  if (a.K1 <= 4) {  // up to 128 features (20 ports)
+    if (a.HP <= 2) policy_block<W, NT, 4, 2>(a, xb, hb);
+    else if (a.HP <= 4) policy_block<W, NT, 4, 4>(a, xb, hb);
+    else policy_block<W, NT, 4, 8>(a, xb, hb);
+  } else {
+    if (a.HP <= 2) policy_block<W, NT, 8, 2>(a, xb, hb);
+    else if (a.HP <= 4) policy_block<W, NT, 8, 4>(a, xb, hb);
+    else policy_block<W, NT, 8, 8>(a, xb, hb);
+  }
+}
+
+// 32 observations per block, whatever their number: 65,537 observations (32
+// ports, 256 hidden units) take 43 us a draw; blocks of 64 take 46, of 16 62, and
+// the blocks of 256 that this kernel had, one per CU and one block too many,
+// 137.  300 observations: 11 us, 63 before.
+constexpr int kPolWaves = 4, kPolNT = 2;
+constexpr size_t kPolLds = (size_t)16 * kPolNT * kPolXbRow * 16 + (size_t)kPolHP * kPolNT * 1024;
+
+__global__ __launch_bounds__(64 * kPolWaves) void k_policy(PolicyArgs a) {
+  extern __shared__ u32x4 pol_lds[];
+  lds_u32x4 *xb = (lds_u32x4 *)pol_lds;
+  policy_sizes<kPolWaves, kPolNT>(a, xb, xb + 16 * kPolNT * kPolXbRow);
 }
 
 // Observation of the current state (the features the step kernel records).
@@ -281,10 +233,9 @@ __global__ void k_observe(const ClassDev *cls, int64_t n_envs, const double *q, 
 }
 
 hipError_t launch_policy(const PolicyArgs &a, hipStream_t st) {
-  const int64_t waves = (a.n + 16 * kPolNT - 1) / (16 * kPolNT);
-  const int64_t blocks = (waves + kPolWaves - 1) / kPolWaves;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_policy, dim3((unsigned)blocks), dim3(64 * kPolWaves), 0, st, a);
+  if (a.n <= 0) return hipSuccess;
+  const int64_t blocks = (a.n + 16 * kPolNT - 1) / (16 * kPolNT);
+  hipLaunchKernelGGL(k_policy, dim3((unsigned)blocks), dim3(64 * kPolWaves), kPolLds, st, a);
   return hipGetLastError();
 }
 
@@ -309,7 +260,7 @@ PolicyArgs policy_args(const cx_ctx *ctx, const float *obs, int64_t n) {
   a.obs = obs;
   a.n = n;
   a.in_dim = p.in_dim; a.K1 = p.K1; a.HP = p.HP; a.R = p.R; a.G = p.G; a.N = p.N; a.L1 = p.L1;
-  a.w1f = p.w1f; a.b1 = p.b1; a.w2f = p.w2f; a.b2f = p.b2f;
+  a.w1f = p.w1p; a.b1 = p.b1p; a.w2f = p.w2p; a.b2f = p.b2p;
   a.seed = ctx->seed;
   a.env0 = ctx->classes[0].env_begin;
   return a;
@@ -436,12 +387,12 @@ cx_status noalloc_scratch(int device, unsigned char **ptr) {
 
 namespace {
 
-// The fused rollout runs SIMPLE classes of 8, 16 or 32 slots (stations of 8
-// lanes, 1, 2 or 4 slots per lane); others take the two kernels per step.
+// The fused rollout runs classes of 8, 16 or 32 slots (stations of 8 lanes, 1, 2
+// or 4 slots per lane); larger ones take the two kernels per step.
 bool fused_eligible(const cx_ctx *ctx) {
   const ClassRt &c = ctx->classes[0];
   const int S = c.comp.S;
-  return c.host_view.kind == kKindSimple && (S == 8 || S == 16 || S == 32);
+  return c.host_view.kind != kKindExt && (S == 8 || S == 16 || S == 32);
 }
 
 cx_status ensure_fused(cx_ctx *ctx) {
@@ -472,7 +423,7 @@ cx_status ensure_fused(cx_ctx *ctx) {
 // One launch for the whole rollout: the observation the rollout starts from
 // (into the scratch), then the persistent kernel with the MLP between steps.
 cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_traj *out, size_t lds,
-                        const LaunchArgs::Pol &lay) {
+                        int32_t stage_floats, const LaunchArgs::Pol &lay) {
   PolicyRt &p = *ctx->policy;
   const ClassRt &c = ctx->classes[0];
   const bool ret_obs = out && out_mode == CX_OUT_FULL && out->obs;
@@ -491,7 +442,7 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.done = out ? out->done : nullptr;
   a.lds_tdwell = 1;
   a.stage_off = lay.hb_off;
-  a.stage_floats = (int32_t)(((size_t)kPolRolloutEnvs * c.comp.obs_dim + 3) & ~(size_t)3);
+  a.stage_floats = stage_floats;
   a.pol = lay;
   a.pol.obs0 = p.obs;
   a.pol.w1f = p.w1p;
@@ -504,7 +455,8 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.pol.R = p.R;
   a.pol.G = p.G;
   a.pol.L1 = p.L1;
-  if ((e = launch_policy_rollout(a, c.comp.S / 8, p.n_blocks, lds, ctx->stream)) != hipSuccess)
+  if ((e = launch_policy_rollout(a, c.host_view.kind == kKindSimple, c.comp.S / 8, p.HP, p.n_blocks, lds,
+                                 ctx->stream)) != hipSuccess)
     return hip_fail(ctx, e, "policy rollout kernel");
   advance_clock(ctx, T);
   return CX_OK;
@@ -529,7 +481,7 @@ cx_status policy_step(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_tra
     if (lds <= kMaxBlockLds) {
       if (T == 0) return CX_OK;
       if ((st = ensure_fused(ctx)) != CX_OK) return st;
-      return fused_rollout(ctx, T, out_mode, out, lds, lay);
+      return fused_rollout(ctx, T, out_mode, out, lds, stage_floats, lay);
     }
   }
   return policy_step_with(ctx, T, out_mode, out, ctx->policy->obs, ctx->policy->act);
@@ -558,29 +510,31 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
   if (L1 > 4 * kPolR) return fail_status(CX_E_INVALID, "cx_set_policy: at most 11 levels per port");
   const int K1 = (in_dim + 31) / 32, HP = hidden / 32, R = (L1 + 3) / 4, G = (N + 3) / 4;
   const int out_dim = N * L1;
-  // W1^T fragments: tile m (hidden 16m..16m+15), K-step s, lane l -> hidden
-  // 16m + l % 16, features 32s + 8 (l / 16) + j
-  std::vector<uint16_t> w1f((size_t)2 * HP * K1 * 64 * 8, 0);
+  // W1^T fragments: tile m (hidden 16m..16m+15), K-step s at (m * 8 + s), lane l
+  // -> hidden 16m + l % 16, features 32s + 8 (l / 16) + j
+  std::vector<uint16_t> w1p((size_t)2 * kPolHP * kPolK1 * 64 * 8, 0);
   for (int m = 0; m < 2 * HP; ++m)
     for (int s = 0; s < K1; ++s)
       for (int l = 0; l < 64; ++l)
         for (int j = 0; j < 8; ++j) {
           const int f = 32 * s + 8 * (l >> 4) + j, hu = 16 * m + (l & 15);
-          if (f < in_dim) w1f[(((size_t)m * K1 + s) * 64 + l) * 8 + j] = w1[(size_t)f * hidden + hu];
+          if (f < in_dim) w1p[(((size_t)m * kPolK1 + s) * 64 + l) * 8 + j] = w1[(size_t)f * hidden + hu];
         }
-  std::vector<float> b1f(hidden);
-  for (int j = 0; j < hidden; ++j) b1f[j] = (float)bf16_to_double(b1[j]);
-  // W2^T fragments: tile (grp, r), K-step s, lane l -> row l % 16 = port
-  // 4 grp + (l % 16) / 4, level 4 r + l % 4; slot j -> hidden unit in the
-  // order the first product leaves them in a lane
-  std::vector<uint16_t> w2f((size_t)G * R * HP * 64 * 8, 0);
-  std::vector<float> b2f((size_t)G * R * 16, 0.f);
+  std::vector<float> b1p((size_t)32 * kPolHP, 0.f);
+  for (int j = 0; j < hidden; ++j) b1p[j] = (float)bf16_to_double(b1[j]);
+  // W2^T fragments: tile (grp, r), K-step s at ((grp * 3 + r) * 8 + s), lane l ->
+  // row l % 16 = port 4 grp + (l % 16) / 4, level 4 r + l % 4; slot j -> hidden
+  // unit in the order the first product leaves them in a lane.  Levels past the
+  // class's have weights 0 and bias -inf: the draw never takes them.
+  std::vector<uint16_t> w2p((size_t)G * kPolR * kPolHP * 64 * 8, 0);
+  std::vector<float> b2p((size_t)G * kPolR * 16, 0.f);
   for (int grp = 0; grp < G; ++grp)
-    for (int r = 0; r < R; ++r) {
-      const int tile = grp * R + r;
+    for (int r = 0; r < kPolR; ++r) {
+      const int tile = grp * kPolR + r;
       for (int row = 0; row < 16; ++row) {
         const int port = 4 * grp + (row >> 2), lev = 4 * r + (row & 3);
-        if (port < N && lev < L1) b2f[(size_t)tile * 16 + row] = (float)bf16_to_double(b2[port * L1 + lev]);
+        if (lev >= L1) b2p[(size_t)tile * 16 + row] = -std::numeric_limits<float>::infinity();
+        else if (port < N) b2p[(size_t)tile * 16 + row] = (float)bf16_to_double(b2[port * L1 + lev]);
       }
       for (int s = 0; s < HP; ++s)
         for (int l = 0; l < 64; ++l) {
@@ -590,42 +544,19 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
           const int o = port * L1 + lev;
           for (int j = 0; j < 8; ++j) {
             const int hu = 32 * s + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
-            w2f[((((size_t)tile * HP + s) * 64 + l) * 8) + j] = w2[(size_t)hu * out_dim + o];
+            w2p[((((size_t)tile * kPolHP + s) * 64 + l) * 8) + j] = w2[(size_t)hu * out_dim + o];
           }
         }
     }
-  // padded copies: W1^T tile m, K-step s at (m * 8 + s); W2^T tile (grp, r),
-  // K-step s at ((grp * 3 + r) * 8 + s)
-  std::vector<uint16_t> w1p((size_t)2 * kPolHP * kPolK1 * 64 * 8, 0);
-  for (int m = 0; m < 2 * HP; ++m)
-    for (int s = 0; s < K1; ++s)
-      std::memcpy(&w1p[((size_t)m * kPolK1 + s) * 64 * 8], &w1f[((size_t)m * K1 + s) * 64 * 8], 64 * 8 * 2);
-  std::vector<float> b1p((size_t)32 * kPolHP, 0.f);
-  std::memcpy(b1p.data(), b1f.data(), (size_t)hidden * 4);
-  std::vector<uint16_t> w2p((size_t)G * kPolR * kPolHP * 64 * 8, 0);
-  std::vector<float> b2p((size_t)G * kPolR * 16, 0.f);
-  for (int grp = 0; grp < G; ++grp)
-    for (int r = 0; r < R; ++r) {
-      std::memcpy(&b2p[((size_t)grp * kPolR + r) * 16], &b2f[((size_t)grp * R + r) * 16], 16 * 4);
-      for (int s = 0; s < HP; ++s)
-        std::memcpy(&w2p[(((size_t)grp * kPolR + r) * kPolHP + s) * 64 * 8],
-                    &w2f[(((size_t)grp * R + r) * HP + s) * 64 * 8], 64 * 8 * 2);
-    }
-  const size_t s_w1 = w1f.size() * 2, s_b1 = (size_t)hidden * 4, s_w2 = w2f.size() * 2, s_b2 = b2f.size() * 4;
   const size_t s_w1p = w1p.size() * 2, s_b1p = b1p.size() * 4, s_w2p = w2p.size() * 2, s_b2p = b2p.size() * 4;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t o_w1p = al(s_w1) + al(s_b1) + al(s_w2) + al(s_b2);
-  const size_t o_b1p = o_w1p + al(s_w1p), o_w2p = o_b1p + al(s_b1p), o_b2p = o_w2p + al(s_w2p);
+  const size_t o_b1p = al(s_w1p), o_w2p = o_b1p + al(s_b1p), o_b2p = o_w2p + al(s_w2p);
   const size_t bytes = o_b2p + al(s_b2p);
   void *mem = nullptr;
   if (hipMalloc(&mem, bytes) != hipSuccess) return fail_status(CX_E_OOM, "cx_set_policy: hipMalloc failed");
   unsigned char *b = static_cast<unsigned char *>(mem);
   hipError_t e;
-  if ((e = hipMemcpy(b, w1f.data(), s_w1, hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMemcpy(b + al(s_w1), b1f.data(), s_b1, hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMemcpy(b + al(s_w1) + al(s_b1), w2f.data(), s_w2, hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMemcpy(b + al(s_w1) + al(s_b1) + al(s_w2), b2f.data(), s_b2, hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMemcpy(b + o_w1p, w1p.data(), s_w1p, hipMemcpyHostToDevice)) != hipSuccess ||
+  if ((e = hipMemcpy(b, w1p.data(), s_w1p, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(b + o_b1p, b1p.data(), s_b1p, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(b + o_w2p, w2p.data(), s_w2p, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(b + o_b2p, b2p.data(), s_b2p, hipMemcpyHostToDevice)) != hipSuccess) {
@@ -642,11 +573,7 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
   p->hidden = hidden; p->in_dim = in_dim; p->N = N; p->L1 = L1;
   p->K1 = K1; p->HP = HP; p->R = R; p->G = G;
   p->mem = mem;
-  p->w1f = reinterpret_cast<const u32x4 *>(b);
-  p->b1 = reinterpret_cast<const float *>(b + al(s_w1));
-  p->w2f = reinterpret_cast<const u32x4 *>(b + al(s_w1) + al(s_b1));
-  p->b2f = reinterpret_cast<const float *>(b + al(s_w1) + al(s_b1) + al(s_w2));
-  p->w1p = reinterpret_cast<const u32x4 *>(b + o_w1p);
+  p->w1p = reinterpret_cast<const u32x4 *>(b);
   p->b1p = reinterpret_cast<const float *>(b + o_b1p);
   p->w2p = reinterpret_cast<const u32x4 *>(b + o_w2p);
   p->b2p = reinterpret_cast<const float *>(b + o_b2p);
