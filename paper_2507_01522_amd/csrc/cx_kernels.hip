@@ -1,8 +1,10 @@
 // cx_kernels.hip -- gfx950 kernels of the batched EV charging-station step.
 //
 // One station occupies L lanes of a 64-wide wavefront and each lane holds P
-// slots (L * P = the station's padded slot count); a wave carries 64 / L
-// stations.  Slot s of a station lives in lane s % L, register s / L.  A wave
+// adjacent slots (L * P = the station's padded slot count); a wave carries 64 / L
+// stations.  Slot s of a station lives in lane s / P, register s % P: blocks of up
+// to P slots are summed inside a lane, and a lane's values of one feature are
+// one 8- or 16-byte store (with slots L apart, P stores of 4 bytes).  A wave
 // runs its stations for T steps with the whole state in registers and writes
 // the per-step records out; the plain one-step form is the same kernel with
 // T = 1.  Per step (App. A.2 order):
@@ -93,6 +95,22 @@ __device__ __forceinline__ float xlane(float v) {
     return __int_as_float((__lane_id() & 32) ? r[0] : r[1]);
   }
   return v;
+}
+
+// The value of the lane whose index differs in bit K, whatever the lanes in
+// between hold (xlane<2> and <3> take the mirrored lane, which holds the same
+// only after the steps below K).
+template <int K>
+__device__ __forceinline__ float xor_lane(float v) {
+  const int iv = __float_as_int(v);
+  if constexpr (K == 2) {  // l ^ 7, then l ^ 3
+    const int m = __builtin_amdgcn_update_dpp(0, iv, 0x141, 0xF, 0xF, true);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true));
+  } else if constexpr (K == 3) {  // rotate the row of 16 by 8
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, iv, 0x128, 0xF, 0xF, true));
+  } else {
+    return xlane<K>(v);
+  }
 }
 
 // One butterfly step of a sum: v plus the value of the lane whose index
@@ -219,6 +237,22 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
 typedef __attribute__((address_space(3))) f32x4u lds_f32x4u;
+// P floats at any float's address
+template <int P>
+struct FVec;
+template <>
+struct FVec<1> { typedef float type; };
+template <>
+struct FVec<2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+template <>
+struct FVec<4> { typedef f32x4u type; };
+template <int P>
+using fvec = typename FVec<P>::type;
+template <class V>
+__device__ __forceinline__ void set_at(V &x, int j, float v) {
+  if constexpr (sizeof(V) == 4) x = v;
+  else x[j] = v;
+}
 
 // Write n staged floats to dst (4-byte aligned).  The stage holds them from
 // float pad = (dst / 4) mod 4 on, so that LDS and HBM agree on 16-byte chunks:
@@ -358,6 +392,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
                                           int stage_floats, int g_blk0, int n_run,
                                           const LaunchArgs::Pol *pol = nullptr, lds_char *lds = nullptr) {
   constexpr int SPW = 64 / L;
+  constexpr int LOGP = P == 1 ? 0 : P == 2 ? 1 : 2;
   constexpr int LOGL = (L == 4) ? 2 : (L == 8) ? 3 : (L == 16) ? 4 : (L == 32) ? 5 : 6;
   constexpr bool NOPAD = SIMPLE;  // every slot holds a port: slot s = port s
   constexpr bool POL = HPOL > 0;
@@ -390,7 +425,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   uint32_t lbp[P];
 #pragma unroll
   for (int j = 0; j < P; ++j) {
-    const int s = j * L + l;
+    const int s = l * P + j;
     port[j] = NOPAD ? s : gld(C.slot_port, s);
     if constexpr (SIMPLE) {
       pmax[j] = C.pmax_u;
@@ -424,7 +459,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   const int64_t sofs = (int64_t)env * S;
 #pragma unroll
   for (int j = 0; j < P; ++j) {
-    const int64_t i = sofs + j * L + l;
+    const int64_t i = sofs + l * P + j;
     q[j] = active ? gld(sg.q, i) : 0.0;
     qf[j] = (float)q[j];
     u[j] = active ? gld(sg.u, i) : 0.f;
@@ -433,7 +468,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     dw[j] = active ? (int)gld(sg.dwell, i) : 0;
     cs[j] = (users && active) ? (int)gld(sg.utype, i) : 0;
     rb[j] = models ? (active ? gld(sg.rbar, i) : 0.f) : pmax[j];
-    dc[j] = models ? gld(C.slot_dc, j * L + l) : 0;
+    dc[j] = models ? gld(C.slot_dc, l * P + j) : 0;
     icap[j] = cap[j] > 0.f ? frcp(cap[j]) : 0.f;
   }
   // The state is in registers before the first step: a load still pending when
@@ -462,7 +497,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   }
   uint32_t bkp = 0u, bkq = 0u;  // EXT: the battery's action bytes of the current group of 8 steps
   // the levels of a SIMPLE class by block size (as a copy in scalar registers)
-  constexpr int kBlk = LOGL + (P == 1 ? 0 : P == 2 ? 1 : 2);
+  constexpr int kBlk = LOGL + LOGP;
   [[maybe_unused]] float blk_cap[kBlk + 1];
   [[maybe_unused]] const uint32_t blk_mask = SIMPLE ? C.blk_mask : 0u;
   if constexpr (SIMPLE) {
@@ -487,9 +522,9 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   }
   int bM = 0, bdw = 1, bus = 0, bmod = 0;
   float bpb = 0.f, bcp = 0.f, bs0 = 0.f, btg = 0.f;
-  // 64-lane SIMPLE stations, which often take two cars in a step: the
-  // second car (rank 1) drawn ahead as well
-  constexpr bool AHEAD2 = SIMPLE && L == 64;
+  // SIMPLE stations of 64 ports and more, which often take two cars in a step:
+  // the second car (rank 1) drawn ahead as well
+  constexpr bool AHEAD2 = SIMPLE && L * P >= 64;
   int bdw1 = 1;
   float bcp1 = 0.f, bs01 = 0.f, btg1 = 0.f;
   // RANDOM: each slot's action bytes of the current group of 8 steps, one per
@@ -551,6 +586,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     policy_phase<kPolSteps1, HPOL>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true, hid);
   }
 
+  // every lane's P slots hold P adjacent ports (no padding slots)
+  [[maybe_unused]] const bool adjacent = NOPAD || S == N;
   [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
   [[maybe_unused]] int kb_in = 0;
   const int T = uni(dy.T);
@@ -699,22 +736,22 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       }
     }
 
-    // Sum over the station of one value per slot.  The fused policy of a class
-    // that is not SIMPLE adds lanes first, then registers: the order of the
-    // packing with one slot per lane that such a class runs in by default, so
-    // that its records are those of the two-kernel path bit for bit.
+    // Sum over the station of one value per slot, pairs of slots first (slot
+    // bits from the lowest up: the same sums for every packing).  The general and
+    // extended kinds with two slots per lane add the two halves of the station
+    // first: the order they have always summed in, which a charge-sensitive
+    // user's departure at a near-tie depends on.  The fused policy takes the
+    // order of one slot per lane, as the two-kernel path does by default.
     auto station_total = [&](const float (&v)[P]) {
-      if constexpr (POL && !SIMPLE && P > 1) {
-        float r[P];
-#pragma unroll
-        for (int j = 0; j < P; ++j) r[j] = station_sum<L>(v[j]);
-        if constexpr (P == 2) return r[0] + r[1];
-        else return (r[0] + r[1]) + (r[2] + r[3]);
+      if constexpr (P == 1) {
+        return station_sum<L>(v[0]);
+      } else if constexpr (P == 2 && !SIMPLE && !POL) {
+        const float a = v[0] + xor_lane<LOGL - 1>(v[0]), b = v[1] + xor_lane<LOGL - 1>(v[1]);
+        return station_sum<L / 2>(a + b);
+      } else if constexpr (P == 2) {
+        return station_sum<L>(v[0] + v[1]);
       } else {
-        float a = v[0];
-#pragma unroll
-        for (int j = 1; j < P; ++j) a += v[j];
-        return station_sum<L>(a);
+        return station_sum<L>((v[0] + v[1]) + (v[2] + v[3]));
       }
     };
 
@@ -728,47 +765,61 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       // the levels below (a scaled block contributes its limit); so each level
       // is checked when its block size is reached.  A slot's final factor is
       // the product of the factors of the nodes on its path.
-      float r[P], F[P];
+      // Blocks smaller than a lane's P slots (rare: such levels take a path of
+      // their own) have a factor per slot, larger ones one factor for the lane.
+      float F[P], r;
 #pragma unroll
-      for (int j = 0; j < P; ++j) {
-        r[j] = pw[j];
-        F[j] = 1.0f;
-      }
-      auto check = [&](int k) {
-        if ((blk_mask >> k) & 1u) {  // a level of blocks of 2^k slots (wave-uniform)
-          // a real (scalar) branch: most k have no level, and computing the
-          // check for every k and selecting would cost more than it saves
-          asm volatile("");
-          const float c = blk_cap[k];
-#pragma unroll
-          for (int j = 0; j < P; ++j) {
-            const bool over = r[j] > c;
-            F[j] = over ? F[j] * (c * frcp(r[j])) : F[j];
-            r[j] = over ? c : r[j];
-          }
-        }
+      for (int j = 0; j < P; ++j) F[j] = 1.0f;
+      auto limit = [&](float &load, float &f, float c) {
+        const bool over = load > c;
+        f = over ? f * (c * frcp(load)) : f;
+        load = over ? c : load;
       };
+      if (P > 1 && (blk_mask & ((1u << LOGP) - 1u))) {
+        float v[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+          v[j] = pw[j];
+          if (blk_mask & 1u) limit(v[j], F[j], blk_cap[0]);
+        }
+        if constexpr (P == 2) {
+          r = v[0] + v[1];
+        } else if constexpr (P == 4) {
+          float lo = v[0] + v[1], hi = v[2] + v[3];
+          if (blk_mask & 2u) {
+            float fl = 1.0f, fh = 1.0f;
+            limit(lo, fl, blk_cap[1]);
+            limit(hi, fh, blk_cap[1]);
+            F[0] *= fl; F[1] *= fl; F[2] *= fh; F[3] *= fh;
+          }
+          r = lo + hi;
+        } else {
+          r = v[0];
+        }
+      } else if constexpr (P == 1) {
+        r = pw[0];
+      } else if constexpr (P == 2) {
+        r = pw[0] + pw[1];
+      } else {
+        r = (pw[0] + pw[1]) + (pw[2] + pw[3]);
+      }
+      float f = 1.0f;
 #pragma unroll
       for (int k = 0; k < LOGL; ++k) {
-        check(k);
-#pragma unroll
-        for (int j = 0; j < P; ++j) r[j] = xsum_k<L>(r[j], k);
-      }
-      if constexpr (P >= 2) {  // blocks of 2 L slots: registers (0, 1) and (2, 3)
-        check(LOGL);
-        r[0] = r[1] = r[0] + r[1];
-        if constexpr (P == 4) r[2] = r[3] = r[2] + r[3];
-      }
-      if constexpr (P == 4) {  // blocks of 4 L slots: all four registers
-        check(LOGL + 1);
-        r[0] = r[1] = r[2] = r[3] = r[0] + r[2];
+        if ((blk_mask >> (k + LOGP)) & 1u) {  // a level of blocks of P 2^k slots (wave-uniform)
+          // a real (scalar) branch: most sizes have no level, and computing the
+          // check for every one and selecting would cost more than it saves
+          asm volatile("");
+          limit(r, f, blk_cap[k + LOGP]);
+        }
+        r = xsum_k<L>(r, k);
       }
       // the root: the whole station, delivered energy its scaled load (App. A.3)
-      const float tot = r[0];
+      const float tot = r;
       const bool over = tot > c_root;
-      const float f = over ? c_root * frcp(tot) : 1.0f;
+      const float fr = over ? c_root * frcp(tot) : 1.0f;
 #pragma unroll
-      for (int j = 0; j < P; ++j) pw[j] *= F[j] * f;
+      for (int j = 0; j < P; ++j) pw[j] *= (P == 1 ? f : F[j] * f) * fr;
       e_net = dt * (over ? c_root : tot);
       e_grid = e_net * inv_eta_u;
     } else {
@@ -777,7 +828,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       if (d < D - 1) {
         float s[P];
         const int lbu = (int)((C.lvl_lb_uniform >> (8 * d)) & 0xFF);
-        const int nd = SIMPLE ? 0 : (int)((C.dense_nodes >> (8 * d)) & 0xFF);
+        const int nd = (int)((C.dense_nodes >> (8 * d)) & 0xFF);
         if (nd != 0) {
           // dense layout: at most 4 nodes on this level, each summed over the
           // whole station from the slots it covers
@@ -795,34 +846,38 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
               for (int j = 0; j < P; ++j) s[j] = ((lbp[j] >> (8 * d)) & 0xFFu) == code ? acc : s[j];
             }
           }
-        } else if (SIMPLE || lbu != 0xFF) {  // every slot of the level sits in a block of 2^lbu slots
+        } else if (lbu != 0xFF && lbu >= LOGP) {  // every slot of the level sits in a block of 2^lbu slots
+          float v = pw[0];
+          if constexpr (P == 2) v = pw[0] + pw[1];
+          if constexpr (P == 4) v = (pw[0] + pw[1]) + (pw[2] + pw[3]);
+          v = block_sum_lanes<L>(v, lbu - LOGP);
 #pragma unroll
-          for (int j = 0; j < P; ++j) s[j] = block_sum_lanes<L>(pw[j], lbu);
+          for (int j = 0; j < P; ++j) s[j] = v;
         } else {
+          // block sizes differ from slot to slot (a block's own slots agree):
+          // first inside the lane, then over the lanes of blocks wider than it
+          int lb[P];
 #pragma unroll
-          for (int j = 0; j < P; ++j) s[j] = block_sum_lanes<L>(pw[j], (int)((lbp[j] >> (8 * d)) & 0xFF));
-        }
-        // blocks wider than a row of L slots span whole registers: add across them
-        // (aligned layout only: a dense level's sums are already station-wide)
-        if constexpr (P >= 2) {
-          const int lb0 = nd != 0 ? 0 : (int)((lbp[0] >> (8 * d)) & 0xFF);
-          if (lb0 > LOGL) {
+          for (int j = 0; j < P; ++j) {
+            lb[j] = (int)((lbp[j] >> (8 * d)) & 0xFF);
+            s[j] = pw[j];
+          }
+          if constexpr (P >= 2) {
             const float a = s[0] + s[1];
-            s[0] = a;
-            s[1] = a;
+            s[0] = lb[0] > 0 ? a : s[0];
+            s[1] = lb[1] > 0 ? a : s[1];
           }
           if constexpr (P == 4) {
-            const int lb2 = nd != 0 ? 0 : (int)((lbp[2] >> (8 * d)) & 0xFF);
-            if (lb2 > LOGL) {
-              const float a = s[2] + s[3];
-              s[2] = a;
-              s[3] = a;
-            }
-            if (lb0 > LOGL + 1) {
-              const float a = s[0] + s[2];
-              s[0] = a; s[1] = a; s[2] = a; s[3] = a;
-            }
+            const float b = s[2] + s[3];
+            s[2] = lb[2] > 0 ? b : s[2];
+            s[3] = lb[3] > 0 ? b : s[3];
+            const float a = s[0] + s[2];
+            const bool quad = lb[0] > 1;
+#pragma unroll
+            for (int j = 0; j < P; ++j) s[j] = quad ? a : s[j];
           }
+#pragma unroll
+          for (int j = 0; j < P; ++j) s[j] = block_sum_lanes<L>(s[j], lb[j] - LOGP);
         }
 #pragma unroll
         for (int j = 0; j < P; ++j) {
@@ -839,10 +894,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // root: the station total before root scaling; the delivered energy is its
     // scaled value (App. A.3, charging only)
     if constexpr (EXT) {
-      float tot = 0.f;
-#pragma unroll
-      for (int j = 0; j < P; ++j) tot += pw[j];
-      tot = station_sum<L>(tot);
+      const float tot = station_total(pw);
       const float a = fabsf(tot);
       const bool over = a > c_root;
       const float f = over ? c_root * frcp(a) : 1.0f;
@@ -850,14 +902,14 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       for (int j = 0; j < P; ++j) pw[j] *= f;
       e_net = dt * (over ? copysignf(c_root, tot) : tot);
       // grid energy: charging ports draw e / eta, discharging ports return eta e
-      float tg = 0.f, to = 0.f;
+      float tg[P], to[P];
 #pragma unroll
       for (int j = 0; j < P; ++j) {
-        tg += pw[j] > 0.f ? pw[j] * inv_eta[j] : pw[j] * eta[j];
-        to += pw[j] < 0.f ? pw[j] * eta[j] : 0.f;
+        tg[j] = pw[j] > 0.f ? pw[j] * inv_eta[j] : pw[j] * eta[j];
+        to[j] = pw[j] < 0.f ? pw[j] * eta[j] : 0.f;
       }
-      e_grid = dt * station_sum<L>(tg);
-      if (C.alpha_dc != 0.0f) e_out = dt * station_sum<L>(to);
+      e_grid = dt * station_total(tg);
+      if (C.alpha_dc != 0.0f) e_out = dt * station_total(to);
     } else {
       const float tot = station_total(pw);
       const bool over = tot > c_root;
@@ -869,8 +921,13 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
         e_grid = e_net * inv_eta_u;
       } else {
         float tg[P];
+        {
+          // each product rounded before it is added, so that every lane and every
+          // packing adds the same numbers
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int j = 0; j < P; ++j) tg[j] = pw[j] * inv_eta[j];
+          for (int j = 0; j < P; ++j) tg[j] = pw[j] * inv_eta[j];
+        }
         e_grid = dt * station_total(tg);
       }
     }
@@ -908,7 +965,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // charge-sensitive one (EXT) when no energy is wanted any more
     // (c_satisfaction,1: hours overstayed - beta x hours left early)
     float csat = 0.f, csat1 = 0.f;
-    float missed[P] = {};
+    float missed[P] = {}, moved[P] = {};
 #pragma unroll
     for (int j = 0; j < P; ++j) {
       const bool occ = CX_OCCUPIED(j);              // (pw = 0 on empty slots)
@@ -927,7 +984,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           dep = occ && (csu ? q[j] <= (double)u[j] : dw[j] == 0);
           dep0 = dep && !csu;
           const float tl = (float)dw[j] * dt;
-          csat1 += (dep && csu) ? fmaxf(0.0f, -tl) - C.beta_sat1 * fmaxf(0.0f, tl) : 0.0f;
+          moved[j] = (dep && csu) ? fmaxf(0.0f, -tl) - C.beta_sat1 * fmaxf(0.0f, tl) : 0.0f;
           cs[j] = dep ? 0 : cs[j];
           dw[j] = dep ? 0 : dw[j];   // a charged user may leave with steps of its stay left
         }
@@ -942,22 +999,20 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     }
     if (flags & kSat) csat = station_total(missed);
     if constexpr (EXT) {
-      if (users && C.alpha_sat1 != 0.0f) csat1 = station_sum<L>(csat1);
+      if (users && C.alpha_sat1 != 0.0f) csat1 = station_total(moved);
     }
 
     // ---- arrivals: first free ports in port order take the accepted cars
     int rej = 0;
     if (ballot(M > 0)) {
-      int cnt[P], below[P];
       bool fr[P];
-      int n_free = 0;
+      int n_free = 0, below = 0;   // free slots of the station, and of its lanes before this one
 #pragma unroll
       for (int j = 0; j < P; ++j) {
         fr[j] = (EXT ? !CX_OCCUPIED(j) : dw[j] == 0) && (NOPAD || port[j] >= 0);
         const uint64_t m = ballot(fr[j]) & smask;
-        cnt[j] = __popcll(m);
-        below[j] = __popcll(m & below_mask);
-        n_free += cnt[j];
+        n_free += __popcll(m);
+        below += __popcll(m & below_mask);
       }
       const int acc = M < n_free ? M : n_free;
       rej = M - acc;
@@ -977,10 +1032,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           f_dw1 = bcast<L>(bdw1, tb);
         }
       }
-      int run = 0;
+      int run = below;
 #pragma unroll
       for (int j = 0; j < P; ++j) {
-        const int rank = run + below[j];
+        const int rank = run;
         if (fr[j] && rank < acc) {
           float cp = f_cp, s0 = f_s0, tg = f_tg;
           int dd = f_dw;
@@ -1019,7 +1074,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           u[j] = 1.0f - tg;
           plast[j] = 0.f;
         }
-        run += cnt[j];
+        run += fr[j] ? 1 : 0;
       }
     }
 
@@ -1070,28 +1125,56 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
                         : 0;
     if (active) {
       if (POL || (flags & kWObs)) {
+        // put(feature offset, port's offset, value) writes one value; with every
+        // lane's ports adjacent (slot s = port s), put_lane writes a lane's P values
+        // of a feature at once
         int n_occ = 0;
+        if constexpr (P == 1) {
+          n_occ = __popcll(ballot(CX_OCCUPIED(0) && (NOPAD || port[0] >= 0)) & smask);
+        } else {
+          float on = 0.f;   // (small whole numbers: exact)
 #pragma unroll
-        for (int j = 0; j < P; ++j)
-          n_occ += __popcll(ballot(CX_OCCUPIED(j) && (NOPAD || port[j] >= 0)) & smask);
-        auto obs_record = [&](auto put, auto put4) {
+          for (int j = 0; j < P; ++j) on += CX_OCCUPIED(j) && (NOPAD || port[j] >= 0) ? 1.0f : 0.0f;
+          n_occ = (int)station_sum<L>(on);
+        }
+        auto obs_record = [&](auto put, auto put_lane, auto put4) {
+          float f[6][P];
 #pragma unroll
           for (int j = 0; j < P; ++j) {
-            if (NOPAD || port[j] >= 0) {
-              const bool occ = CX_OCCUPIED(j);
-              const uint32_t o = 4u * (uint32_t)port[j];
-              put(0u * 4u * N, o, occ ? 1.0f : 0.0f);
-              put(1u * 4u * N, o, occ ? 1.0f - qf[j] : 0.0f);
-              put(2u * 4u * N, o, occ ? qf[j] - u[j] : 0.0f);
-              put(3u * 4u * N, o, (float)dw[j] * inv_steps_ep);
-              float rh = fminf(1.0f, qf[j] * inv_1mtau);
-              if constexpr (EXT) {
-                if (models) rh *= rb[j] * inv_pmax[j];  // the car's curve, as a share of the port maximum
+            const bool occ = CX_OCCUPIED(j);
+            f[0][j] = occ ? 1.0f : 0.0f;
+            f[1][j] = occ ? 1.0f - qf[j] : 0.0f;
+            f[2][j] = occ ? qf[j] - u[j] : 0.0f;
+            f[3][j] = (float)dw[j] * inv_steps_ep;
+            float rh = fminf(1.0f, qf[j] * inv_1mtau);
+            if constexpr (EXT) {
+              if (models) rh *= rb[j] * inv_pmax[j];  // the car's curve, as a share of the port maximum
+            }
+            f[4][j] = occ ? rh : 0.0f;
+            f[5][j] = occ ? plast[j] * inv_pmax[j] : 0.0f;
+          }
+          const uint32_t Nb = 4u * (uint32_t)N;
+          if (P > 1 && adjacent) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i) put_lane((uint32_t)i * Nb, 4u * (uint32_t)port[0], f[i]);
+            if constexpr (EXT) {
+              if (users) {
+                float c[P];
+#pragma unroll
+                for (int j = 0; j < P; ++j) c[j] = cs[j] ? 1.0f : 0.0f;
+                put_lane(4u * (uint32_t)C.user_obs, 4u * (uint32_t)port[0], c);
               }
-              put(4u * 4u * N, o, occ ? rh : 0.0f);
-              put(5u * 4u * N, o, occ ? plast[j] * inv_pmax[j] : 0.0f);
-              if constexpr (EXT) {
-                if (users) put(4u * (uint32_t)C.user_obs, 4u * (uint32_t)port[j], cs[j] ? 1.0f : 0.0f);
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+              if (NOPAD || port[j] >= 0) {
+                const uint32_t o = 4u * (uint32_t)port[j];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) put((uint32_t)i * Nb, o, f[i][j]);
+                if constexpr (EXT) {
+                  if (users) put(4u * (uint32_t)C.user_obs, o, cs[j] ? 1.0f : 0.0f);
+                }
               }
             }
           }
@@ -1115,6 +1198,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           typedef __attribute__((address_space(3))) uint16_t lds_u16;
           lds_u16 *xr = reinterpret_cast<lds_u16 *>(lds + pol->xb_off) + (env - env_blk0) * (kPolXbRow * 8);
           obs_record([&](uint32_t fo, uint32_t lo, float v) { xr[(fo + lo) >> 2] = (uint16_t)pack2(v, 0.f); },
+                     [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
+                       // (P even and N a multiple of P: a whole number of words)
+                       lds_u32 *x2 = reinterpret_cast<lds_u32 *>(xr) + ((fo + lo) >> 3);
+#pragma unroll
+                       for (int j = 0; j + 1 < P; j += 2) x2[j / 2] = pack2(v[j], v[j + 1]);
+                     },
                      [&](uint32_t fo, float a, float b, float c, float d) {
                        lds_u32 *x2 = reinterpret_cast<lds_u32 *>(xr) + (fo >> 3);  // (6 N is even)
                        x2[0] = pack2(a, b);
@@ -1123,6 +1212,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
         } else if constexpr (STAGE) {
           lds_char *sb = reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_floats) + pad) + stage_bo;
           obs_record([&](uint32_t fo, uint32_t lo, float v) { *reinterpret_cast<lds_float *>(sb + fo + lo) = v; },
+                     [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
+                       fvec<P> x;
+#pragma unroll
+                       for (int j = 0; j < P; ++j) set_at(x, j, v[j]);
+                       *reinterpret_cast<__attribute__((address_space(3))) fvec<P> *>(sb + fo + lo) = x;
+                     },
                      [&](uint32_t fo, float a, float b, float c, float d) {
                        *reinterpret_cast<lds_f32x4u *>(sb + fo) = f32x4{a, b, c, d};
                      });
@@ -1130,6 +1225,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           // the feature's offset goes on the wave-uniform base, the lane's on its
           // 32-bit offset
           obs_record([&](uint32_t fo, uint32_t lo, float v) { st_at((float *)((char *)ob_now + fo), obs_bo_t + lo, v); },
+                     [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
+                       fvec<P> x;
+#pragma unroll
+                       for (int j = 0; j < P; ++j) set_at(x, j, v[j]);
+                       st_at((fvec<P> *)((char *)ob_now + fo), obs_bo_t + lo, x);
+                     },
                      [&](uint32_t fo, float a, float b, float c, float d) {
                        st_at((f32x4u *)((char *)ob_now + fo), obs_bo_t, (f32x4u){a, b, c, d});
                      });
@@ -1137,18 +1238,23 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       }
       if (flags & kWAct) {
         if (NOPAD && (flags & kActQuads)) {
-          // four consecutive ports' bytes gathered into the first lane of each
-          // quad (the pair's second byte, then the second pair, each moved and
-          // shifted by one 24-bit multiply) and stored as one dword (an env's
-          // bytes start at a multiple of 4, N being one; every step's row too)
+          // four consecutive ports' bytes gathered into the lane of the first
+          // (moved from the neighbours and shifted by one 24-bit multiply a pair)
+          // and stored as one dword (an env's bytes start at a multiple of 4, N
+          // being one; every step's row too)
+          uint32_t w = (uint32_t)k[0];   // the lane's own bytes
 #pragma unroll
-          for (int j = 0; j < P; ++j) {
-            const uint32_t b1 = (uint32_t)__builtin_amdgcn_update_dpp(0, k[j], 0xF5, 0xF, 0xF, true);  // lanes 1, 1, 3, 3
-            const uint32_t w2 = (uint32_t)k[j] | __umul24(b1, 1u << 8);
-            const uint32_t b2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w2, 0xAA, 0xF, 0xF, true);  // lane 2
-            const uint32_t w4 = w2 | __umul24(b2, 1u << 16);
-            if ((l & 3) == 0) st_at((uint32_t *)ab_t, act_bo_t + (uint32_t)port[j], w4);
+          for (int j = 1; j < P; ++j) w |= (uint32_t)k[j] << (8 * j);
+          if constexpr (P == 1) {  // lanes 1, 1, 3, 3 of the quad
+            const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xF5, 0xF, 0xF, true);
+            w |= __umul24(b, 1u << 8);
           }
+          if constexpr (P <= 2) {  // lane 2 (P = 1), lanes 1, 1, 3, 3 (P = 2)
+            const uint32_t b =
+                (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, P == 1 ? 0xAA : 0xF5, 0xF, 0xF, true);
+            w |= __umul24(b, 1u << 16);
+          }
+          if ((l & (4 / P - 1)) == 0) st_at((uint32_t *)ab_t, act_bo_t + (uint32_t)port[0], w);
         } else {
 #pragma unroll
           for (int j = 0; j < P; ++j)
@@ -1196,7 +1302,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   if (active) {
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-      const int64_t i = sofs + j * L + l;
+      const int64_t i = sofs + l * P + j;
       const bool occ = CX_OCCUPIED(j);
       gst(so.q, i, occ ? q[j] : 0.0);
       gst(so.u, i, occ ? u[j] : 0.f);
