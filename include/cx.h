@@ -378,9 +378,10 @@ cx_status cx_set_packing(cx_ctx *ctx, int32_t cls, int32_t lanes_per_station, in
 /* on = 1: classes without padding slots, with one port maximum and efficiency
  * and one block size per tree level write their observation records through an
  * LDS stage of each block, as 16-byte stores of whole record runs; on = 0 (the
- * default): every lane stores its own values.  The records are bit for bit the
- * same either way; which is faster depends on the launch (a mixed launch of
- * many classes gains).  CX_E_INVALID unless on is 0 or 1. */
+ * default): every lane stores its own values, except in rollouts of at least as
+ * many waves as the GPU holds at once, where the stage is always the faster.
+ * The records are bit for bit the same either way; which is faster depends on
+ * the launch.  CX_E_INVALID unless on is 0 or 1. */
 cx_status cx_set_obs_stage(cx_ctx *ctx, int32_t on);
 
 /* Time every legal packing of every class on a T_probe-step rollout (state is

@@ -216,8 +216,8 @@ void build_groups(const std::vector<SegDev> &in, const std::vector<int> &log2_dw
     }
     // fewer waves per block where the observation stages would not fit
     g.wpb = wpb;
-    while (group_stages(g.kind, g.pack) && g.wpb > 1 &&
-           group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, nullptr, nullptr) > kMaxBlockLds)
+    while (g.kind == kKindSimpleStaged && g.wpb > 1 &&
+           lds_plan(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, true, false).bytes > kMaxBlockLds)
       g.wpb >>= 1;
     int blocks = 0;
     for (size_t i = 0; i < in.size(); ++i) {

@@ -29,7 +29,7 @@ constexpr int kNumPackings = 15;
 // constant uniform), and extended classes (V2G ports, a station battery or
 // charge-sensitive users).
 // kKindSimpleStaged: a SIMPLE class whose observations go through the block's
-// LDS stage (a context option, cx_set_obs_stage).
+// LDS stage (a context option, cx_set_obs_stage, or the launch's choice).
 enum : int { kKindGeneral = 0, kKindSimple = 1, kKindExt = 2, kKindSimpleStaged = 3, kNumKinds = 4 };
 __host__ __device__ constexpr int pack_lanes(int id) { return 4 << (id % 5); }
 __host__ __device__ constexpr int pack_per_lane(int id) { return 1 << (id / 5); }
@@ -157,6 +157,7 @@ struct LaunchArgs {
   // the two stage buffers in the dynamic LDS and floats per buffer (0: each
   // lane stores its observation values to HBM itself)
   int32_t stage_off, stage_floats;
+  int32_t day_off, car_off;  // byte offsets of the day's tables and (extended classes) the car models'
   float *obs;
   uint8_t *act;
   float *reward;
@@ -194,38 +195,46 @@ struct LaunchGroup {
   int wpb = 1;             // waves per block: the context's choice, halved until the LDS fits
 };
 
-// Does a launch group stage its observations?  Its SIMPLE classes do, in every
-// packing, when the context asks for it.
-__host__ __device__ constexpr bool group_stages(int kind, int pack) {
-  (void)pack;
-  return kind == kKindSimpleStaged;
-}
-
 // LDS a block may take for its tables and the two observation stages.
 constexpr size_t kMaxBlockLds = 64 << 10;
 // Per-step tables of a day kept in LDS when a day has at most this many steps:
 // the first four arrival thresholds of every step (one 16-byte row each) and
 // the base price of every step (so the draws ahead read no device memory).
 constexpr int kLdsExoSteps = 512;
+// The car models' tables of an extended class: 8 thresholds, 8 x 3 floats.
+constexpr size_t kCarTabBytes = 32 * 4;
 constexpr int kLdsExoMinT = 32;   // ... in launches of at least this many steps
 
-// LDS layout of a launch group's blocks: the stay table (4 << dwell_log2
-// bytes), the day's tables (16 bytes a step, then 4), then two observation
-// stages of waves x stations per wave x the largest observation floats, plus 3
-// floats to align them with HBM (rounded to 16 bytes).
-inline size_t group_table_bytes(int dwell_log2, int day_steps) {
-  return ((((size_t)4 << dwell_log2) + 15) & ~(size_t)15) + (((size_t)day_steps * 20 + 15) & ~(size_t)15);
-}
-// Bytes with the stages; *stage_off / *stage_floats: where the stages begin
-// and floats per stage.
-inline size_t group_lds_bytes(int wpb, int pack, int max_obs_dim, int dwell_log2, int day_steps, int32_t *stage_off,
-                              int32_t *stage_floats) {
-  const size_t off = group_table_bytes(dwell_log2, day_steps);
+// LDS layout of a launch group's blocks: the stay table (4 << dwell_log2 bytes),
+// the day's tables (16 bytes a step, then 4), two observation stages of waves x
+// stations per wave x the largest observation floats, plus 3 floats to align
+// them with HBM (rounded to 16 bytes), and the car models' tables.  A block of
+// one wave needs one stage (its own reads and writes of LDS are in order): the
+// day's tables follow it, over what would be the second.
+struct LdsPlan {
+  int32_t day_off = 0, stage_off = 0, stage_floats = 0, car_off = 0;
+  size_t bytes = 0;
+};
+inline LdsPlan lds_plan(int wpb, int pack, int max_obs_dim, int dwell_log2, int day_steps, bool stages, bool cars) {
+  auto a16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+  LdsPlan p;
+  const size_t stay = a16((size_t)4 << dwell_log2), days = a16((size_t)day_steps * 20);
   const size_t floats =
-      ((size_t)wpb * (size_t)(64 / pack_lanes(pack)) * (size_t)max_obs_dim + 3 + 3) & ~(size_t)3;
-  if (stage_off) *stage_off = (int32_t)off;
-  if (stage_floats) *stage_floats = (int32_t)floats;
-  return off + 8 * floats;
+      stages ? ((size_t)wpb * (size_t)(64 / pack_lanes(pack)) * (size_t)max_obs_dim + 3 + 3) & ~(size_t)3 : 0;
+  size_t end;
+  if (stages && wpb == 1) {
+    p.stage_off = (int32_t)stay;
+    p.day_off = (int32_t)(stay + 4 * floats);
+    end = std::max((size_t)p.day_off + days, stay + 8 * floats);
+  } else {
+    p.day_off = (int32_t)stay;
+    p.stage_off = (int32_t)(stay + days);
+    end = stay + days + 8 * floats;
+  }
+  p.stage_floats = (int32_t)floats;
+  p.car_off = (int32_t)a16(end);
+  p.bytes = cars ? (size_t)p.car_off + kCarTabBytes : end;
+  return p;
 }
 
 // The fused policy rollout: blocks of 4 waves of 8-lane stations (32 envs, two

@@ -35,30 +35,27 @@
 namespace cx {
 namespace {
 
-// Arrivals of one step: thresholds exceeded by w in a 32-entry row.  The
-// first four entries come in one 16-byte load; the full bisection runs only
-// when w exceeds all four (rare for the rates used here).
-__device__ __forceinline__ int arrivals(const uint32_t *row, uint32_t w) {
-  const u32x4 t = gld(reinterpret_cast<const u32x4 *>(row), 0);
-  const int m = (int)(w > t.x) + (int)(w > t.y) + (int)(w > t.z) + (int)(w > t.w);
-  if (m < 4) return m;
-  int pos = 0;
-  for (int s = 16; s >= 1; s >>= 1)
-    if (gld(row, pos + s - 1) < w) pos += s;
-  return pos;
+// Arrivals of one step: thresholds exceeded by w in a row of 24 (and 8 of
+// 0xFFFFFFFF).  The first four come in one 16-byte load, from the block's LDS
+// copy of them where there is one; the rest are read only when w exceeds all
+// four, from device memory and together: the wait for them is also one for the
+// records in flight, and a bisection has five of them.
+__device__ __forceinline__ int arrivals_after4(const uint32_t *row, uint32_t w) {
+  const u32x4 *r = reinterpret_cast<const u32x4 *>(row);
+  const u32x4 a = gld(r, 1), b = gld(r, 2);
+  int m = 4 + (int)(w > a.x) + (int)(w > a.y) + (int)(w > a.z) + (int)(w > a.w) + (int)(w > b.x) + (int)(w > b.y) +
+          (int)(w > b.z) + (int)(w > b.w);
+  if (m == 12)
+    for (int i = 12; i < kPoisK; ++i) m += (int)(w > gld(row, i));
+  return m;
 }
-
-// The same with the row's first four thresholds from the block's LDS copy
-// (the rest, rarely needed, from device memory).
-__device__ __forceinline__ int arrivals_lds(const __attribute__((address_space(3))) u32x4 *first4, const uint32_t *row,
-                                            uint32_t w) {
-  const u32x4 t = *first4;
+__device__ __forceinline__ int arrivals(const __attribute__((address_space(3))) u32x4 *first4, const uint32_t *row,
+                                        uint32_t w) {
+  u32x4 t;
+  if (first4) t = *first4;
+  else t = gld(reinterpret_cast<const u32x4 *>(row), 0);
   const int m = (int)(w > t.x) + (int)(w > t.y) + (int)(w > t.z) + (int)(w > t.w);
-  if (m < 4) return m;
-  int pos = 0;
-  for (int s = 16; s >= 1; s >>= 1)
-    if (gld(row, pos + s - 1) < w) pos += s;
-  return pos;
+  return m < 4 ? m : arrivals_after4(row, w);
 }
 
 // Stay length of an arriving car: 1 + #{thresholds below w}, bisecting the
@@ -295,10 +292,10 @@ __device__ __forceinline__ void flush_stage(const lds_float *sb, float *dst, int
 // per-slot constant is wave-uniform (scalar registers).
 // EXT: V2G ports, a station battery, charge-sensitive users, price days and / or
 // car models (never SIMPLE); each switched on per class by a uniform flag.
-// STAGE: observations through the block's LDS stage (SIMPLE classes, when the
-// context asks for it): stage / stage_floats are the two
-// stage buffers and floats per buffer, g_blk0 the block's first group and
-// n_run the number of its waves that run.
+// STAGE: observations through the block's LDS stage (SIMPLE classes): stage is the first
+// buffer, the second stage_step floats on (0: one buffer, enough for a block of
+// one wave), g_blk0 the block's first group and n_run the number of its waves
+// that run.
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -384,12 +381,14 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 // record pointers from it (serving) instead of from the launch arguments.
 // tdw: the block's LDS copy of the stay thresholds; exo_tp / exo_pr: its LDS
 // copies of the first four arrival thresholds and the base price of every step
-// of the day (NULL: read device memory).
+// of the day (NULL: read device memory); car_tab: of the car models' 8 thresholds
+// and 8 x {capacity, AC rate, DC rate} (extended classes).
 // HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units.
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL = 0>
 __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, int group, const lds_u32 *tdw,
-                                          const lds_u32x4 *exo_tp, const lds_float *exo_pr, lds_float *stage,
-                                          int stage_floats, int g_blk0, int n_run,
+                                          const lds_u32x4 *exo_tp, const lds_float *exo_pr,
+                                          const lds_u32 *car_tab, lds_float *stage,
+                                          int stage_step, int g_blk0, int n_run,
                                           const LaunchArgs::Pol *pol = nullptr, lds_char *lds = nullptr) {
   constexpr int SPW = 64 / L;
   constexpr int LOGP = P == 1 ? 0 : P == 2 ? 1 : 2;
@@ -522,10 +521,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   }
   int bM = 0, bdw = 1, bus = 0, bmod = 0;
   float bpb = 0.f, bcp = 0.f, bs0 = 0.f, btg = 0.f;
+  [[maybe_unused]] float bpn = 0.f;  // price days: the base price after the step
   // SIMPLE stations of 64 ports and more, which often take two cars in a step:
   // the second car (rank 1) drawn ahead as well
   constexpr bool AHEAD2 = SIMPLE && L * P >= 64;
   int bdw1 = 1;
+
   float bcp1 = 0.f, bs01 = 0.f, btg1 = 0.f;
   // RANDOM: each slot's action bytes of the current group of 8 steps, one per
   // byte (steps 0-3 of the group in kp, 4-7 in kq)
@@ -588,6 +589,13 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
 
   // every lane's P slots hold P adjacent ports (no padding slots)
   [[maybe_unused]] const bool adjacent = NOPAD || S == N;
+  // (from LDS: a load from device memory would wait for the records in flight)
+  [[maybe_unused]] auto car_model = [&](uint32_t w) {
+    int m = 0;
+    for (int i = 0; i < n_models; ++i) m += w > car_tab[i] ? 1 : 0;
+    return m;
+  };
+  [[maybe_unused]] auto car_data = [&](int i) { return __uint_as_float(car_tab[8 + i]); };
   [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
   [[maybe_unused]] int kb_in = 0;
   const int T = uni(dy.T);
@@ -602,10 +610,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       while (td >= steps_ep) td -= steps_ep;
       const uint32_t gl = g + (uint32_t)l;
       const U4 w = philox(env_id, gl, 0u, kDomEnv, k0, k1);
-      if (exo_tp)
-        bM = active ? arrivals_lds(exo_tp + td, C.tpois + td * kPoisStride, w.x) : 0;
-      else
-        bM = active ? arrivals(C.tpois + td * kPoisStride, w.x) : 0;
+      bM = active ? arrivals(exo_tp ? exo_tp + td : nullptr, C.tpois + td * kPoisStride, w.x) : 0;
       const float u1 = (float)((w.y >> 8) + 1u) * 0x1p-24f;
       const float u2 = u24(w.z);
       const float z = __builtin_amdgcn_sqrtf(-2.0f * __logf(u1)) * __builtin_amdgcn_cosf(u2);
@@ -620,16 +625,28 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
         asm volatile("" ::"v"(base));
       }
       if constexpr (EXT) {
-        if (days) base = gld(C.price_days, episode_day(env_id, gl - (uint32_t)td, k0, k1, n_days) * steps_ep + td);
+        if (days) {
+          // the price of this step and of the one after it (its observation's),
+          // which is the first of the next day's when this is the day's last
+          const int day = episode_day(env_id, gl - (uint32_t)td, k0, k1, n_days);
+          int day1 = day, td1 = td + 1;
+          if (ballot(td1 == steps_ep)) {
+            const int next = episode_day(env_id, gl + 1u, k0, k1, n_days);
+            day1 = td1 == steps_ep ? next : day;
+            td1 = td1 == steps_ep ? 0 : td1;
+          }
+          base = gld(C.price_days, day * steps_ep + td);
+          bpn = gld(C.price_days, day1 * steps_ep + td1);
+          asm volatile("" ::"v"(base), "v"(bpn));  // (waited for here, not in every step)
+        }
       }
       bpb = base + C.price_sigma * z;
       const U4 b = philox(env_id, gl, 0u, kDomCar, k0, k1);
       bcp = C.cap_lo + C.cap_span * u24(b.x);
       if constexpr (EXT) {
         if (models) {  // the car's model fixes its capacity
-          bmod = 0;
-          for (int m = 0; m < n_models; ++m) bmod += b.x > gld(C.model_thresh, m) ? 1 : 0;
-          bcp = gld(C.model_data, 3 * bmod);
+          bmod = car_model(b.x);
+          bcp = car_data(3 * bmod);
         }
       }
       bs0 = C.soc_lo + C.soc_span * u24(b.y);
@@ -651,6 +668,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     const int tb = t & (L - 1);
     const int M = bcast<L>(bM, tb);
     const float pbuy = bcastf<L>(bpb, tb);
+    [[maybe_unused]] float p_next = 0.f;
+    if constexpr (EXT) {
+      if (days) p_next = bcastf<L>(bpn, tb);
+    }
     // the observation's time features of the step after this one (a scalar
     // load, issued early; it does not wait for the records in flight)
     const int t_obs = t_day + 1 == steps_ep ? 0 : t_day + 1;
@@ -722,14 +743,19 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       const float rhat = pmax[j] * fminf(1.0f, qf[j] * inv_1mtau);
       const float room = qf[j] * cap[j] * inv_dt;
       if constexpr (EXT) {
-        const int lev = k[j] - n_neg;
-        const float soc = (float)(1.0 - q[j]);
-        const float creq = (float)lev * inv_n_levels * pmax[j];
-        const float dreq = (float)(-lev) * inv_n_levels * pdis[j];
         const float crate = rb[j] * fminf(1.0f, qf[j] * inv_1mtau);   // the car's curve
-        const float drate = rb[j] * fminf(1.0f, soc * inv_1mtau);
-        const float stored = soc * cap[j] * inv_dt;
-        const float p = lev >= 0 ? fminf(fminf(creq, crate), room) : -fminf(fminf(dreq, drate), stored);
+        float p;
+        if (n_neg != 0) {
+          const int lev = k[j] - n_neg;
+          const float soc = (float)(1.0 - q[j]);
+          const float creq = (float)lev * inv_n_levels * pmax[j];
+          const float dreq = (float)(-lev) * inv_n_levels * pdis[j];
+          const float drate = rb[j] * fminf(1.0f, soc * inv_1mtau);
+          const float stored = soc * cap[j] * inv_dt;
+          p = lev >= 0 ? fminf(fminf(creq, crate), room) : -fminf(fminf(dreq, drate), stored);
+        } else {
+          p = fminf(fminf(req, crate), room);
+        }
         pw[j] = CX_OCCUPIED(j) ? p : 0.0f;
       } else {
         pw[j] = dw[j] > 0 ? fminf(fminf(req, rhat), room) : 0.0f;
@@ -1050,9 +1076,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
             cp = C.cap_lo + C.cap_span * u24(b.x);
             if constexpr (EXT) {
               if (models) {
-                md = 0;
-                for (int m = 0; m < n_models; ++m) md += b.x > gld(C.model_thresh, m) ? 1 : 0;
-                cp = gld(C.model_data, 3 * md);
+                md = car_model(b.x);
+                cp = car_data(3 * md);
               }
             }
             s0 = C.soc_lo + C.soc_span * u24(b.y);
@@ -1065,7 +1090,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           dw[j] = dd;
           if constexpr (EXT) {
             cs[j] = us;
-            if (models) rb[j] = gld(C.model_data, 3 * md + (dc[j] ? 2 : 1));
+            if (models) rb[j] = car_data(3 * md + (dc[j] ? 2 : 1));
           }
           cap[j] = cp;
           icap[j] = frcp(cp);
@@ -1181,7 +1206,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
           if (l == 0) {  // the station's four: its first lane
             float price = gl.z;
             if constexpr (EXT) {
-              if (days) price = gld(C.price_days, dday * steps_ep + t_day);
+              if (days) price = p_next;
             }
             put4(4u * (uint32_t)(6 * N), gl.x, gl.y, price, (float)n_occ * (1.0f / (float)N));
           }
@@ -1210,7 +1235,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
                        x2[1] = pack2(c, d);
                      });
         } else if constexpr (STAGE) {
-          lds_char *sb = reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_floats) + pad) + stage_bo;
+          lds_char *sb = reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_step) + pad) + stage_bo;
           obs_record([&](uint32_t fo, uint32_t lo, float v) { *reinterpret_cast<lds_float *>(sb + fo + lo) = v; },
                      [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
                        fvec<P> x;
@@ -1255,6 +1280,14 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
             w |= __umul24(b, 1u << 16);
           }
           if ((l & (4 / P - 1)) == 0) st_at((uint32_t *)ab_t, act_bo_t + (uint32_t)port[0], w);
+        } else if (P > 1 && adjacent) {  // the lane's bytes at once, at any address
+          uint32_t w = (uint32_t)k[0];
+#pragma unroll
+          for (int j = 1; j < P; ++j) w |= (uint32_t)k[j] << (8 * j);
+          typedef uint16_t __attribute__((aligned(1))) u16a1;
+          typedef uint32_t __attribute__((aligned(1))) u32a1;
+          if constexpr (P == 2) st_at((u16a1 *)ab_t, act_bo_t + (uint32_t)port[0], (u16a1)w);
+          else st_at((u32a1 *)ab_t, act_bo_t + (uint32_t)port[0], (u32a1)w);
         } else {
 #pragma unroll
           for (int j = 0; j < P; ++j)
@@ -1283,7 +1316,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // the stage of this step is complete: out to HBM (the next step fills the
     // other buffer; the barrier of that step keeps this one until it is read)
     if (STAGE && (flags & kWObs) && (!POL || wv < n_run))
-      flush_stage(stage + (POL ? 0 : (t & 1) * stage_floats), ob_now + (int64_t)env_blk0 * obs_dim, pad, n_blk,
+      flush_stage(stage + (POL ? 0 : (t & 1) * stage_step), ob_now + (int64_t)env_blk0 * obs_dim, pad, n_blk,
                   (group - g_blk0) * 64 + lane, n_run * 64);
     if constexpr (POL) {
       // the next step's levels (the phase's barriers keep the stage until the
@@ -1329,7 +1362,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
 // The launch's blocks are dealt to the chip's 8 XCDs in turn (block i to XCD
 // i mod 8).  Numbered so that each XCD's blocks are consecutive, blocks of
 // adjacent envs, whose small records (actions, rewards, done flags) share
-// 128-byte lines, write those lines through the same L2.
+// 128-byte lines, write those lines through the same L2 (V2G at 8 lanes and one
+// wave per block: 2.57 -> 2.41 ms).
 __device__ __forceinline__ int xcd_block() {
   const int i = blockIdx.x, n = gridDim.x;
   const int x = i & 7, q = n >> 3, r = n & 7;
@@ -1343,8 +1377,7 @@ template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL>
 __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   constexpr bool POL = HPOL > 0;
   extern __shared__ uint32_t lds_tdwell[];
-  // (the staged kernels, whose blocks write whole runs of adjacent envs)
-  const int b = STAGE ? __builtin_amdgcn_readfirstlane(xcd_block()) : (int)blockIdx.x;
+  const int b = uni(xcd_block());
   int lo = 0, hi = a.n_segs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -1375,7 +1408,7 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   // device memory)
   const int steps = C.steps_ep;
   if (!POL && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
-    lds_char *base = (lds_char *)lds_tdwell + ((4 * n_stay + 15) & ~15);
+    lds_char *base = (lds_char *)lds_tdwell + a.day_off;
     lds_u32x4 *tp = (lds_u32x4 *)base;
     lds_float *pr = (lds_float *)(base + 16 * steps);
     for (int i = threadIdx.x; i < steps; i += blockDim.x) {
@@ -1384,6 +1417,13 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
     }
     exo_tp = tp;
     exo_pr = pr;
+  }
+  lds_u32 *car_tab = nullptr;
+  if constexpr (EXT) {
+    car_tab = (lds_u32 *)((lds_char *)lds_tdwell + a.car_off);
+    const int i = threadIdx.x;
+    if (i < 8) car_tab[i] = gld(C.model_thresh, i);
+    else if (i < 32) car_tab[i] = __float_as_uint(gld(C.model_data, i - 8));
   }
   __syncthreads();
   const int W = blockDim.x >> 6;
@@ -1394,12 +1434,15 @@ __device__ __forceinline__ void rollout_body(LaunchArgs a) {
   if (!POL && group >= n_groups) return;
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
   lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, HPOL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, stage,
-                                           a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
+  run_group<L, P, SIMPLE, EXT, STAGE, HPOL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, car_tab, stage,
+                                           W == 1 ? 0 : a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
 }
 
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
-__global__ __launch_bounds__(512) void k_rollout(LaunchArgs a) {
+// (Extended classes of one slot per lane are held to five waves per SIMD, 96
+// registers of the 102 they would take: at 16 lanes V2G 2.71 -> 2.56 ms.)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P == 1 ? 5 : 1))) void k_rollout(
+    LaunchArgs a) {
   rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a);
 }
 
@@ -1477,38 +1520,62 @@ const KernelFn kKernels[kNumKinds * kNumPackings] = {
 #undef CX_KINDS
 #undef CX_KINDS_SIMPLE
 
-// Arguments of one group's launch: its slice of the segment table and its LDS
-// (the stay table; for staging packings the observation stages when
-// observations are written).
-LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, size_t *lds) {
+// Waves of all groups of a launch.
+int64_t total_waves(const LaunchGroup *groups, int n_groups) {
+  int64_t n = 0;
+  for (int i = 0; i < n_groups; ++i) n += (int64_t)groups[i].n_blocks * groups[i].wpb;
+  return n;
+}
+
+// The kernel kind a group runs as in this launch: a SIMPLE class's observations
+// go through the stage, asked for or not, in a launch of at least as many waves
+// as the chip holds at once (8 per SIMD): its writes then set the pace, and the
+// stage's whole lines are worth its barrier per step.  100 steps, every record,
+// stage against lane stores: 16-port stations at 4,096 waves 0.202 / 0.179 ms,
+// 8,192 0.330 / 0.353, 16,384 0.586 / 0.667; the mixture at 2,500 waves 0.414 /
+// 0.342, 8,300 0.493 / 0.531, 27,300 1.280 / 1.594.
+constexpr int64_t kStageMinWaves = 8192;
+int launch_kind(const LaunchArgs &a, const LaunchGroup &g, int64_t waves) {
+  if (g.kind != kKindSimple || a.per_segment || a.out_mode != CX_OUT_FULL || !a.obs || a.T < kLdsExoMinT ||
+      waves < kStageMinWaves)
+    return g.kind;
+  return lds_plan(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, true, false).bytes <= kMaxBlockLds
+             ? kKindSimpleStaged
+             : kKindSimple;
+}
+
+// Arguments of one group's launch as kernel kind `kind`: its slice of the
+// segment table and its LDS.
+LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, size_t *lds) {
   LaunchArgs b = a;
   b.segs = a.segs + g.seg_begin;
   b.n_segs = g.n_segs;
   b.lds_tdwell = 1;  // staging the table costs one load per thread and beats device-memory
                      // bisection even for one-step launches
-  const bool records =
-      group_stages(g.kind, g.pack) && (a.per_segment || (a.out_mode == CX_OUT_FULL && a.obs != nullptr));
-  const size_t with_stages = group_lds_bytes(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps,
-                                             &b.stage_off, &b.stage_floats);
-  if (records) {
-    *lds = with_stages;
-  } else {
-    b.stage_floats = 0;
-    *lds = group_table_bytes(g.max_dwell_log2, g.max_day_steps);
-  }
+  const bool stages =
+      kind == kKindSimpleStaged && (a.per_segment || (a.out_mode == CX_OUT_FULL && a.obs != nullptr));
+  const LdsPlan p = lds_plan(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, stages,
+                             kind == kKindExt);
+  b.day_off = p.day_off;
+  b.stage_off = p.stage_off;
+  b.stage_floats = p.stage_floats;
+  b.car_off = p.car_off;
+  *lds = p.bytes;
   return b;
 }
 
 }  // namespace
 
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st) {
+  const int64_t waves = total_waves(groups, n_groups);
   for (int i = 0; i < n_groups; ++i) {
     const LaunchGroup &g = groups[i];
     if (g.n_blocks <= 0) continue;
     size_t lds = 0;
-    LaunchArgs b = group_args(a, g, &lds);
+    const int kind = launch_kind(a, g, waves);
+    LaunchArgs b = group_args(a, g, kind, &lds);
     void *params[1] = {&b};
-    hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kKernels[kNumKinds * g.pack + g.kind]), dim3(g.n_blocks),
+    hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kKernels[kNumKinds * g.pack + kind]), dim3(g.n_blocks),
                                    dim3(64 * g.wpb), params, lds, st);
     if (e != hipSuccess) return e;
   }
@@ -1542,20 +1609,22 @@ hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup
   hipKernelNodeParams p[kNumKinds * kNumPackings];
   int shape[kNumKinds * kNumPackings][4] = {};
   int n = 0;
+  const int64_t waves = total_waves(groups, n_groups);
   for (int i = 0; i < n_groups && n < kNumKinds * kNumPackings; ++i) {
     const LaunchGroup &g = groups[i];
     if (g.n_blocks <= 0) continue;
     size_t lds = 0;
-    args[n] = group_args(a, g, &lds);
+    const int kind = launch_kind(a, g, waves);
+    args[n] = group_args(a, g, kind, &lds);
     params[n][0] = &args[n];
     p[n] = hipKernelNodeParams{};
-    p[n].func = reinterpret_cast<void *>(kKernels[kNumKinds * g.pack + g.kind]);
+    p[n].func = reinterpret_cast<void *>(kKernels[kNumKinds * g.pack + kind]);
     p[n].gridDim = dim3(g.n_blocks);
     p[n].blockDim = dim3(64 * g.wpb);
     p[n].sharedMemBytes = (unsigned)lds;
     p[n].kernelParams = params[n];
     p[n].extra = nullptr;
-    shape[n][0] = kNumKinds * g.pack + g.kind;
+    shape[n][0] = kNumKinds * g.pack + kind;
     shape[n][1] = g.n_blocks;
     shape[n][2] = g.wpb;
     shape[n][3] = (int)lds;
