@@ -279,8 +279,9 @@ cx_status cx_step_ex(cx_ctx *ctx, cx_action_mode mode, const uint8_t *actions_in
  * stations' state in registers for all T steps and streams the records
  * selected by out_mode to *out (device buffers, caller-owned, layouts of
  * cx_traj; NULL members are not written).  actions_in_dev ([T][total_ports] uint8) is read only for EXTERNAL.
- * The launch is captured once per (T, modes, buffers) into a HIP graph and
- * replayed.  Results equal T calls of cx_step_ex.
+ * Classes of several packings share one launch where it is small enough, else
+ * they are the kernels of a HIP graph, instantiated once per launch shape.
+ * Results equal T calls of cx_step_ex.
  * CX_ACT_POLICY draws every step's levels from the policy (cx_set_policy) on
  * the observation of the state before the step.  For a class of 8, 16 or 32
  * slots the whole rollout is one launch of a fused persistent kernel that runs

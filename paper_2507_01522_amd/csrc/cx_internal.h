@@ -40,6 +40,9 @@ inline int pack_id(int lanes, int per_lane) {
   return pi * 5 + li;
 }
 
+// Packings of one or two slots per lane, as k_rollout_parts numbers them.
+__host__ __device__ constexpr int part_id(int lanes, int per_lane) { return 100 * per_lane + lanes; }
+
 // One compiled station class, in device memory.  Per-slot arrays use the
 // padded, aligned slot layout: slot s of a station holds port slot_port[s]
 // (-1 for a padding slot that never holds a car).
@@ -164,6 +167,12 @@ struct LaunchArgs {
   uint8_t *done;
   const uint8_t *act_in;
   int64_t obs_stride, act_stride, env_stride;
+  // several groups in one launch: each one's blocks, segments and packing
+  static constexpr int kMaxParts = 10;
+  struct Part {
+    int32_t block_begin, n_blocks, seg_begin, n_segs, pack;
+  } part[kMaxParts];
+  int32_t n_parts;
   // the fused policy rollout (mode CX_ACT_POLICY): the MLP's weights in
   // fragment order, its sizes, the observation the rollout starts from, and
   // where the block's BF16 observations, hidden units and levels sit in LDS

@@ -1359,13 +1359,12 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
 
 #undef CX_OCCUPIED
 
-// The launch's blocks are dealt to the chip's 8 XCDs in turn (block i to XCD
+// A launch's blocks are dealt to the chip's 8 XCDs in turn (block i to XCD
 // i mod 8).  Numbered so that each XCD's blocks are consecutive, blocks of
 // adjacent envs, whose small records (actions, rewards, done flags) share
 // 128-byte lines, write those lines through the same L2 (V2G at 8 lanes and one
 // wave per block: 2.57 -> 2.41 ms).
-__device__ __forceinline__ int xcd_block() {
-  const int i = blockIdx.x, n = gridDim.x;
+__device__ __forceinline__ int xcd_block(int i, int n) {
   const int x = i & 7, q = n >> 3, r = n & 7;
   return x * q + (x < r ? x : r) + (i >> 3);
 }
@@ -1374,19 +1373,19 @@ __device__ __forceinline__ int xcd_block() {
 // kind (general, SIMPLE, bidirectional), so that each keeps its own register
 // budget; the entry points below add the launch bounds of each kind.
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL>
-__device__ __forceinline__ void rollout_body(LaunchArgs a) {
+__device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *segs, int n_segs, int b) {
   constexpr bool POL = HPOL > 0;
   extern __shared__ uint32_t lds_tdwell[];
-  const int b = uni(xcd_block());
-  int lo = 0, hi = a.n_segs - 1;
+  CX_KONST SegDev *const seg0 = konst(segs);
+  int lo = 0, hi = n_segs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (a.segs[mid].block_begin <= b) lo = mid;
+    if (seg0[mid].block_begin <= b) lo = mid;
     else hi = mid - 1;
   }
   // the segment is block-uniform: say so, so its fields come in scalar loads
-  lo = __builtin_amdgcn_readfirstlane(lo);
-  CX_KONST SegDev *const sgp = konst(a.segs) + lo;
+  lo = uni(lo);
+  CX_KONST SegDev *const sgp = seg0 + lo;
   CX_KONST SegDev &sg = *sgp;
   CX_KONST ClassDev &C = *konst((const ClassDev *)sg.cls);
   Dyn dy;
@@ -1443,7 +1442,7 @@ template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
 // registers of the 102 they would take: at 16 lanes V2G 2.71 -> 2.56 ms.)
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P == 1 ? 5 : 1))) void k_rollout(
     LaunchArgs a) {
-  rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a);
+  rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // SIMPLE classes of 1 or 2 slots per lane: the kernel held to CX_SIMPLE_WAVES
@@ -1455,21 +1454,47 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P ==
 template <int L, int P, bool STAGE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CX_SIMPLE_WAVES))) void k_rollout_simple(
     LaunchArgs a) {
-  rollout_body<L, P, true, false, STAGE, 0>(a);
+  rollout_body<L, P, true, false, STAGE, 0>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // The fused policy rollout (4 waves per block): three blocks per CU, so that
 // one block's matrix-core work and memory waits overlap the others' steps.
 template <int L, int P, int HP>
 __global__ __launch_bounds__(64 * kPolRolloutWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_rollout_policy(LaunchArgs a) {
-  rollout_body<L, P, true, false, true, HP>(a);
+  rollout_body<L, P, true, false, true, HP>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 // ... of classes that are not SIMPLE (padding slots, port maxima or limits that
 // differ, the dense layout): a policy rollout of the 10 DC + 6 AC station used to
 // take two launches a step.
 template <int L, int P, int HP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
-  rollout_body<L, P, false, false, true, HP>(a);
+  rollout_body<L, P, false, false, true, HP>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
+}
+
+// Several groups of SIMPLE classes in one launch (a.part: each group's blocks, at
+// a multiple of 8 so that they are dealt to the XCDs as in a launch of their
+// own).  For launches too short to fill the chip one group at a time: one step
+// of 65,536 uneven stations took five kernels one after the other (74 us, now 50).
+__global__ __launch_bounds__(512) void k_rollout_parts(LaunchArgs a) {
+  int i = 0;
+  while (i + 1 < a.n_parts && (int)blockIdx.x >= a.part[i + 1].block_begin) ++i;
+  i = uni(i);
+  const LaunchArgs::Part &p = a.part[i];
+  const int b0 = (int)blockIdx.x - p.block_begin;
+  if (b0 >= p.n_blocks) return;   // (the gap before the next group)
+  const int b = xcd_block(b0, p.n_blocks);
+  const SegDev *segs = a.segs + p.seg_begin;
+  const int n = p.n_segs;
+  switch (p.pack) {
+#define CX_PART(L, P)                                                                              \
+  case part_id(L, P):                                                                              \
+    rollout_body<L, P, true, false, false, 0>(a, segs, n, b);                                      \
+    break;
+    CX_PART(4, 1) CX_PART(8, 1) CX_PART(16, 1) CX_PART(32, 1) CX_PART(64, 1)
+    CX_PART(4, 2) CX_PART(8, 2) CX_PART(16, 2) CX_PART(32, 2) CX_PART(64, 2)
+#undef CX_PART
+    default: break;
+  }
 }
 
 // Observation of empty stations at t_day = 0 for every env of one segment
@@ -1566,7 +1591,55 @@ LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, size_
 
 }  // namespace
 
+namespace {
+
+// All groups in one launch (k_rollout_parts) when they are SIMPLE classes of one
+// or two slots per lane with one block size and the launch is one step, or has
+// at most kPartsMaxWaves waves.  A graph of one kernel per packing costs 95 us of
+// host time a launch and runs its kernels only partly at once, but keeps each
+// packing's own registers (the shared kernel takes the largest, five waves per
+// SIMD) and the stage, which pays when the chip is full.  Uneven stations x 288
+// steps, every record (rewards only), one launch against the graph: 2,000 0.50
+// (0.35) / 0.78 (0.56) ms, 10,000 0.58 (0.35) / 0.86 (0.55), 20,000 (8,400 waves)
+// 1.15 (0.62) / 1.20 (0.62), 65,536 (27,300) 3.54 (1.69) / 3.49 (1.57).  One step:
+// 300 stations 35 -> 9 us, 65,536 74 -> 50.  False: not such a launch.
+constexpr int64_t kPartsMaxWaves = 12288;
+bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st, hipError_t *e) {
+  if (n_groups < 2 || n_groups > LaunchArgs::kMaxParts || a.per_segment) return false;
+  if (a.T > 1 && total_waves(groups, n_groups) > kPartsMaxWaves) return false;
+  LaunchArgs b = a;
+  int blocks = 0, dwell = 1, days = 0;
+  b.n_parts = 0;
+  for (int i = 0; i < n_groups; ++i) {
+    const LaunchGroup &g = groups[i];
+    if ((g.kind != kKindSimple && g.kind != kKindSimpleStaged) || pack_per_lane(g.pack) > 2 || g.wpb != groups[0].wpb)
+      return false;
+    if (g.n_blocks <= 0) continue;
+    blocks = (blocks + 7) & ~7;
+    b.part[b.n_parts++] = {blocks, g.n_blocks, g.seg_begin, g.n_segs,
+                           part_id(pack_lanes(g.pack), pack_per_lane(g.pack))};
+    blocks += g.n_blocks;
+    dwell = std::max(dwell, g.max_dwell_log2);
+    days = std::max(days, g.max_day_steps);
+  }
+  if (blocks == 0) {
+    *e = hipSuccess;
+    return true;
+  }
+  b.lds_tdwell = 1;
+  const LdsPlan p = lds_plan(groups[0].wpb, groups[0].pack, 0, dwell, a.T >= kLdsExoMinT ? days : 0, false, false);
+  b.day_off = p.day_off;
+  void *params[1] = {&b};
+  *e = hipLaunchKernel(reinterpret_cast<const void *>(&k_rollout_parts), dim3(blocks), dim3(64 * groups[0].wpb), params,
+                       p.bytes, st);
+  return true;
+}
+
+}  // namespace
+
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st) {
+  hipError_t pe;
+  if (launch_parts(a, groups, n_groups, st, &pe)) return pe;
   const int64_t waves = total_waves(groups, n_groups);
   for (int i = 0; i < n_groups; ++i) {
     const LaunchGroup &g = groups[i];
@@ -1604,6 +1677,10 @@ hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int per_lane,
 
 hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st) {
+  // one kernel is launched as it is; so are groups that share a launch
+  hipError_t pe;
+  if (n_groups == 1) return launch_groups(a, groups, n_groups, st);
+  if (launch_parts(a, groups, n_groups, st, &pe)) return pe;
   LaunchArgs args[kNumKinds * kNumPackings];
   void *params[kNumKinds * kNumPackings][1];
   hipKernelNodeParams p[kNumKinds * kNumPackings];

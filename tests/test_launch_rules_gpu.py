@@ -33,3 +33,27 @@ def test_stage_chosen_by_size(cxm, ports, extra):
         for k in y:
             assert torch.equal(x[k][t0:t0 + 20], y[k]), (k, t0)
     assert a.get_state() == b.get_state()
+
+
+@pytest.mark.parametrize("n,T", [(40, 1), (40, 45), (700, 33)])
+def test_one_launch_for_all_packings(cxm, n, T):
+    """Classes of five packings (8 to 128 ports, ragged env counts) in one launch
+    against each class in a context of its own, where it is a launch of its own."""
+    specs = [W.fanout4_tree(p, d) for p in (8, 16, 32, 64, 128) for d in (1, 3)]
+    counts = [n + 3 * i for i in range(len(specs))]
+    ec = np.repeat(np.arange(len(specs)), counts)
+    env = cxm.Env(specs, env_class=ec, seed=43)
+    env.rollout(140, cxm.ACT_MAX, cxm.OUT_REWARD)
+    out = env.step(cxm.ACT_RANDOM) if T == 1 else env.rollout(T, cxm.ACT_RANDOM)
+    # a context per class, its other envs in a second class that keeps the env indices
+    for c, spec in enumerate(specs):
+        pair = cxm.Env([spec, W.two_charger_types()], env_class=np.repeat([0, 1], [ec.size - 1, 1]), seed=43)
+        pair.rollout(140, cxm.ACT_MAX, cxm.OUT_REWARD)
+        ref = pair.step(cxm.ACT_RANDOM) if T == 1 else pair.rollout(T, cxm.ACT_RANDOM)
+        ci = env.class_info(c)
+        e0, e1 = ci.env_begin, min(ci.env_begin + ci.n_envs, ec.size - 1)   # same env index, same draws
+        k = e1 - e0
+        for key, off, width in (("reward", e0, 1), ("done", e0, 1), ("actions", ci.port_offset, ci.n_actions),
+                                ("obs", ci.obs_offset, ci.obs_dim)):
+            own = ref[key][:, e0 * width:e1 * width]
+            assert torch.equal(out[key][:, off:off + k * width], own), (c, key)
