@@ -583,7 +583,7 @@ cx_status cx_get_tables(const cx_ctx *ctx, int32_t cls, uint32_t *tpois_host, ui
   if (!ctx) return fail_status(CX_E_INVALID, "context is NULL");
   if (cls < 0 || cls >= (int32_t)ctx->classes.size()) return fail_status(CX_E_INVALID, "class out of range");
   const Tables &t = ctx->classes[cls].tab;
-  if (tpois_host) std::memcpy(tpois_host, t.tpois.data(), sizeof(uint32_t) * t.tpois.size());
+  if (tpois_host) copy_tpois(t, tpois_host);
   if (tdwell_host) std::memcpy(tdwell_host, t.tdwell.data(), sizeof(uint32_t) * t.tdwell.size());
   return CX_OK;
 }
@@ -652,7 +652,7 @@ cx_status cx_build_tables(const cx_station_spec *spec, uint32_t *tpois, uint32_t
   if (!copy_spec(*spec, &sc, &err) || !compile_spec(sc, &k, &err)) return fail_status(CX_E_INVALID, err);
   Tables t;
   build_tables(sc, &t);
-  if (tpois) std::memcpy(tpois, t.tpois.data(), sizeof(uint32_t) * t.tpois.size());
+  if (tpois) copy_tpois(t, tpois);
   if (tdwell) std::memcpy(tdwell, t.tdwell.data(), sizeof(uint32_t) * t.tdwell.size());
   return CX_OK;
 }

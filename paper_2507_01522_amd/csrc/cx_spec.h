@@ -55,7 +55,6 @@ struct Compiled {
 };
 
 struct Tables {
-  std::vector<uint32_t> tpois;      // [steps][24] as defined
   std::vector<uint32_t> tpois_dev;  // [steps][32] padded with 0xFFFFFFFF
   std::vector<uint32_t> tdwell;     // [dwell_max], entry 0 unused
   std::vector<uint32_t> tdwell_dev; // [2^dwell_log2]: entries 1.. of tdwell, then 0xFFFFFFFF
@@ -67,6 +66,7 @@ struct Tables {
 bool copy_spec(const cx_station_spec &in, SpecCopy *out, std::string *err);
 bool compile_spec(const SpecCopy &sc, Compiled *c, std::string *err);
 void build_tables(const SpecCopy &sc, Tables *t);
+void copy_tpois(const Tables &t, uint32_t *out);  // [steps][24]: the rows without their padding
 bool tables_monotone(const Tables &t);
 
 }  // namespace cx
