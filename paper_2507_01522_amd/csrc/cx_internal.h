@@ -247,24 +247,38 @@ inline LdsPlan lds_plan(int wpb, int pack, int max_obs_dim, int dwell_log2, int 
 }
 
 // The fused policy rollout: blocks of 4 waves of 8-lane stations (32 envs, two
-// 16-env tiles of the MLP).  LDS: the stay table, then the stage (one
-// buffer of 32 observations), which the hidden units (8 x 2 KiB) overwrite once
-// it has been read, then the observations in BF16 (32 x 528 bytes) and a level
-// byte per port and env.  Returns the bytes; sets the offsets.
+// 16-env tiles of the MLP) or of 16-lane ones (16 envs).  LDS: the stay table, then
+// the stage (one buffer of 32 observations), the hidden units (8 x 2 KiB; over
+// the stage, once it has been read, or after it), then the observations in BF16 (32
+// x 528 bytes) and a level byte per port and env.  Returns the bytes; sets the offsets.
 constexpr int kPolRolloutWaves = 4;
 constexpr int kPolRolloutEnvs = kPolRolloutWaves * 8;
+// Launches of at most one block per CU hold the MLP's weights in registers: one
+// wave per SIMD has 512 of them, and its step is one chain that fetching 160 KB a
+// block from L2 (and waiting, in order, for the records before them) only made
+// longer.  16-port stations, 256 hidden units, every record, 96 steps: 8,192 envs
+// (256 blocks) 588 -> 397 us held; a second round of such blocks would cost as much
+// again, and 8,224 envs, three blocks to a CU, take 583.
+constexpr int kPolHeldBlocks = 256;
+// The step writes its observations in BF16 beside the records' stage, and the
+// hidden units have an LDS region of their own: with held weights, and for
+// stations of up to 16 slots (three such blocks still fit a CU's LDS; of 32
+// slots they would not).  Else the stage is converted and then overwritten, a
+// pass over LDS and a barrier more: the same launch 677 -> 583 us at 8,224 envs.
+constexpr bool policy_dual(int slots, bool held) { return held || slots <= 16; }
 constexpr int kPolXbRow = 33;  // 16-byte fragments per env row of the BF16 observations (32 used)
-inline size_t policy_rollout_lds(int dwell_log2, int obs_dim, int N, int32_t *stage_off,
+inline size_t policy_rollout_lds(int dwell_log2, int obs_dim, int N, bool over_stage, int32_t *stage_off,
                                  int32_t *stage_floats, int32_t *hb_off, int32_t *xb_off, int32_t *act_off) {
   auto a16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
   const size_t off = a16((size_t)4 << dwell_log2);  // the stay table only (no per-step tables)
   const size_t floats = ((size_t)kPolRolloutEnvs * obs_dim + 3 + 3) & ~(size_t)3;  // 3: alignment with HBM
-  const size_t region = a16(std::max(4 * floats, (size_t)8 * (kPolRolloutEnvs / 16) * 64 * 16));
-  const size_t xb = off + region;
+  const size_t hidden = (size_t)8 * (kPolRolloutEnvs / 16) * 64 * 16;
+  const size_t hb = over_stage ? off : off + a16(4 * floats);
+  const size_t xb = std::max(off + a16(4 * floats), hb + hidden);
   const size_t act = xb + (size_t)kPolRolloutEnvs * 16 * kPolXbRow;
   *stage_off = (int32_t)off;
   *stage_floats = (int32_t)floats;
-  *hb_off = (int32_t)off;
+  *hb_off = (int32_t)hb;
   *xb_off = (int32_t)xb;
   *act_off = (int32_t)act;
   return act + a16((size_t)kPolRolloutEnvs * N);
@@ -303,8 +317,8 @@ struct PolicyArgs {
 // Host-side launchers (defined in cx_kernels.hip).  `a.segs` is the base of
 // the device segment table; each group launches with its own slice.
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st);
-hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int per_lane, int hp, int n_blocks, size_t lds,
-                                 hipStream_t st);
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, int hp, bool held,
+                                 int n_blocks, size_t lds, hipStream_t st);
 hipError_t graph_rollout(RolloutGraph &g, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st);
 void graph_destroy(RolloutGraph &g);

@@ -315,13 +315,17 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 // rows 33 fragments apart so that the 16 envs of a tile fall in different
 // banks) and act (a level byte per port and env).  wv: this wave in the block;
 // convert: the step left its observations in the FP32 stage; hid: the first
-// product, its first fragments already asked for.
-template <int K1, int HP>
+// product, its first fragments already asked for.  HELD (launches of at most one
+// block per CU): both products' fragments and biases stay in registers for the
+// whole rollout, those of the second in `held` (NG port groups a wave; HELD2) or
+// a group's K-steps ahead in its ring, which then goes round over the steps.
+template <int K1, int HP, int NT, bool HELD, bool HELD2, int DEPTH, int NG>
 __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const lds_float *stage, lds_char *lds,
                                              int obs_dim, int N, int blk_envs, int wv, uint32_t env_id0,
                                              uint32_t g, uint32_t k0, uint32_t k1, bool convert,
-                                             HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, K1, HP> &hid) {
-  constexpr int W = kPolRolloutWaves, NT = kPolRolloutEnvs / 16, CPR = 4 * K1;  // chunks of 8 per row
+                                             HiddenLayer<kPolRolloutWaves, NT, K1, HP, HELD> &hid,
+                                             LogitLayer<NT, HP, HELD2, DEPTH> (&held)[NG]) {
+  constexpr int W = kPolRolloutWaves, E = 16 * NT, CPR = 4 * K1;  // E envs; chunks of 8 per row
   const int lane = __lane_id(), col = lane & 15, lg = lane >> 4, tid = wv * 64 + lane;
   const int in_dim = pl.in_dim, G = pl.G, L1 = pl.L1;
   lds_u32x4 *xb = reinterpret_cast<lds_u32x4 *>(lds + pl.xb_off);
@@ -331,7 +335,7 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
   // Without observation records the step wrote its values straight into xb
   // (convert = false), whose padding the first conversion zeroed.
   if (convert) {
-    for (int c = tid; c < kPolRolloutEnvs * CPR; c += 64 * W) {
+    for (int c = tid; c < E * CPR; c += 64 * W) {
       const int e = c / CPR, k = c % CPR, f = 8 * k;
       const lds_float *row = stage + e * obs_dim + f;
       u32x4 v = {0u, 0u, 0u, 0u};
@@ -353,8 +357,8 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
   }
   hid.run(frag_rsrc(pl.w1f, 2 * kPolHP * kPolK1), pl.b1, xb, kPolXbRow, hb, wv);
   const __amdgpu_buffer_rsrc_t w2 = frag_rsrc(pl.w2f, G * kPolR * kPolHP);
-  LogitLayer<NT, HP> logit;
-  logit.start(w2, min(wv, G - 1));
+  LogitLayer<NT, HP, HELD2, DEPTH> &logit = held[0];
+  if constexpr (!HELD) logit.start(w2, pl.b2f, min(wv, G - 1));
   // the lane's ports are 4 wv + lg + 16 i (group wv + 4 i): one Philox call per
   // env serves them all
   U4 dw[NT];
@@ -362,10 +366,10 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
   for (int n = 0; n < NT; ++n)
     dw[n] = philox(env_id0 + (uint32_t)(16 * n + col), g, draw_index(4 * wv + lg), kDomGum, k0, k1);
   __syncthreads();
-  for (int grp = wv; grp < G; grp += W) {
+  const auto draw_group = [&](int grp, LogitLayer<NT, HP, HELD2, DEPTH> &layer) {
     const int port = 4 * grp + lg;
     f32x4 c[kPolR][NT];
-    logit.run(w2, pl.b2f, hb, grp, min(grp + W, G - 1), c);
+    layer.run(w2, pl.b2f, hb, grp, grp + W < G ? grp + W : HELD ? wv : -1, c);
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const int e = 16 * n + col;
@@ -373,6 +377,13 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
       const int lev = sample_level(cn, L1, draw_uniform(draw_word(dw[n], port)));
       if (port < N && e < blk_envs) act[e * N + port] = (uint8_t)lev;
     }
+  };
+  if constexpr (HELD2) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+      if (wv + W * i < G) draw_group(wv + W * i, held[i]);
+  } else {
+    for (int grp = wv; grp < G; grp += W) draw_group(grp, logit);
   }
   __syncthreads();
 }
@@ -383,8 +394,9 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 // copies of the first four arrival thresholds and the base price of every step
 // of the day (NULL: read device memory); car_tab: of the car models' 8 thresholds
 // and 8 x {capacity, AC rate, DC rate} (extended classes).
-// HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL = 0>
+// HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units; HELD:
+// its weights stay in registers.
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL = 0, bool HELD = false>
 __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, int group, const lds_u32 *tdw,
                                           const lds_u32x4 *exo_tp, const lds_float *exo_pr,
                                           const lds_u32 *car_tab, lds_float *stage,
@@ -578,13 +590,27 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   // 6 L P + 4 features)
   constexpr int kPolSteps1 = (6 * L * P + 4 + 31) / 32;
   [[maybe_unused]] const auto w1_rsrc = [&] { return frag_rsrc(pol->w1f, 2 * kPolHP * kPolK1); };
+  constexpr int NT = POL ? kPolRolloutWaves * SPW / 16 : 1, HP = POL ? HPOL : 2;  // 16-env tiles of the block
+  // port groups of a wave, and whether the second product's fragments of all of
+  // them fit in the registers beside the step (96 of them; at 32 slots and 256
+  // hidden units they would take 192, and spill)
+  constexpr bool DUAL = POL && policy_dual(L * P, HELD);
+  constexpr int kGroups = L * P > 16 ? L * P / 16 : 1;
+  constexpr bool HELD2 = HELD && kGroups * HP <= 8;
+  constexpr int NG = HELD2 ? kGroups : 1;
+  [[maybe_unused]] HiddenLayer<kPolRolloutWaves, NT, kPolSteps1, HP, HELD> held1;
+  [[maybe_unused]] LogitLayer<NT, HP, HELD2, HELD ? HP : kRing> held2[NG];
   if constexpr (POL) {
     const float *src = pol->obs0 + sg.obs_off + (int64_t)env_blk0 * obs_dim;
     for (int i = wv * 64 + lane; i < n_blk; i += kPolRolloutWaves * 64) stage[i] = gld(src, i);
-    HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, kPolSteps1, HPOL> hid;
-    hid.start(w1_rsrc(), wv);
+    held1.start(w1_rsrc(), pol->b1, wv);
+    if constexpr (HELD) {
+#pragma unroll
+      for (int i = 0; i < NG; ++i)
+        held2[i].start(frag_rsrc(pol->w2f, pol->G * kPolR * kPolHP), pol->b2f, min(wv + kPolRolloutWaves * i, pol->G - 1));
+    }
     __syncthreads();
-    policy_phase<kPolSteps1, HPOL>(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true, hid);
+    policy_phase(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true, held1, held2);
   }
 
   // every lane's P slots hold P adjacent ports (no padding slots)
@@ -1216,26 +1242,38 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
               put(4u * (uint32_t)C.day_obs, 4u * (uint32_t)l, l == 0 ? (float)dday * C.inv_n_days : (dday % 7 >= 5 ? 1.0f : 0.0f));
           }
         };
-        if (POL && !(flags & kWObs)) {
-          // the fused policy without observation records: the values go to
-          // the MLP's BF16 rows directly (their padding was zeroed by the
-          // first conversion)
+        // the fused policy: the values go to the MLP's BF16 rows directly (their
+        // padding was zeroed by the first conversion), unless they are converted
+        // from the stage
+        [[maybe_unused]] lds_char *const sb =
+            STAGE ? reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_step) + pad) + stage_bo : nullptr;
+        const bool to_stage = flags & kWObs;
+        if (POL && (DUAL || !to_stage)) {
           typedef __attribute__((address_space(3))) uint16_t lds_u16;
           lds_u16 *xr = reinterpret_cast<lds_u16 *>(lds + pol->xb_off) + (env - env_blk0) * (kPolXbRow * 8);
-          obs_record([&](uint32_t fo, uint32_t lo, float v) { xr[(fo + lo) >> 2] = (uint16_t)pack2(v, 0.f); },
+          obs_record([&](uint32_t fo, uint32_t lo, float v) {
+                       xr[(fo + lo) >> 2] = (uint16_t)pack2(v, 0.f);
+                       if (DUAL && to_stage) *reinterpret_cast<lds_float *>(sb + fo + lo) = v;
+                     },
                      [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
                        // (P even and N a multiple of P: a whole number of words)
                        lds_u32 *x2 = reinterpret_cast<lds_u32 *>(xr) + ((fo + lo) >> 3);
 #pragma unroll
                        for (int j = 0; j + 1 < P; j += 2) x2[j / 2] = pack2(v[j], v[j + 1]);
+                       if (DUAL && to_stage) {
+                         fvec<P> x;
+#pragma unroll
+                         for (int j = 0; j < P; ++j) set_at(x, j, v[j]);
+                         *reinterpret_cast<__attribute__((address_space(3))) fvec<P> *>(sb + fo + lo) = x;
+                       }
                      },
                      [&](uint32_t fo, float a, float b, float c, float d) {
                        lds_u32 *x2 = reinterpret_cast<lds_u32 *>(xr) + (fo >> 3);  // (6 N is even)
                        x2[0] = pack2(a, b);
                        x2[1] = pack2(c, d);
+                       if (DUAL && to_stage) *reinterpret_cast<lds_f32x4u *>(sb + fo) = f32x4{a, b, c, d};
                      });
         } else if constexpr (STAGE) {
-          lds_char *sb = reinterpret_cast<lds_char *>(stage + (POL ? 0 : (t & 1) * stage_step) + pad) + stage_bo;
           obs_record([&](uint32_t fo, uint32_t lo, float v) { *reinterpret_cast<lds_float *>(sb + fo + lo) = v; },
                      [&](uint32_t fo, uint32_t lo, const float (&v)[P]) {
                        fvec<P> x;
@@ -1322,10 +1360,9 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       // the next step's levels (the phase's barriers keep the stage until the
       // flush above has read it)
       if (t + 1 < T) {
-        HiddenLayer<kPolRolloutWaves, kPolRolloutEnvs / 16, kPolSteps1, HPOL> hid;
-        hid.start(w1_rsrc(), wv);
-        policy_phase<kPolSteps1, HPOL>(*pol, stage + pad, lds, obs_dim, N, blk_envs, wv, env_id0, g + 1u, k0, k1,
-                                       w_obs, hid);
+        if constexpr (!HELD) held1.start(w1_rsrc(), pol->b1, wv);
+        policy_phase(*pol, stage + pad, lds, obs_dim, N, blk_envs, wv, env_id0, g + 1u, k0, k1,
+                     w_obs && !DUAL, held1, held2);
       }
     }
   }
@@ -1372,7 +1409,7 @@ __device__ __forceinline__ int xcd_block(int i, int n) {
 // One kernel per packing (lanes per station L, slots per lane P) and class
 // kind (general, SIMPLE, bidirectional), so that each keeps its own register
 // budget; the entry points below add the launch bounds of each kind.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL>
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD = false>
 __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *segs, int n_segs, int b) {
   constexpr bool POL = HPOL > 0;
   extern __shared__ uint32_t lds_tdwell[];
@@ -1406,7 +1443,7 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   // launches long enough to repay copying them (short ones read them from
   // device memory)
   const int steps = C.steps_ep;
-  if (!POL && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
+  if ((HELD ? a.day_off > 0 : !POL) && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
     lds_char *base = (lds_char *)lds_tdwell + a.day_off;
     lds_u32x4 *tp = (lds_u32x4 *)base;
     lds_float *pr = (lds_float *)(base + 16 * steps);
@@ -1433,7 +1470,7 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   if (!POL && group >= n_groups) return;
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
   lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, HPOL>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, car_tab, stage,
+  run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, car_tab, stage,
                                            W == 1 ? 0 : a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
 }
 
@@ -1458,17 +1495,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CX_SIMPLE_W
 }
 
 // The fused policy rollout (4 waves per block): three blocks per CU, so that
-// one block's matrix-core work and memory waits overlap the others' steps.
-template <int L, int P, int HP>
-__global__ __launch_bounds__(64 * kPolRolloutWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_rollout_policy(LaunchArgs a) {
-  rollout_body<L, P, true, false, true, HP>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
+// one block's matrix-core work and memory waits overlap the others' steps, and
+// the weights' way from L2 bounds it (304 KB a block and step at 32 ports and 256
+// hidden units: 16 of the 31 us a step of 65,536 stations takes).  HELD: one
+// block per CU with the weights in registers and the day's tables in LDS, so
+// that no step loads anything from device memory; it is bound by the length of
+// one step's chain (10 DC + 6 AC ports, 256 hidden units, every record, 4,096 x
+// 288 steps: 1,770 -> 804 us, 2.8 us a step).
+template <int L, int P, int HP, bool HELD>
+__global__ __launch_bounds__(64 * kPolRolloutWaves) __attribute__((amdgpu_waves_per_eu(HELD ? 1 : 3))) void k_rollout_policy(LaunchArgs a) {
+  rollout_body<L, P, true, false, true, HP, HELD>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 // ... of classes that are not SIMPLE (padding slots, port maxima or limits that
 // differ, the dense layout): a policy rollout of the 10 DC + 6 AC station used to
 // take two launches a step.
-template <int L, int P, int HP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
-  rollout_body<L, P, false, false, true, HP>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
+template <int L, int P, int HP, bool HELD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
+  rollout_body<L, P, false, false, true, HP, HELD>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // Several groups of SIMPLE classes in one launch (a.part: each group's blocks, at
@@ -1656,19 +1699,26 @@ hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_g
 }
 
 // The fused policy rollout of one class: stations of 8 lanes (8, 16 or 32
-// slots), 4 waves per block (32 stations, two 16-env tiles of the MLP).  hp:
+// slots), 4 waves per block (32 stations, two 16-env tiles of the MLP), or of 16
+// lanes (16 stations, one tile).  hp:
 // K-steps of 32 hidden units; the kernels are built for 2, 4 and 8 (a policy
 // of 64 hidden units does a quarter of the matrix work of one of 256).
-hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int per_lane, int hp, int n_blocks, size_t lds,
-                                 hipStream_t st) {
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, int hp, bool held,
+                                 int n_blocks, size_t lds, hipStream_t st) {
   if (n_blocks <= 0) return hipSuccess;
-#define CX_POL(K, P) {&K<8, P, 2>, &K<8, P, 4>, &K<8, P, 8>}
-  static const KernelFn kPol[2][3][3] = {
-      {CX_POL(k_rollout_policy_general, 1), CX_POL(k_rollout_policy_general, 2), CX_POL(k_rollout_policy_general, 4)},
-      {CX_POL(k_rollout_policy, 1), CX_POL(k_rollout_policy, 2), CX_POL(k_rollout_policy, 4)}};
+  // stations of 8 lanes with 1, 2 and 4 slots per lane, the same with their
+  // weights held, and of 16 lanes, always held
+#define CX_POL(K, L, P, H) {&K<L, P, 2, H>, &K<L, P, 4, H>, &K<L, P, 8, H>}
+#define CX_POLS(K)                                                                                           \
+  {CX_POL(K, 8, 1, false), CX_POL(K, 8, 2, false), CX_POL(K, 8, 4, false), CX_POL(K, 8, 1, true),             \
+   CX_POL(K, 8, 2, true),  CX_POL(K, 8, 4, true),  CX_POL(K, 16, 1, true)}
+  static const KernelFn kPol[2][7][3] = {CX_POLS(k_rollout_policy_general), CX_POLS(k_rollout_policy)};
+#undef CX_POLS
 #undef CX_POL
   if ((per_lane != 1 && per_lane != 2 && per_lane != 4) || hp < 1 || hp > 8) return hipErrorInvalidValue;
-  const KernelFn f = kPol[simple ? 1 : 0][per_lane == 4 ? 2 : per_lane - 1][hp <= 2 ? 0 : hp <= 4 ? 1 : 2];
+  if (lanes != 8 && (lanes != 16 || per_lane != 1 || !held)) return hipErrorInvalidValue;
+  const int v = lanes == 16 ? 6 : (held ? 3 : 0) + (per_lane == 4 ? 2 : per_lane - 1);
+  const KernelFn f = kPol[simple ? 1 : 0][v][hp <= 2 ? 0 : hp <= 4 ? 1 : 2];
   LaunchArgs b = a;
   void *params[1] = {&b};
   return hipLaunchKernel(reinterpret_cast<const void *>(f), dim3(n_blocks), dim3(64 * kPolRolloutWaves), params, lds,

@@ -128,14 +128,16 @@ __device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
 // computes its pairs of 16-unit hidden tiles (HP pairs in all; with fewer pairs
 // than waves, waves share a pair and split its env tiles) from the BF16
 // observations xb (xrow fragments an env) into the hidden-unit fragments hb
-// [HP][NT][64].  K1 K-steps of 32 features.
-template <int W, int NT, int K1, int HP>
+// [HP][NT][64].  K1 K-steps of 32 features.  HELD: the ring holds every K-step's
+// fragments and the biases too, and start() is called once for many run()s.
+template <int W, int NT, int K1, int HP, bool HELD = false>
 struct HiddenLayer {
   static constexpr int NI = HP >= W ? HP / W : 1;   // pairs of this wave
   static constexpr int SH = HP >= W ? 1 : W / HP;   // waves that share a pair
   static constexpr int NN = SH <= NT ? NT / SH : 1; // env tiles of this wave
-  static constexpr int D = ring_depth(K1, kRing);
+  static constexpr int D = HELD ? K1 : ring_depth(K1, kRing);
   u32x4 a[D][NI][2];
+  f32x4 bias[HELD ? NI : 1][2];   // HELD
 
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t w1, int wv, int s) {
     const int mp0 = SH == 1 ? wv : wv % HP;
@@ -144,11 +146,20 @@ struct HiddenLayer {
 #pragma unroll
       for (int h = 0; h < 2; ++h) a[s % D][i][h] = frag(w1, (2 * (mp0 + W * i) + h) * kPolK1 + s);
   }
+  __device__ __forceinline__ void load_bias(const float *b1, int wv, int i, f32x4 (&b)[2]) {
+    const int mp = (SH == 1 ? wv : wv % HP) + W * i, lg = __lane_id() >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) b[h] = gld(reinterpret_cast<const f32x4 *>(b1 + 32 * mp + 16 * h + 4 * lg), 0);
+  }
   // the first K-steps' fragments, ahead of run()
-  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w1, int wv) {
+  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w1, [[maybe_unused]] const float *b1, int wv) {
     pin();
 #pragma unroll
     for (int s = 0; s < D; ++s) load(w1, wv, s);
+    if constexpr (HELD) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) load_bias(b1, wv, i, bias[i]);
+    }
     pin();
   }
   __device__ __forceinline__ void run(__amdgpu_buffer_rsrc_t w1, const float *b1, const lds_u32x4 *xb, int xrow,
@@ -172,45 +183,59 @@ struct HiddenLayer {
           c[i][1][n] = mfma_bf16(a[s % D][i][1], b, c[i][1][n]);
         }
       }
-      pin();
-      if (s + D < K1) load(w1, wv, s + D);
-      pin();
+      if constexpr (!HELD) {
+        pin();
+        if (s + D < K1) load(w1, wv, s + D);
+        pin();
+      }
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int mp = mp0 + W * i;
-      const f32x4 bA = gld(reinterpret_cast<const f32x4 *>(b1 + 32 * mp + 4 * lg), 0);
-      const f32x4 bB = gld(reinterpret_cast<const f32x4 *>(b1 + 32 * mp + 16 + 4 * lg), 0);
+      f32x4 b[2];
+      if constexpr (HELD) b[0] = bias[i][0], b[1] = bias[i][1];
+      else load_bias(b1, wv, i, b);
 #pragma unroll
-      for (int n = 0; n < NN; ++n) hb[(mp * NT + n0 + n) * 64 + lane] = hidden_frag(c[i][0][n], c[i][1][n], bA, bB);
+      for (int n = 0; n < NN; ++n) hb[(mp * NT + n0 + n) * 64 + lane] = hidden_frag(c[i][0][n], c[i][1][n], b[0], b[1]);
     }
   }
 };
 
 // The logits of port groups grp (4 ports) for 16 NT envs: c[r][n] holds levels
 // 4 r .. 4 r + 3 of port 4 grp + lane / 16 of env 16 n + lane % 16.  run()
-// leaves the first K-steps of group `next` in flight.
-template <int NT, int HP>
+// leaves the first K-steps of group `next` (if >= 0) in flight.  HELD: one group's
+// fragments and biases, all of them, for many run()s.
+template <int NT, int HP, bool HELD = false, int DEPTH = kRing>
 struct LogitLayer {
-  static constexpr int D = ring_depth(HP, kRing);   // divides HP
+  static constexpr int D = HELD ? HP : ring_depth(HP, DEPTH);   // divides HP
   u32x4 w[D][kPolR];
+  f32x4 bias[HELD ? kPolR : 1];   // HELD
 
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t w2, int grp, int s) {
 #pragma unroll
     for (int r = 0; r < kPolR; ++r) w[s % D][r] = frag(w2, (grp * kPolR + r) * kPolHP + s);
   }
-  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w2, int grp) {
+  __device__ __forceinline__ f32x4 load_bias(const float *b2f, int grp, int r) {
+    return gld(reinterpret_cast<const f32x4 *>(b2f + (int64_t)(grp * kPolR + r) * 16 + 4 * (__lane_id() >> 4)), 0);
+  }
+  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t w2, [[maybe_unused]] const float *b2f, int grp) {
     pin();
 #pragma unroll
     for (int s = 0; s < D; ++s) load(w2, grp, s);
+    if constexpr (HELD) {
+#pragma unroll
+      for (int r = 0; r < kPolR; ++r) bias[r] = load_bias(b2f, grp, r);
+    }
     pin();
   }
   __device__ __forceinline__ void run(__amdgpu_buffer_rsrc_t w2, const float *b2f, const lds_u32x4 *hb, int grp, int next,
                                       f32x4 (&c)[kPolR][NT]) {
-    const int lane = __lane_id(), lg = lane >> 4;
+    const int lane = __lane_id();
 #pragma unroll
     for (int r = 0; r < kPolR; ++r) {
-      const f32x4 b = gld(reinterpret_cast<const f32x4 *>(b2f + (int64_t)(grp * kPolR + r) * 16 + 4 * lg), 0);
+      f32x4 b;
+      if constexpr (HELD) b = bias[r];
+      else b = load_bias(b2f, grp, r);
 #pragma unroll
       for (int n = 0; n < NT; ++n) c[r][n] = b;
     }
@@ -223,10 +248,12 @@ struct LogitLayer {
       for (int r = 0; r < kPolR; ++r)
 #pragma unroll
         for (int n = 0; n < NT; ++n) c[r][n] = mfma_bf16(w[s % D][r], hv[n], c[r][n]);
-      pin();
-      if (s + D < HP) load(w2, grp, s + D);
-      else load(w2, next, s + D - HP);
-      pin();
+      if constexpr (!HELD) {
+        pin();
+        if (s + D < HP) load(w2, grp, s + D);
+        else if (next >= 0) load(w2, next, s + D - HP);
+        pin();
+      }
     }
   }
 };

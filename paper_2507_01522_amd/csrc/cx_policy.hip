@@ -40,9 +40,9 @@ struct PolicyRt {
   float *obs = nullptr;  // one step of observations (rollouts that do not return them)
   uint8_t *act = nullptr;  // one step of levels (rollouts that do not return them)
   int64_t scratch_envs = 0;
-  // the fused rollout's segment table (stations of 8 lanes, 4 waves per block)
+  // the fused rollout's segment table (stations of 8 or 16 lanes, 4 waves per block)
   SegDev *segs_dev = nullptr;
-  int n_segs = 0, n_blocks = 0;
+  int lanes = 8, n_segs = 0, n_blocks = 0;
 };
 
 namespace {
@@ -61,7 +61,7 @@ __device__ __forceinline__ void policy_block(const PolicyArgs &a, lds_u32x4 *xb,
   typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
   const __amdgpu_buffer_rsrc_t w1 = frag_rsrc(a.w1f, 2 * kPolHP * kPolK1);
   HiddenLayer<W, NT, K1, HP> hid;
-  hid.start(w1, wv);
+  hid.start(w1, a.b1, wv);
   const float *obs = a.obs + e0 * a.in_dim;
   for (int c = tid; c < E * CPR; c += 64 * W) {
     const int e = c / CPR, k = c % CPR, f = 8 * k;
@@ -84,7 +84,7 @@ __device__ __forceinline__ void policy_block(const PolicyArgs &a, lds_u32x4 *xb,
   hid.run(w1, a.b1, xb, XR, hb, wv);
   const __amdgpu_buffer_rsrc_t w2 = frag_rsrc(a.w2f, a.G * kPolR * kPolHP);
   LogitLayer<NT, HP> logit;
-  logit.start(w2, min(wv, a.G - 1));
+  logit.start(w2, a.b2f, min(wv, a.G - 1));
   // the lane's ports are 4 wv + lg + 4 W i, a multiple of 16 apart: one Philox
   // call per observation serves them all
   U4 dw[NT];
@@ -108,7 +108,7 @@ __device__ __forceinline__ void policy_block(const PolicyArgs &a, lds_u32x4 *xb,
   for (int g0 = 0; g0 < a.G; g0 += W) {
     const int grp = min(g0 + wv, a.G - 1), port = 4 * (g0 + wv) + lg;
     f32x4 c[kPolR][NT];
-    logit.run(w2, a.b2f, hb, grp, min(g0 + W + wv, a.G - 1), c);
+    logit.run(w2, a.b2f, hb, grp, g0 + W < a.G ? min(g0 + W + wv, a.G - 1) : -1, c);
     if (a.logits) {
       const int n_z = min(4 * W, a.N - 4 * g0) * a.L1;   // floats per observation of these groups
 #pragma unroll
@@ -400,11 +400,20 @@ cx_status ensure_fused(cx_ctx *ctx) {
   if (p.segs_dev) return CX_OK;
   const ClassRt &c = ctx->classes[0];
   std::vector<SegDev> segs;
-  class_segments(ctx, c, 8, c.comp.S / 8, &segs);
+  // 16-slot stations take 16 lanes each (16 stations a block) while that gives
+  // every block a CU of its own: half the MLP and a shorter step per block (96
+  // steps of 4,096 such envs, 256 hidden units, every record: 253 us, 383 with 8
+  // lanes)
   int blocks = 0;
-  for (SegDev &sg : segs) {
-    sg.block_begin = blocks;
-    blocks += (sg.n_groups + kPolRolloutWaves - 1) / kPolRolloutWaves;
+  for (p.lanes = c.comp.S == 16 ? 16 : 8;; p.lanes = 8) {
+    segs.clear();
+    class_segments(ctx, c, p.lanes, c.comp.S / p.lanes, &segs);
+    blocks = 0;
+    for (SegDev &sg : segs) {
+      sg.block_begin = blocks;
+      blocks += (sg.n_groups + kPolRolloutWaves - 1) / kPolRolloutWaves;
+    }
+    if (p.lanes == 8 || blocks <= kPolHeldBlocks) break;
   }
   void *d = nullptr;
   if (hipMalloc(&d, sizeof(SegDev) * std::max<size_t>(1, segs.size())) != hipSuccess)
@@ -422,12 +431,23 @@ cx_status ensure_fused(cx_ctx *ctx) {
 
 // One launch for the whole rollout: the observation the rollout starts from
 // (into the scratch), then the persistent kernel with the MLP between steps.
-cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_traj *out, size_t lds,
-                        int32_t stage_floats, const LaunchArgs::Pol &lay) {
+cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_traj *out) {
   PolicyRt &p = *ctx->policy;
   const ClassRt &c = ctx->classes[0];
   const bool ret_obs = out && out_mode == CX_OUT_FULL && out->obs;
   const bool ret_act = out && out_mode != CX_OUT_REWARD && out->actions;
+  LaunchArgs::Pol lay{};
+  int32_t stage_off = 0, stage_floats = 0;
+  const auto plan = [&](bool over_stage) {
+    return policy_rollout_lds(c.tab.dwell_log2, c.comp.obs_dim, c.comp.N, over_stage, &stage_off, &stage_floats,
+                              &lay.hb_off, &lay.xb_off, &lay.act_off);
+  };
+  bool held = p.n_blocks <= kPolHeldBlocks;
+  size_t lds = plan(!policy_dual(c.comp.S, held));
+  if (lds > kMaxBlockLds) {   // 32 slots and a stay table of more than 1024 entries
+    held = false;
+    lds = plan(true);
+  }
   hipError_t e = launch_observe(ctx, p.obs, ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "policy rollout: observation kernel");
   LaunchArgs a = base_args(ctx);
@@ -441,8 +461,15 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.reward = out ? out->reward : nullptr;
   a.done = out ? out->done : nullptr;
   a.lds_tdwell = 1;
-  a.stage_off = lay.hb_off;
+  a.stage_off = stage_off;
   a.stage_floats = stage_floats;
+  // launches with held weights keep the day's tables in LDS too, where they fit:
+  // their steps then load nothing from device memory and wait for no record
+  const size_t days = (size_t)ctx->steps_ep * 20;
+  if (held && ctx->steps_ep <= kLdsExoSteps && lds + days <= kMaxBlockLds) {
+    a.day_off = (int32_t)lds;
+    lds += days;
+  }
   a.pol = lay;
   a.pol.obs0 = p.obs;
   a.pol.w1f = p.w1p;
@@ -455,8 +482,8 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.pol.R = p.R;
   a.pol.G = p.G;
   a.pol.L1 = p.L1;
-  if ((e = launch_policy_rollout(a, c.host_view.kind == kKindSimple, c.comp.S / 8, p.HP, p.n_blocks, lds,
-                                 ctx->stream)) != hipSuccess)
+  if ((e = launch_policy_rollout(a, c.host_view.kind == kKindSimple, p.lanes, c.comp.S / p.lanes, p.HP, held,
+                                 p.n_blocks, lds, ctx->stream)) != hipSuccess)
     return hip_fail(ctx, e, "policy rollout kernel");
   advance_clock(ctx, T);
   return CX_OK;
@@ -476,12 +503,12 @@ cx_status policy_step(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_tra
     const ClassRt &c = ctx->classes[0];
     LaunchArgs::Pol lay{};
     int32_t stage_off = 0, stage_floats = 0;
-    const size_t lds = policy_rollout_lds(c.tab.dwell_log2, c.comp.obs_dim, c.comp.N, &stage_off,
+    const size_t lds = policy_rollout_lds(c.tab.dwell_log2, c.comp.obs_dim, c.comp.N, true, &stage_off,
                                           &stage_floats, &lay.hb_off, &lay.xb_off, &lay.act_off);
     if (lds <= kMaxBlockLds) {
       if (T == 0) return CX_OK;
       if ((st = ensure_fused(ctx)) != CX_OK) return st;
-      return fused_rollout(ctx, T, out_mode, out, lds, stage_floats, lay);
+      return fused_rollout(ctx, T, out_mode, out);
     }
   }
   return policy_step_with(ctx, T, out_mode, out, ctx->policy->obs, ctx->policy->act);

@@ -79,3 +79,39 @@ def test_policy_kernel_sizes(cxm, ports, hidden):
         assert torch.equal(env.policy_sample(obs[:n], 11), k[:n]), n
     odd = torch.zeros(1000 * ports + 1, dtype=torch.uint8, device="cuda")[1:].view(1000, ports)
     assert torch.equal(env.policy_sample(obs[:1000], 11, odd), k[:1000])   # levels at an odd address
+
+
+def big_stay():
+    # 32 slots with a stay table of 2048 entries: no LDS for the held layout
+    return W.policy_station().replace(dwell_max=2048)
+
+
+def long_day():
+    # more steps a day than the LDS day tables hold
+    return W.scale_station().replace(steps_per_episode=600)
+
+
+@pytest.mark.parametrize("make,n", [(W.scale_station, 1), (W.scale_station, 17), (W.scale_station, 4096),
+                                    (W.scale_station, 4097), (W.scale_station, 8192), (W.scale_station, 8193),
+                                    (W.two_charger_types, 4097), (W.two_charger_types, 8193),
+                                    (W.policy_station, 33), (W.policy_station, 8193),
+                                    (big_stay, 67), (long_day, 67)])
+@pytest.mark.parametrize("hidden", [64, 160])
+def test_launch_sizes_equal_two_kernels(cxm, make, n, hidden):
+    """Around the sizes where a rollout's blocks change (16 lanes a station and
+    held weights while every block has a CU of its own: 256 blocks of 16 or 32
+    stations), with the day's tables in LDS (T >= 32) and without: records and state
+    bit for bit those of the two kernels per step."""
+    spec = make()
+    weights = W.policy_weights(spec.n_ports, hidden=hidden, n_levels=spec.n_levels, std=0.2, seed=41)
+    print(f"fused {spec.name} {n} envs hidden {hidden}", flush=True)
+    a, b = cxm.Env(spec, n_envs=n, seed=43), cxm.Env(spec, n_envs=n, seed=43)
+    for e in (a, b):
+        e.rollout(140, cxm.ACT_RANDOM, cxm.OUT_REWARD)
+        e.set_policy(hidden, weights)
+    for T, out_mode in ((33, cxm.OUT_FULL), (5, cxm.OUT_ACT_REWARD), (1, cxm.OUT_FULL)):
+        x = PY.to_np(a.rollout(T, cxm.ACT_POLICY, out_mode))
+        y = PY.to_np(b.rollout_policy_noalloc(T, out_mode))
+        for k in x:
+            assert np.array_equal(x[k], y[k]), (T, k)
+        assert a.get_state() == b.get_state()
