@@ -173,6 +173,7 @@ struct LaunchArgs {
     int32_t block_begin, n_blocks, seg_begin, n_segs, pack;
   } part[kMaxParts];
   int32_t n_parts;
+  int32_t pace;   // 1: a step's records leave before the next step (kernels without the stage)
   // the fused policy rollout (mode CX_ACT_POLICY): the MLP's weights in
   // fragment order, its sizes, the observation the rollout starts from, and
   // where the block's BF16 observations, hidden units and levels sit in LDS

@@ -205,6 +205,7 @@ struct Dyn {
   uint8_t *done;
   const uint8_t *act_in;
   int64_t obs_stride, act_stride, env_stride;
+  int32_t pace;         // 1: a step's records leave before the next step
 };
 
 // Store / load at a wave-uniform base plus a per-lane 32-bit byte offset
@@ -390,18 +391,19 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 
 // sg: the segment's descriptor; seg_args: take the horizon, clock, modes and
 // record pointers from it (serving) instead of from the launch arguments.
-// tdw: the block's LDS copy of the stay thresholds; exo_tp / exo_pr: its LDS
+// tdw: the block's LDS copy of the stay thresholds; exo_tp: its LDS
 // copies of the first four arrival thresholds and the base price of every step
 // of the day (NULL: read device memory); car_tab: of the car models' 8 thresholds
 // and 8 x {capacity, AC rate, DC rate} (extended classes).
 // HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units; HELD:
 // its weights stay in registers.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL = 0, bool HELD = false>
-__device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, int group, const lds_u32 *tdw,
-                                          const lds_u32x4 *exo_tp, const lds_float *exo_pr,
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD, class Fill>
+__device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *sgp, const Dyn &dy, int group,
+                                          const lds_u32 *tdw,
+                                          const lds_u32x4 *exo_tp,
                                           const lds_u32 *car_tab, lds_float *stage,
                                           int stage_step, int g_blk0, int n_run,
-                                          const LaunchArgs::Pol *pol = nullptr, lds_char *lds = nullptr) {
+                                          const LaunchArgs::Pol *pol, lds_char *lds) {
   constexpr int SPW = 64 / L;
   constexpr int LOGP = P == 1 ? 0 : P == 2 ? 1 : 2;
   constexpr int LOGL = (L == 4) ? 2 : (L == 8) ? 3 : (L == 16) ? 4 : (L == 32) ? 5 : 6;
@@ -472,7 +474,6 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   for (int j = 0; j < P; ++j) {
     const int64_t i = sofs + l * P + j;
     q[j] = active ? gld(sg.q, i) : 0.0;
-    qf[j] = (float)q[j];
     u[j] = active ? gld(sg.u, i) : 0.f;
     cap[j] = active ? gld(sg.cap, i) : 0.f;
     plast[j] = active ? gld(sg.p_last, i) : 0.f;
@@ -480,6 +481,22 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     cs[j] = (users && active) ? (int)gld(sg.utype, i) : 0;
     rb[j] = models ? (active ? gld(sg.rbar, i) : 0.f) : pmax[j];
     dc[j] = models ? gld(C.slot_dc, l * P + j) : 0;
+  }
+  double ret = active ? gld(sg.ret, env) : 0.0;
+  // station battery (EXT): SoC in FP64 and last power, alike in every lane of the station
+  double bsoc = 0.0;
+  float bpw = 0.f;
+  if constexpr (EXT) {
+    if (batt && active) {
+      bsoc = gld(sg.bsoc, env);
+      bpw = gld(sg.bp, env);
+    }
+  }
+  // the block's tables while the state is on its way
+  fill_tables();
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    qf[j] = (float)q[j];
     icap[j] = cap[j] > 0.f ? frcp(cap[j]) : 0.f;
   }
   // The state is in registers before the first step: a load still pending when
@@ -496,16 +513,6 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   // a slot is occupied while its car's stay runs, or while a charge-sensitive
   // user waits to be charged
 #define CX_OCCUPIED(j) (EXT ? (dw[j] > 0 || cs[j] != 0) : dw[j] > 0)
-  double ret = active ? gld(sg.ret, env) : 0.0;
-  // station battery (EXT): SoC in FP64 and last power, alike in every lane of the station
-  double bsoc = 0.0;
-  float bpw = 0.f;
-  if constexpr (EXT) {
-    if (batt && active) {
-      bsoc = gld(sg.bsoc, env);
-      bpw = gld(sg.bp, env);
-    }
-  }
   uint32_t bkp = 0u, bkq = 0u;  // EXT: the battery's action bytes of the current group of 8 steps
   // the levels of a SIMPLE class by block size (as a copy in scalar registers)
   constexpr int kBlk = LOGL + LOGP;
@@ -567,12 +574,17 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   // afresh every step (a bit test and a scalar branch each).  Rewards and done
   // flags share their step: each is written under its own flag (with one of
   // them NULL, its advanced pointer is no address).
-  enum : uint32_t { kWObs = 1, kWAct = 2, kWRew = 4, kWDone = 8, kActQuads = 16, kSat = 32, kRandom = 64, kMax = 128 };
+  enum : uint32_t { kWObs = 1, kWAct = 2, kWRew = 4, kWDone = 8, kActQuads = 16, kSat = 32, kRandom = 64, kMax = 128,
+                    kDayTabs = 256, kBatt = 512, kUsers = 1024, kDays = 2048, kModels = 4096, kEtaU = 8192,
+                    kPace = 16384 };
   const uint32_t flags0 =
       (uint32_t)uni((w_obs ? kWObs : 0) | (w_act ? kWAct : 0) | (rw_t ? kWRew : 0) | (dn_t ? kWDone : 0) |
                     // every step's action row is 4-byte aligned
                     (((reinterpret_cast<uintptr_t>(ab_t) | (uint64_t)act_step) & 3u) == 0 ? kActQuads : 0) |
                     (alpha_sat != 0.0f ? kSat : 0) | (dy.mode == CX_ACT_RANDOM ? kRandom : 0) |
+                    (exo_tp ? kDayTabs : 0) | (w_obs && dy.pace ? kPace : 0) |
+                    (batt ? kBatt : 0) | (users ? kUsers : 0) | (days ? kDays : 0) | (models ? kModels : 0) |
+                    (!SIMPLE && !EXT && C.uniform_eta ? kEtaU : 0) |
                     (dy.mode == CX_ACT_MAX ? kMax : 0));
   // the block's LDS observation stage (staging packings, whenever observations
   // are written): the block's first env, the floats the block writes per step
@@ -607,7 +619,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     if constexpr (HELD) {
 #pragma unroll
       for (int i = 0; i < NG; ++i)
-        held2[i].start(frag_rsrc(pol->w2f, pol->G * kPolR * kPolHP), pol->b2f, min(wv + kPolRolloutWaves * i, pol->G - 1));
+        held2[i].start(frag_rsrc(pol->w2f, pol->G * kPolR * kPolHP), pol->b2f,
+                       min(wv + kPolRolloutWaves * i, pol->G - 1));
     }
     __syncthreads();
     policy_phase(*pol, stage, lds, obs_dim, N, blk_envs, wv, env_id0, g, k0, k1, true, held1, held2);
@@ -625,9 +638,26 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
   [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
   [[maybe_unused]] int kb_in = 0;
   const int T = uni(dy.T);
+  [[maybe_unused]] const uint32_t lvl_lb0 = C.lvl_lb_uniform, dense0 = C.dense_nodes;
+  [[maybe_unused]] const int D0 = D;
   for (int t = 0; t < T; ++t, ++g) {
     uint32_t flags = flags0;
     asm volatile("" : "+s"(flags));
+    // what the step tests, by bits and by slots: a test made ahead of the loop
+    // holds a mask of two scalar registers, and the masks spilled to vector lanes
+    [[maybe_unused]] uint32_t levels = blk_mask, lvl_lb = lvl_lb0, dense = dense0;
+    [[maybe_unused]] int D = D0;
+    if constexpr (SIMPLE) {
+      // (at 8 lanes and fewer the masks fit: 0.266 ms a day of 400 stations so, 0.285
+      // bit by bit; at 16 0.288 against 0.275, at 64 with two slots 0.50 / 0.46)
+      if constexpr (L > 8) asm volatile("" : "+s"(levels));
+    } else {
+      asm volatile("" : "+s"(lvl_lb), "+s"(dense), "+s"(D));
+#pragma unroll
+      for (int j = 0; j < P; ++j) asm volatile("" : "+v"(lbp[j]));
+    }
+    [[maybe_unused]] const bool batt = EXT && (flags & kBatt), users = EXT && (flags & kUsers),
+                                days = EXT && (flags & kDays), models = EXT && (flags & kModels);
     // ---- exogenous draws for the next L steps, lane l -> step t + l: the
     // arrival count, the price noise and the first arriving car's profile
     if ((t & (L - 1)) == 0) {
@@ -636,13 +666,13 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       while (td >= steps_ep) td -= steps_ep;
       const uint32_t gl = g + (uint32_t)l;
       const U4 w = philox(env_id, gl, 0u, kDomEnv, k0, k1);
-      bM = active ? arrivals(exo_tp ? exo_tp + td : nullptr, C.tpois + td * kPoisStride, w.x) : 0;
+      bM = active ? arrivals(flags & kDayTabs ? exo_tp + td : nullptr, C.tpois + td * kPoisStride, w.x) : 0;
       const float u1 = (float)((w.y >> 8) + 1u) * 0x1p-24f;
       const float u2 = u24(w.z);
       const float z = __builtin_amdgcn_sqrtf(-2.0f * __logf(u1)) * __builtin_amdgcn_cosf(u2);
       float base;
-      if (exo_pr) {
-        base = exo_pr[td];
+      if (flags & kDayTabs) {
+        base = reinterpret_cast<const lds_float *>(exo_tp + steps_ep)[td];
       } else {
         // wait for the load here, where it is issued: a load still pending
         // where the two paths join would make every step wait for all the
@@ -827,18 +857,18 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
         f = over ? f * (c * frcp(load)) : f;
         load = over ? c : load;
       };
-      if (P > 1 && (blk_mask & ((1u << LOGP) - 1u))) {
+      if (P > 1 && (levels & ((1u << LOGP) - 1u))) {
         float v[P];
 #pragma unroll
         for (int j = 0; j < P; ++j) {
           v[j] = pw[j];
-          if (blk_mask & 1u) limit(v[j], F[j], blk_cap[0]);
+          if (levels & 1u) limit(v[j], F[j], blk_cap[0]);
         }
         if constexpr (P == 2) {
           r = v[0] + v[1];
         } else if constexpr (P == 4) {
           float lo = v[0] + v[1], hi = v[2] + v[3];
-          if (blk_mask & 2u) {
+          if (levels & 2u) {
             float fl = 1.0f, fh = 1.0f;
             limit(lo, fl, blk_cap[1]);
             limit(hi, fh, blk_cap[1]);
@@ -858,7 +888,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
       float f = 1.0f;
 #pragma unroll
       for (int k = 0; k < LOGL; ++k) {
-        if ((blk_mask >> (k + LOGP)) & 1u) {  // a level of blocks of P 2^k slots (wave-uniform)
+        if ((levels >> (k + LOGP)) & 1u) {  // a level of blocks of P 2^k slots (wave-uniform)
           // a real (scalar) branch: most sizes have no level, and computing the
           // check for every one and selecting would cost more than it saves
           asm volatile("");
@@ -879,8 +909,8 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     for (int d = 0; d < kMaxLevels - 1; ++d) {
       if (d < D - 1) {
         float s[P];
-        const int lbu = (int)((C.lvl_lb_uniform >> (8 * d)) & 0xFF);
-        const int nd = (int)((C.dense_nodes >> (8 * d)) & 0xFF);
+        const int lbu = (int)((lvl_lb >> (8 * d)) & 0xFF);
+        const int nd = (int)((dense >> (8 * d)) & 0xFF);
         if (nd != 0) {
           // dense layout: at most 4 nodes on this level, each summed over the
           // whole station from the slots it covers
@@ -969,7 +999,7 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
 #pragma unroll
       for (int j = 0; j < P; ++j) pw[j] *= f;
       e_net = dt * (over ? c_root : tot);
-      if (C.uniform_eta) {
+      if (flags & kEtaU) {
         e_grid = e_net * inv_eta_u;
       } else {
         float tg[P];
@@ -1351,6 +1381,10 @@ __device__ __forceinline__ void run_group(CX_KONST SegDev *sgp, const Dyn &dy, i
     // many steps.  Waves that left early (past the last env) do not count.
     // (Rewards and done flags alone are too few bytes for that.)
     if (POL || (flags & (kWObs | kWAct))) __syncthreads();
+    // (the host's rule stands at paced())
+    if constexpr (!POL && !EXT && !STAGE) {
+      if (flags & kPace) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0, the other counters as they are
+    }
     // the stage of this step is complete: out to HBM (the next step fills the
     // other buffer; the barrier of that step keeps this one until it is read)
     if (STAGE && (flags & kWObs) && (!POL || wv < n_run))
@@ -1428,50 +1462,56 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   Dyn dy;
   if (a.per_segment) {
     dy = Dyn{sg.T, sg.t_day0, sg.g0, sg.mode, sg.out_mode, sg.obs, sg.act, sg.reward, sg.done, sg.act_in,
-             sg.obs_stride, sg.act_stride, sg.env_stride};
+             sg.obs_stride, sg.act_stride, sg.env_stride, 0};
   } else {
     dy = Dyn{a.T, a.t_day0, a.g0, a.mode, a.out_mode, a.obs, a.act, a.reward, a.done, a.act_in,
-             a.obs_stride, a.act_stride, a.env_stride};
+             a.obs_stride, a.act_stride, a.env_stride, a.pace};
   }
-  // stay-length thresholds in LDS (every wave of the block helps load them
-  // before any wave may leave)
+  // stay-length thresholds in LDS; the day's per-step tables too, for launches
+  // long enough to repay copying them (short ones read them from device memory)
   const lds_u32x4 *exo_tp = nullptr;
-  const lds_float *exo_pr = nullptr;
-  const int n_stay = 1 << C.dwell_log2;
-  for (int i = threadIdx.x; i < n_stay; i += blockDim.x) lds_tdwell[i] = gld(C.tdwell, i);
-  // the day's per-step tables after the (16-byte aligned) stay table, for
-  // launches long enough to repay copying them (short ones read them from
-  // device memory)
   const int steps = C.steps_ep;
   if ((HELD ? a.day_off > 0 : !POL) && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
-    lds_char *base = (lds_char *)lds_tdwell + a.day_off;
-    lds_u32x4 *tp = (lds_u32x4 *)base;
-    lds_float *pr = (lds_float *)(base + 16 * steps);
-    for (int i = threadIdx.x; i < steps; i += blockDim.x) {
-      tp[i] = gld(reinterpret_cast<const u32x4 *>(C.tpois + (int64_t)i * kPoisStride), 0);
-      pr[i] = gld(C.glob, 4 * i + 2);
+    exo_tp = (const lds_u32x4 *)((lds_char *)lds_tdwell + a.day_off);
+  }
+  lds_u32 *const car_tab = EXT ? (lds_u32 *)((lds_char *)lds_tdwell + a.car_off) : nullptr;
+  // every wave of the block helps load them, those past the last env too; the
+  // others ask for their state first, so that a short launch waits once (one step
+  // of 65,536 uneven stations 50.3 -> 46.5 us) and nothing is still on its way
+  // when the steps begin (a step had waited for its records at the first use of
+  // the return's load: a day of 64 16-port stations 226 -> 210 us)
+  const auto fill_tables = [&] {
+    const int n_stay = 1 << C.dwell_log2;
+    for (int i = threadIdx.x; i < n_stay; i += blockDim.x) lds_tdwell[i] = gld(C.tdwell, i);
+    if (exo_tp) {
+      lds_u32x4 *tp = const_cast<lds_u32x4 *>(exo_tp);
+      lds_float *pr = reinterpret_cast<lds_float *>(tp + steps);
+      for (int i = threadIdx.x; i < steps; i += blockDim.x) {
+        tp[i] = gld(reinterpret_cast<const u32x4 *>(C.tpois + (int64_t)i * kPoisStride), 0);
+        pr[i] = gld(C.glob, 4 * i + 2);
+      }
     }
-    exo_tp = tp;
-    exo_pr = pr;
-  }
-  lds_u32 *car_tab = nullptr;
-  if constexpr (EXT) {
-    car_tab = (lds_u32 *)((lds_char *)lds_tdwell + a.car_off);
-    const int i = threadIdx.x;
-    if (i < 8) car_tab[i] = gld(C.model_thresh, i);
-    else if (i < 32) car_tab[i] = __float_as_uint(gld(C.model_data, i - 8));
-  }
-  __syncthreads();
+    if constexpr (EXT) {
+      const int i = threadIdx.x;
+      if (i < 8) car_tab[i] = gld(C.model_thresh, i);
+      else if (i < 32) car_tab[i] = __float_as_uint(gld(C.model_data, i - 8));
+    }
+    __syncthreads();
+  };
   const int W = blockDim.x >> 6;
   const int g_blk0 = (b - sg.block_begin) * W;  // the block's first group
   const int group = uni(g_blk0 + (int)(threadIdx.x >> 6));
   // (the fused policy keeps every wave: all take part in the MLP)
   const int n_groups = sg.n_groups;
-  if (!POL && group >= n_groups) return;
+  if (!POL && group >= n_groups) {
+    fill_tables();
+    return;
+  }
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
   lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD>(sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, exo_pr, car_tab, stage,
-                                           W == 1 ? 0 : a.stage_floats, g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
+  run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD>(fill_tables, sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp,
+                                                  car_tab, stage, W == 1 ? 0 : a.stage_floats, g_blk0, n_run, &a.pol,
+                                                  (lds_char *)lds_tdwell);
 }
 
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
@@ -1503,14 +1543,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CX_SIMPLE_W
 // one step's chain (10 DC + 6 AC ports, 256 hidden units, every record, 4,096 x
 // 288 steps: 1,770 -> 804 us, 2.8 us a step).
 template <int L, int P, int HP, bool HELD>
-__global__ __launch_bounds__(64 * kPolRolloutWaves) __attribute__((amdgpu_waves_per_eu(HELD ? 1 : 3))) void k_rollout_policy(LaunchArgs a) {
+__global__ __launch_bounds__(64 * kPolRolloutWaves)
+__attribute__((amdgpu_waves_per_eu(HELD ? 1 : 3))) void k_rollout_policy(LaunchArgs a) {
   rollout_body<L, P, true, false, true, HP, HELD>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 // ... of classes that are not SIMPLE (padding slots, port maxima or limits that
 // differ, the dense layout): a policy rollout of the 10 DC + 6 AC station used to
 // take two launches a step.
 template <int L, int P, int HP, bool HELD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
+__global__ __launch_bounds__(64 * kPolRolloutWaves)
+__attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_policy_general(LaunchArgs a) {
   rollout_body<L, P, false, false, true, HP, HELD>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
@@ -1614,7 +1656,17 @@ int launch_kind(const LaunchArgs &a, const LaunchGroup &g, int64_t waves) {
 
 // Arguments of one group's launch as kernel kind `kind`: its slice of the
 // segment table and its LDS.
-LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, size_t *lds) {
+// Records stored by the lanes themselves share their lines' halves with the next
+// lanes', envs' and blocks', which meet in L2 only while the waves keep together:
+// where the stores set the pace, a wave waits for a step's records before the next
+// step.  Every record, free against paced: the mixture in one launch, 2,000 stations
+// 0.507 / 0.483 ms, 10,000 0.630 / 0.605, 20,000 1.178 / 1.162; 10 DC + 6 AC
+// ports, 144 steps, 8,192 waves 0.940 / 0.917, 16,384 1.160 / 1.126, but 2,000
+// waves 0.161 / 0.176; extended classes, bound by their steps, 1.100 / 1.125
+// (V2G, 8,192 waves).
+bool paced(int kind, int64_t waves) { return kind == kKindGeneral && waves >= kStageMinWaves; }
+
+LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, int64_t waves, size_t *lds) {
   LaunchArgs b = a;
   b.segs = a.segs + g.seg_begin;
   b.n_segs = g.n_segs;
@@ -1628,6 +1680,7 @@ LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, size_
   b.stage_off = p.stage_off;
   b.stage_floats = p.stage_floats;
   b.car_off = p.car_off;
+  b.pace = paced(kind, waves) ? 1 : 0;
   *lds = p.bytes;
   return b;
 }
@@ -1672,6 +1725,7 @@ bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, 
   b.lds_tdwell = 1;
   const LdsPlan p = lds_plan(groups[0].wpb, groups[0].pack, 0, dwell, a.T >= kLdsExoMinT ? days : 0, false, false);
   b.day_off = p.day_off;
+  b.pace = 1;
   void *params[1] = {&b};
   *e = hipLaunchKernel(reinterpret_cast<const void *>(&k_rollout_parts), dim3(blocks), dim3(64 * groups[0].wpb), params,
                        p.bytes, st);
@@ -1689,7 +1743,7 @@ hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_g
     if (g.n_blocks <= 0) continue;
     size_t lds = 0;
     const int kind = launch_kind(a, g, waves);
-    LaunchArgs b = group_args(a, g, kind, &lds);
+    LaunchArgs b = group_args(a, g, kind, waves, &lds);
     void *params[1] = {&b};
     hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kKernels[kNumKinds * g.pack + kind]), dim3(g.n_blocks),
                                    dim3(64 * g.wpb), params, lds, st);
@@ -1742,7 +1796,7 @@ hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup
     if (g.n_blocks <= 0) continue;
     size_t lds = 0;
     const int kind = launch_kind(a, g, waves);
-    args[n] = group_args(a, g, kind, &lds);
+    args[n] = group_args(a, g, kind, waves, &lds);
     params[n][0] = &args[n];
     p[n] = hipKernelNodeParams{};
     p[n].func = reinterpret_cast<void *>(kKernels[kNumKinds * g.pack + kind]);
