@@ -292,7 +292,7 @@ def run_policy(args):
                       "n_envs": E, "T": T_DAY, "hidden": H, "kernel": "fused (8 lanes x 4 slots, 4 waves per block)"},
                      dtype="bf16")
     line["roofline"] = {"bound": "mfma", "achieved": achieved, "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                        "frac": achieved / BF16_PEAK_TFLOPS, "traffic": None, "kernel": "k_rollout_policy<8, 4>",
+                        "frac": achieved / BF16_PEAK_TFLOPS, "traffic": None, "kernel": "k_rollout_policy<8, 4, 8, false>",
                         "kernel_ms": ev_ms, "algorithmic_flops": flops,
                         "note": "HIP-event time of the rollout: the fused kernel plus the observation kernel of "
                                 "the start state (well under 1 %)"}

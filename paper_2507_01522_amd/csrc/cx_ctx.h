@@ -52,8 +52,8 @@ struct cx_ctx {
   std::vector<cx::SegDev> segs_host;
   std::vector<cx::LaunchGroup> groups;
   int wpb = 4;
-  // SIMPLE classes of up to 32 lanes per station write their observations
-  // through an LDS stage (cx_set_obs_stage / cx_autotune)
+  // SIMPLE classes write their observations through an LDS stage
+  // (cx_set_obs_stage / cx_autotune; large launches do so in any case)
   bool stage_obs = false;
   bool failed = false;
   int64_t device_bytes = 0;

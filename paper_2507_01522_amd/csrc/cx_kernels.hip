@@ -1522,9 +1522,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P ==
   rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
-// SIMPLE classes of 1 or 2 slots per lane: the kernel held to CX_SIMPLE_WAVES
-// waves per SIMD (96 VGPRs at 5, a few of them spilled): their step is issue-
-// bound, and the extra waves hide its latencies.
+// SIMPLE classes of 1 or 2 slots per lane: 64-75 VGPRs at one slot per lane (six to
+// eight waves per SIMD), 78-91 at two (five or six), with their constants in
+// scalar registers and nothing spilled; the bound keeps every one at five waves at
+// least.  Every record, 65,536 uneven stations x 288 steps: 3.74
+// ms with the constants in vector registers (96, some spilled), 3.48 now; rewards
+// only 2.25 and 1.60.
 #ifndef CX_SIMPLE_WAVES
 #define CX_SIMPLE_WAVES 5
 #endif
