@@ -397,7 +397,15 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 // and 8 x {capacity, AC rate, DC rate} (extended classes).
 // HPOL: 0, or the fused policy rollout with HPOL K-steps of 32 hidden units; HELD:
 // its weights stay in registers.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD, class Fill>
+// MODE: what a kernel knows of the call: nothing, that it records no observations,
+// or that it is one step (the loop, the draws ahead and the barrier fold away).
+// One kernel for all held the registers of the longest: one step of a SIMPLE class
+// needs 44-54 VGPRs (eight waves per SIMD), a rollout without observations 60-80.
+// One step of 65,536 uneven stations 46.3 -> 38.0 us, of V2G ones 36.8 -> 32.0, of
+// 64 7.0 -> 6.8.  144 steps, rewards only: uneven 933 -> 833 us, V2G 820 -> 663,
+// table-driven 768 -> 611; 288 steps of 20,011 uneven 550 -> 500.
+enum { kModeAny = 0, kModeNoObs = 1, kModeStep = 2 };
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD, int MODE, class Fill>
 __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *sgp, const Dyn &dy, int group,
                                           const lds_u32 *tdw,
                                           const lds_u32x4 *exo_tp,
@@ -560,7 +568,7 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
   const uint32_t act_bo = (uint32_t)env * (uint32_t)n_act;
   const uint32_t env_bo = (uint32_t)env;
   // wave-uniform record pointers of the current step, advanced every step
-  const bool w_obs = dy.out_mode == CX_OUT_FULL && dy.obs != nullptr;
+  const bool w_obs = MODE != kModeNoObs && dy.out_mode == CX_OUT_FULL && dy.obs != nullptr;
   const bool w_act = (dy.out_mode == CX_OUT_FULL || dy.out_mode == CX_OUT_ACT_REWARD) && dy.act != nullptr;
   float *ob_t = w_obs ? dy.obs + sg.obs_off : nullptr;
   uint8_t *ab_t = w_act ? dy.act + sg.act_off : nullptr;
@@ -637,7 +645,7 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
   [[maybe_unused]] auto car_data = [&](int i) { return __uint_as_float(car_tab[8 + i]); };
   [[maybe_unused]] int k_in[P] = {};   // EXTERNAL: the next step's action bytes
   [[maybe_unused]] int kb_in = 0;
-  const int T = uni(dy.T);
+  const int T = MODE == kModeStep ? 1 : uni(dy.T);
   [[maybe_unused]] const uint32_t lvl_lb0 = C.lvl_lb_uniform, dense0 = C.dense_nodes;
   [[maybe_unused]] const int D0 = D;
   for (int t = 0; t < T; ++t, ++g) {
@@ -1205,7 +1213,7 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
                         ? (int)((reinterpret_cast<uintptr_t>(ob_now + (int64_t)env_blk0 * obs_dim) >> 2) & 3u)
                         : 0;
     if (active) {
-      if (POL || (flags & kWObs)) {
+      if (MODE != kModeNoObs && (POL || (flags & kWObs))) {
         // put(feature offset, port's offset, value) writes one value; with every
         // lane's ports adjacent (slot s = port s), put_lane writes a lane's P values
         // of a feature at once
@@ -1380,9 +1388,9 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
     // noticeably faster (better row locality) than the same bytes spread over
     // many steps.  Waves that left early (past the last env) do not count.
     // (Rewards and done flags alone are too few bytes for that.)
-    if (POL || (flags & (kWObs | kWAct))) __syncthreads();
+    if (MODE != kModeStep && (POL || (flags & (kWObs | kWAct)))) __syncthreads();
     // (the host's rule stands at paced())
-    if constexpr (!POL && !EXT && !STAGE) {
+    if constexpr (!POL && !EXT && !STAGE && MODE == kModeAny) {
       if (flags & kPace) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0, the other counters as they are
     }
     // the stage of this step is complete: out to HBM (the next step fills the
@@ -1443,7 +1451,7 @@ __device__ __forceinline__ int xcd_block(int i, int n) {
 // One kernel per packing (lanes per station L, slots per lane P) and class
 // kind (general, SIMPLE, bidirectional), so that each keeps its own register
 // budget; the entry points below add the launch bounds of each kind.
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD = false>
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD = false, int MODE = kModeAny>
 __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *segs, int n_segs, int b) {
   constexpr bool POL = HPOL > 0;
   extern __shared__ uint32_t lds_tdwell[];
@@ -1471,7 +1479,7 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   // long enough to repay copying them (short ones read them from device memory)
   const lds_u32x4 *exo_tp = nullptr;
   const int steps = C.steps_ep;
-  if ((HELD ? a.day_off > 0 : !POL) && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
+  if (MODE != kModeStep && (HELD ? a.day_off > 0 : !POL) && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
     exo_tp = (const lds_u32x4 *)((lds_char *)lds_tdwell + a.day_off);
   }
   lds_u32 *const car_tab = EXT ? (lds_u32 *)((lds_char *)lds_tdwell + a.car_off) : nullptr;
@@ -1509,17 +1517,22 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   }
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
   lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
-  run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD>(fill_tables, sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp,
-                                                  car_tab, stage, W == 1 ? 0 : a.stage_floats, g_blk0, n_run, &a.pol,
-                                                  (lds_char *)lds_tdwell);
+  run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD, MODE>(
+      fill_tables, sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, car_tab, stage, W == 1 ? 0 : a.stage_floats,
+      g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
 }
 
-template <int L, int P, bool SIMPLE, bool EXT, bool STAGE>
-// (Extended classes of one slot per lane are held to five waves per SIMD, 96
-// registers of the 102 they would take: at 16 lanes V2G 2.71 -> 2.56 ms.)
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P == 1 ? 5 : 1))) void k_rollout(
-    LaunchArgs a) {
-  rollout_body<L, P, SIMPLE, EXT, STAGE, 0>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
+// Waves per SIMD extended classes are held to.  One slot per lane: five, 96
+// registers of the 102 they would take (at 16 lanes V2G 2.71 -> 2.56 ms).  Two, without
+// observation records: four, 128 registers of 135 (V2G, 144 steps, 768 -> 663
+// us; with the records four cost more than they give: 288 steps 2.52 -> 2.80 ms).
+constexpr int ext_waves(int P, int mode) {
+  return mode == kModeStep ? 1 : P == 1 ? 5 : P == 2 && mode == kModeNoObs ? 4 : 1;
+}
+template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int MODE>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(EXT ? ext_waves(P, MODE) : 1))) void k_rollout(LaunchArgs a) {
+  rollout_body<L, P, SIMPLE, EXT, STAGE, 0, false, MODE>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // SIMPLE classes of 1 or 2 slots per lane: 64-75 VGPRs at one slot per lane (six to
@@ -1531,10 +1544,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EXT && P ==
 #ifndef CX_SIMPLE_WAVES
 #define CX_SIMPLE_WAVES 5
 #endif
-template <int L, int P, bool STAGE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CX_SIMPLE_WAVES))) void k_rollout_simple(
-    LaunchArgs a) {
-  rollout_body<L, P, true, false, STAGE, 0>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
+template <int L, int P, bool STAGE, int MODE>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(MODE == kModeNoObs ? 6 : CX_SIMPLE_WAVES))) void k_rollout_simple(LaunchArgs a) {
+  rollout_body<L, P, true, false, STAGE, 0, false, MODE>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // The fused policy rollout (4 waves per block): three blocks per CU, so that
@@ -1563,7 +1576,8 @@ __attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_p
 // a multiple of 8 so that they are dealt to the XCDs as in a launch of their
 // own).  For launches too short to fill the chip one group at a time: one step
 // of 65,536 uneven stations took five kernels one after the other (74 us, now 50).
-__global__ __launch_bounds__(512) void k_rollout_parts(LaunchArgs a) {
+template <int MODE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE == kModeNoObs ? 6 : 1))) void k_rollout_parts(LaunchArgs a) {
   int i = 0;
   while (i + 1 < a.n_parts && (int)blockIdx.x >= a.part[i + 1].block_begin) ++i;
   i = uni(i);
@@ -1576,7 +1590,7 @@ __global__ __launch_bounds__(512) void k_rollout_parts(LaunchArgs a) {
   switch (p.pack) {
 #define CX_PART(L, P)                                                                              \
   case part_id(L, P):                                                                              \
-    rollout_body<L, P, true, false, false, 0>(a, segs, n, b);                                      \
+    rollout_body<L, P, true, false, false, 0, false, MODE>(a, segs, n, b);                         \
     break;
     CX_PART(4, 1) CX_PART(8, 1) CX_PART(16, 1) CX_PART(32, 1) CX_PART(64, 1)
     CX_PART(4, 2) CX_PART(8, 2) CX_PART(16, 2) CX_PART(32, 2) CX_PART(64, 2)
@@ -1615,23 +1629,35 @@ __global__ void k_fill_f64(double *p, int64_t n, double v) {
 using KernelFn = void (*)(LaunchArgs);
 
 // The kernels of one packing: general, SIMPLE, extended, SIMPLE with staged
-// observations.
-#define CX_KINDS(L, P)                                                                              \
-  &k_rollout<L, P, false, false, false>, &k_rollout<L, P, true, false, false>,                        \
-      &k_rollout<L, P, false, true, false>, &k_rollout<L, P, true, false, true>
-#define CX_KINDS_SIMPLE(L, P)                                                                       \
-  &k_rollout<L, P, false, false, false>, &k_rollout_simple<L, P, false>,                              \
-      &k_rollout<L, P, false, true, false>, &k_rollout_simple<L, P, true>
+// observations (which needs them; one step has no kernel of its own there).
+#define CX_KINDS(L, P, M)                                                                           \
+  &k_rollout<L, P, false, false, false, M>, &k_rollout<L, P, true, false, false, M>,                  \
+      &k_rollout<L, P, false, true, false, M>,                                                        \
+      &k_rollout<L, P, true, false, M != kModeNoObs, M == kModeNoObs ? kModeNoObs : kModeAny>
+#define CX_KINDS_SIMPLE(L, P, M)                                                                    \
+  &k_rollout<L, P, false, false, false, M>, &k_rollout_simple<L, P, false, M>,                        \
+      &k_rollout<L, P, false, true, false, M>,                                                        \
+      &k_rollout_simple<L, P, M != kModeNoObs, M == kModeNoObs ? kModeNoObs : kModeAny>
+#define CX_ALL(M)                                                                                   \
+  {CX_KINDS_SIMPLE(4, 1, M), CX_KINDS_SIMPLE(8, 1, M), CX_KINDS_SIMPLE(16, 1, M),                     \
+   CX_KINDS_SIMPLE(32, 1, M), CX_KINDS_SIMPLE(64, 1, M), CX_KINDS_SIMPLE(4, 2, M),                    \
+   CX_KINDS_SIMPLE(8, 2, M), CX_KINDS_SIMPLE(16, 2, M), CX_KINDS_SIMPLE(32, 2, M),                    \
+   CX_KINDS_SIMPLE(64, 2, M), CX_KINDS(4, 4, M), CX_KINDS(8, 4, M), CX_KINDS(16, 4, M),               \
+   CX_KINDS(32, 4, M), CX_KINDS(64, 4, M)}
 
-// Kernel of each launch kind: packing id (P index * 5 + L index, as pack_id())
-// times kNumKinds, plus the kernel kind (kKind*).
-const KernelFn kKernels[kNumKinds * kNumPackings] = {
-    CX_KINDS_SIMPLE(4, 1), CX_KINDS_SIMPLE(8, 1), CX_KINDS_SIMPLE(16, 1), CX_KINDS_SIMPLE(32, 1),
-    CX_KINDS_SIMPLE(64, 1), CX_KINDS_SIMPLE(4, 2), CX_KINDS_SIMPLE(8, 2), CX_KINDS_SIMPLE(16, 2),
-    CX_KINDS_SIMPLE(32, 2), CX_KINDS_SIMPLE(64, 2),
-    CX_KINDS(4, 4), CX_KINDS(8, 4), CX_KINDS(16, 4), CX_KINDS(32, 4), CX_KINDS(64, 4)};
+// Kernel of each launch kind by mode: packing id (P index * 5 + L index, as
+// pack_id()) times kNumKinds, plus the kernel kind (kKind*).
+const KernelFn kKernels[3][kNumKinds * kNumPackings] = {CX_ALL(kModeAny), CX_ALL(kModeNoObs), CX_ALL(kModeStep)};
+#undef CX_ALL
 #undef CX_KINDS
 #undef CX_KINDS_SIMPLE
+int launch_mode(const LaunchArgs &a) {
+  if (a.per_segment) return kModeAny;
+  return a.T == 1 ? kModeStep : a.out_mode == CX_OUT_FULL && a.obs ? kModeAny : kModeNoObs;
+}
+const KernelFn &kernel_of(const LaunchArgs &a, int pack, int kind) {
+  return kKernels[launch_mode(a)][kNumKinds * pack + kind];
+}
 
 // Waves of all groups of a launch.
 int64_t total_waves(const LaunchGroup *groups, int n_groups) {
@@ -1730,7 +1756,10 @@ bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, 
   b.day_off = p.day_off;
   b.pace = 1;
   void *params[1] = {&b};
-  *e = hipLaunchKernel(reinterpret_cast<const void *>(&k_rollout_parts), dim3(blocks), dim3(64 * groups[0].wpb), params,
+  static const KernelFn kParts[3] = {&k_rollout_parts<kModeAny>, &k_rollout_parts<kModeNoObs>,
+                                     &k_rollout_parts<kModeStep>};
+  const KernelFn f = kParts[launch_mode(a)];
+  *e = hipLaunchKernel(reinterpret_cast<const void *>(f), dim3(blocks), dim3(64 * groups[0].wpb), params,
                        p.bytes, st);
   return true;
 }
@@ -1748,7 +1777,7 @@ hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_g
     const int kind = launch_kind(a, g, waves);
     LaunchArgs b = group_args(a, g, kind, waves, &lds);
     void *params[1] = {&b};
-    hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kKernels[kNumKinds * g.pack + kind]), dim3(g.n_blocks),
+    hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel_of(a, g.pack, kind)), dim3(g.n_blocks),
                                    dim3(64 * g.wpb), params, lds, st);
     if (e != hipSuccess) return e;
   }
@@ -1802,13 +1831,13 @@ hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup
     args[n] = group_args(a, g, kind, waves, &lds);
     params[n][0] = &args[n];
     p[n] = hipKernelNodeParams{};
-    p[n].func = reinterpret_cast<void *>(kKernels[kNumKinds * g.pack + kind]);
+    p[n].func = reinterpret_cast<void *>(kernel_of(a, g.pack, kind));
     p[n].gridDim = dim3(g.n_blocks);
     p[n].blockDim = dim3(64 * g.wpb);
     p[n].sharedMemBytes = (unsigned)lds;
     p[n].kernelParams = params[n];
     p[n].extra = nullptr;
-    shape[n][0] = kNumKinds * g.pack + kind;
+    shape[n][0] = kNumKinds * (launch_mode(a) * kNumPackings + g.pack) + kind;
     shape[n][1] = g.n_blocks;
     shape[n][2] = g.wpb;
     shape[n][3] = (int)lds;

@@ -57,3 +57,37 @@ def test_one_launch_for_all_packings(cxm, n, T):
                                 ("obs", ci.obs_offset, ci.obs_dim)):
             own = ref[key][:, e0 * width:e1 * width]
             assert torch.equal(out[key][:, off:off + k * width], own), (c, key)
+
+
+MODE_SPECS = {"simple": lambda: W.fanout4_tree(32, 2), "general": lambda: W.fanout4_tree(31, 2).replace(alpha_sat=0.2),
+              "dense": lambda: W.two_charger_types(), "v2g": lambda: W.v2g_station(alpha_degrad_cars=0.03),
+              "users": lambda: W.user_station(), "exo": lambda: W.exo_station()}
+
+
+@pytest.mark.parametrize("stage", [False, True])
+@pytest.mark.parametrize("per_lane", [1, 2, 4])
+@pytest.mark.parametrize("name", sorted(MODE_SPECS))
+def test_modes_equal_full_records(cxm, name, per_lane, stage):
+    """The kernels of calls without observation records and of one step against
+    those of any call: the same levels, rewards, done flags, observations and state."""
+    spec = MODE_SPECS[name]()
+    n, T = 37, 5
+    envs = [cxm.Env(spec, n_envs=n, seed=47) for _ in range(4)]
+    for e in envs:
+        e.set_packing(0, e.class_info(0).slots // per_lane, 2)
+        e.set_obs_stage(stage)
+        e.rollout(140, cxm.ACT_RANDOM)
+    full, levels, rewards, steps = envs
+    x = full.rollout(T, cxm.ACT_RANDOM)
+    y = levels.rollout(T, cxm.ACT_RANDOM, cxm.OUT_ACT_REWARD)
+    z = rewards.rollout(T, cxm.ACT_RANDOM, cxm.OUT_REWARD)
+    assert set(z) < set(y) < set(x)
+    for r in (y, z):
+        for k in r:
+            assert torch.equal(r[k], x[k]), k
+    for t in range(T):
+        w = steps.step(cxm.ACT_EXTERNAL, actions=x["actions"][t]) if t % 2 else steps.step(cxm.ACT_RANDOM)
+        for k in w:
+            assert torch.equal(w[k].reshape(-1), x[k][t].reshape(-1)), (k, t)
+    for e in (levels, rewards, steps):
+        assert e.get_state() == full.get_state()
