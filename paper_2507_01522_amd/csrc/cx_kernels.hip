@@ -1575,7 +1575,7 @@ __attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_p
 // Several groups of SIMPLE classes in one launch (a.part: each group's blocks, at
 // a multiple of 8 so that they are dealt to the XCDs as in a launch of their
 // own).  For launches too short to fill the chip one group at a time: one step
-// of 65,536 uneven stations took five kernels one after the other (74 us, now 50).
+// of 65,536 uneven stations took five kernels one after the other (74 us, now 38).
 template <int MODE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE == kModeNoObs ? 6 : 1))) void k_rollout_parts(LaunchArgs a) {
   int i = 0;
@@ -1719,19 +1719,20 @@ LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, int64
 namespace {
 
 // All groups in one launch (k_rollout_parts) when they are SIMPLE classes of one
-// or two slots per lane with one block size and the launch is one step, or has
-// at most kPartsMaxWaves waves.  A graph of one kernel per packing costs 95 us of
-// host time a launch and runs its kernels only partly at once, but keeps each
-// packing's own registers (the shared kernel takes the largest, five waves per
-// SIMD) and the stage, which pays when the chip is full.  Uneven stations x 288
-// steps, every record (rewards only), one launch against the graph: 2,000 0.50
-// (0.35) / 0.78 (0.56) ms, 10,000 0.58 (0.35) / 0.86 (0.55), 20,000 (8,400 waves)
-// 1.15 (0.62) / 1.20 (0.62), 65,536 (27,300) 3.54 (1.69) / 3.49 (1.57).  One step:
-// 300 stations 35 -> 9 us, 65,536 74 -> 50.  False: not such a launch.
-constexpr int64_t kPartsMaxWaves = 12288;
+// or two slots per lane with one block size and the launch is one step, keeps no
+// observations, or has at most kPartsMaxWaves waves.  A graph of one kernel per
+// packing costs 95 us of host time a launch and runs its kernels only partly at
+// once, but keeps each packing's own registers (the shared kernel takes the
+// largest, five waves per SIMD with observations) and the stage, which pays when
+// the chip is full.  Uneven stations x 288 steps, every record (rewards only), one
+// launch against the graph: 2,000 0.49 (0.30) / 0.80 (0.54) ms, 10,000 0.59 (0.35)
+// / 0.87 (0.53), 20,000 (8,400 waves) 1.16 (0.57) / 1.20 (0.60), 28,000 (11,700)
+// 1.58 (0.70) / 1.52 (0.73), 65,536 (27,300) 3.57 (1.46) / 3.55 (1.51).  One step:
+// 300 stations 35 -> 8.5 us, 65,536 74 -> 38.  False: not such a launch.
+constexpr int64_t kPartsMaxWaves = 10240;
 bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st, hipError_t *e) {
   if (n_groups < 2 || n_groups > LaunchArgs::kMaxParts || a.per_segment) return false;
-  if (a.T > 1 && total_waves(groups, n_groups) > kPartsMaxWaves) return false;
+  if (launch_mode(a) == kModeAny && total_waves(groups, n_groups) > kPartsMaxWaves) return false;
   LaunchArgs b = a;
   int blocks = 0, dwell = 1, days = 0;
   b.n_parts = 0;
