@@ -284,14 +284,14 @@ cx_status cx_step_ex(cx_ctx *ctx, cx_action_mode mode, const uint8_t *actions_in
  * Results equal T calls of cx_step_ex.
  * CX_ACT_POLICY draws every step's levels from the policy (cx_set_policy) on
  * the observation of the state before the step.  For a class of 8, 16 or 32
- * slots the whole rollout is one launch of a fused persistent kernel that runs
- * the perceptron between steps, its observations only in on-chip memory; larger
- * classes run, per step, the
+ * slots (with padding slots, or ports or limits that differ: packed with one slot
+ * per lane, the default) the whole rollout is one launch of a fused persistent
+ * kernel that runs the perceptron between steps, its observations only in on-chip
+ * memory; other classes run, per step, the
  * policy kernel (observation -> levels, as cx_policy_sample) and then the
  * one-step kernel with those levels, the observations in between in a scratch
  * buffer of the context unless out_mode is FULL.  Both compute the same
- * products and sums in the same order (for a class whose slots differ, those of
- * the packing with one slot per lane), so their records are the same.  The rollout
+ * products and sums in the same order, so their records are the same.  The rollout
  * starts from the observation of the current state (as cx_observe).  With
  * CX_OUT_FULL, out->obs must be 16-byte aligned.  Requires cx_set_policy. */
 cx_status cx_rollout(cx_ctx *ctx, int32_t T, cx_action_mode mode, cx_out_mode out_mode,

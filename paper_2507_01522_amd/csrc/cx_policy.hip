@@ -388,11 +388,14 @@ cx_status noalloc_scratch(int device, unsigned char **ptr) {
 namespace {
 
 // The fused rollout runs classes of 8, 16 or 32 slots (stations of 8 lanes, 1, 2
-// or 4 slots per lane); larger ones take the two kernels per step.
+// or 4 slots per lane); larger ones take the two kernels per step.  So do classes
+// that are not SIMPLE in a packing of several slots per lane: their station sums
+// are in that packing's order, the fused kernel's in the order of one slot per
+// lane (the default), and records are those of the two kernels bit for bit.
 bool fused_eligible(const cx_ctx *ctx) {
   const ClassRt &c = ctx->classes[0];
-  const int S = c.comp.S;
-  return c.host_view.kind != kKindExt && (S == 8 || S == 16 || S == 32);
+  const int S = c.comp.S, kind = c.host_view.kind;
+  return (S == 8 || S == 16 || S == 32) && (kind == kKindSimple || (kind == kKindGeneral && c.lanes == S));
 }
 
 cx_status ensure_fused(cx_ctx *ctx) {

@@ -15,11 +15,12 @@ LAUNCH = {
     "tiny": (16, 1, False),
     "scale": (16, 1, False),
 }
-# The policy rollout of a class of 8, 16 or 32 slots (extended classes aside) is
-# the fused kernel, whose launch is fixed (4 waves per block; 8 lanes per station,
-# or 16 for 16-slot stations while every block has a CU of its own); this packing
-# serves the two-kernel path of the other classes and of the rollout that
-# allocates nothing (8 lanes x 4 slots, 4 waves per block).
+# The policy rollout of a SIMPLE class of 8, 16 or 32 slots is the fused kernel,
+# whose launch is fixed (4 waves per block; 8 lanes per station, or 16 for 16-slot
+# stations while every block has a CU of its own), as is that of a general class
+# packed with one slot per lane; this packing of the policy workload's SIMPLE class
+# serves the two-kernel path, which the rollout that allocates nothing takes
+# (8 lanes x 4 slots, 4 waves per block).
 POLICY_LAUNCH = (8, 4)
 
 
