@@ -303,7 +303,7 @@ cx_status rebuild_segments(cx_ctx *ctx) {
                              hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(ctx, e, "upload of segment table");
   }
-  for (RolloutGraph &G : ctx->graph) graph_destroy(G);
+  graph_destroy(ctx->graphs);
   return CX_OK;
 }
 
@@ -327,7 +327,7 @@ void advance_clock(cx_ctx *ctx, int32_t T) {
 
 static void free_ctx(cx_ctx *ctx) {
   if (!ctx) return;
-  for (RolloutGraph &G : ctx->graph) graph_destroy(G);
+  graph_destroy(ctx->graphs);
   for (auto &c : ctx->classes)
     if (c.dev_mem) (void)hipFree(c.dev_mem);
   if (ctx->state_mem) (void)hipFree(ctx->state_mem);
@@ -573,8 +573,7 @@ cx_status cx_rollout(cx_ctx *ctx, int32_t T, cx_action_mode mode, cx_out_mode ou
     a.reward = out->reward;
     a.done = out->done;
   }
-  RolloutGraph &graph = ctx->graph[a.out_mode == CX_OUT_FULL && a.obs ? 0 : 1];
-  hipError_t e = graph_rollout(graph, a, ctx->groups.data(), (int)ctx->groups.size(), ctx->stream);
+  hipError_t e = graph_rollout(ctx->graphs, a, ctx->groups.data(), (int)ctx->groups.size(), ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "cx_rollout graph launch");
   advance_clock(ctx, T);
   return CX_OK;

@@ -57,7 +57,7 @@ struct cx_ctx {
   bool stage_obs = false;
   bool failed = false;
   int64_t device_bytes = 0;
-  cx::RolloutGraph graph[2];      // rollouts with observation records and without: other kernels
+  cx::RolloutGraphs graphs;
   cx::PolicyRt *policy = nullptr;
 };
 

@@ -286,14 +286,24 @@ inline size_t policy_rollout_lds(int dwell_log2, int obs_dim, int N, bool over_s
 }
 
 // The persistent rollout as a HIP graph with one kernel node per launch group
-// (no dependencies between them), instantiated once per launch shape and
-// re-parameterised on every call.
+// (no dependencies between them), re-parameterised on every call.
 struct RolloutGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipGraphNode_t node[kNumKinds * kNumPackings] = {};
   int n_nodes = 0;
   int shape[kNumKinds * kNumPackings][4] = {};  // kernel, blocks, waves per block, LDS bytes
+};
+// A context's graphs, one per launch shape, each instantiated once and kept until
+// the segments are built anew: a graph that gave way to the next call's shape
+// would be destroyed with its last launch still in flight, and a caller that
+// alternates horizons would pay an instantiation a call.  One set of segments has
+// at most five shapes: with observation records short or long (the stage chosen by
+// the launch's size), without them, and one step with them or without.
+struct RolloutGraphs {
+  static constexpr int kMax = 6;
+  RolloutGraph g[kMax];
+  int n = 0;
 };
 
 // Arguments of the policy kernel (cx_policy.hip): the perceptron's weights in
@@ -320,9 +330,9 @@ struct PolicyArgs {
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st);
 hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, int hp, bool held,
                                  int n_blocks, size_t lds, hipStream_t st);
-hipError_t graph_rollout(RolloutGraph &g, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
+hipError_t graph_rollout(RolloutGraphs &gs, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st);
-void graph_destroy(RolloutGraph &g);
+void graph_destroy(RolloutGraphs &gs);
 hipError_t launch_reset_obs_one(const ClassDev *cls_dev, int64_t n_envs, float *obs, uint64_t seed, int64_t env0,
                                 uint32_t g, hipStream_t st);
 // Sets n doubles at p to v (battery SoC at the start of a day).

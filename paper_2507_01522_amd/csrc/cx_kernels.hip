@@ -1873,7 +1873,30 @@ hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, in
                          st);
 }
 
-hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
+namespace {
+void destroy_one(RolloutGraph &g) {
+  if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  if (g.graph) (void)hipGraphDestroy(g.graph);
+  g = RolloutGraph{};
+}
+
+// A new graph of n kernel nodes.
+hipError_t build_graph(RolloutGraph &G, int n, const hipKernelNodeParams *p, const int (*shape)[4]) {
+  hipError_t e = hipGraphCreate(&G.graph, 0);
+  for (int i = 0; e == hipSuccess && i < n; ++i) e = hipGraphAddKernelNode(&G.node[i], G.graph, nullptr, 0, &p[i]);
+  if (e == hipSuccess) e = hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0);
+  if (e != hipSuccess) {
+    destroy_one(G);
+    return e;
+  }
+  G.n_nodes = n;
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < 4; ++j) G.shape[i][j] = shape[i][j];
+  return hipSuccess;
+}
+}  // namespace
+
+hipError_t graph_rollout(RolloutGraphs &gs, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st) {
   // one kernel is launched as it is; so are groups that share a launch
   hipError_t pe;
@@ -1906,30 +1929,31 @@ hipError_t graph_rollout(RolloutGraph &G, const LaunchArgs &a, const LaunchGroup
     ++n;
   }
   if (n == 0) return hipSuccess;
-  bool same = G.exec && G.n_nodes == n;
-  for (int i = 0; same && i < n; ++i)
-    for (int j = 0; j < 4; ++j) same = same && G.shape[i][j] == shape[i][j];
   hipError_t e;
-  if (!same) {
-    graph_destroy(G);
-    if ((e = hipGraphCreate(&G.graph, 0)) != hipSuccess) return e;
-    for (int i = 0; i < n; ++i)
-      if ((e = hipGraphAddKernelNode(&G.node[i], G.graph, nullptr, 0, &p[i])) != hipSuccess) return e;
-    if ((e = hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0)) != hipSuccess) return e;
-    G.n_nodes = n;
-    for (int i = 0; i < n; ++i)
-      for (int j = 0; j < 4; ++j) G.shape[i][j] = shape[i][j];
-  } else {
+  for (int k = 0; k < gs.n; ++k) {
+    RolloutGraph &G = gs.g[k];
+    bool same = G.n_nodes == n;
+    for (int i = 0; same && i < n; ++i)
+      for (int j = 0; j < 4; ++j) same = same && G.shape[i][j] == shape[i][j];
+    if (!same) continue;
     for (int i = 0; i < n; ++i)
       if ((e = hipGraphExecKernelNodeSetParams(G.exec, G.node[i], &p[i])) != hipSuccess) return e;
+    return hipGraphLaunch(G.exec, st);
   }
+  if (gs.n == RolloutGraphs::kMax) {
+    // (more shapes than a set of segments has: only the tuner's, of many sets)
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    graph_destroy(gs);
+  }
+  RolloutGraph &G = gs.g[gs.n];
+  if ((e = build_graph(G, n, p, shape)) != hipSuccess) return e;
+  ++gs.n;
   return hipGraphLaunch(G.exec, st);
 }
 
-void graph_destroy(RolloutGraph &g) {
-  if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (g.graph) (void)hipGraphDestroy(g.graph);
-  g = RolloutGraph{};
+void graph_destroy(RolloutGraphs &gs) {
+  for (int k = 0; k < gs.n; ++k) destroy_one(gs.g[k]);
+  gs.n = 0;
 }
 
 hipError_t launch_reset_obs_one(const ClassDev *cls_dev, int64_t n_envs, float *obs, uint64_t seed, int64_t env0,

@@ -104,7 +104,7 @@ extern "C" cx_status cx_autotune(cx_ctx *ctx, int32_t T_probe, const char *cache
   const uint32_t g_saved = ctx->g;
   const int32_t t_saved = ctx->t_day;
   cx_status st = CX_OK;
-  RolloutGraph *probe_ptr = nullptr;
+  RolloutGraphs *probe_ptr = nullptr;
   auto cleanup = [&]() {
     if (probe_ptr) graph_destroy(*probe_ptr);
     if (saved) {
@@ -142,7 +142,7 @@ extern "C" cx_status cx_autotune(cx_ctx *ctx, int32_t T_probe, const char *cache
   a.done = sb + ((obs_b + act_b + 255) & ~(size_t)255) + sizeof(float) * env_b;
   // time a launch of the given segment table as rollouts run it (one graph,
   // its kernels concurrent); min over 3 after a warm-up
-  RolloutGraph probe;
+  RolloutGraphs probe;
   probe_ptr = &probe;
   auto time_launch = [&](const SegDev *segs, const std::vector<LaunchGroup> &groups, float *best_ms) -> hipError_t {
     LaunchArgs b = a;

@@ -44,10 +44,10 @@ def _compile(src: str, out_dir: str, kind: str) -> str:
     return obj
 
 
-def build(kind: str, out_dir: str) -> str:
-    """Compile and link the driver for one sanitizer; returns the executable."""
+def build(kind: str, out_dir: str, driver: str = "drive") -> str:
+    """Compile and link a driver for one sanitizer; returns the executable."""
     os.makedirs(out_dir, exist_ok=True)
-    srcs = LIB_SOURCES + [os.path.join(HERE, "fake_hip.cpp"), os.path.join(HERE, "drive.cpp")]
+    srcs = LIB_SOURCES + [os.path.join(HERE, "fake_hip.cpp"), os.path.join(HERE, f"{driver}.cpp")]
     with cf.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         objs = list(ex.map(lambda s: _compile(s, out_dir, kind), srcs))
     # the device-code blobs the host objects refer to (there is no device code):
@@ -60,7 +60,7 @@ def build(kind: str, out_dir: str) -> str:
     with open(blobs, "w") as f:
         f.write("".join(f'extern "C" {{ char {n}[16]; }}\n' for n in sorted(names)))
     objs.append(_compile(blobs, out_dir, kind))
-    exe = os.path.join(out_dir, f"drive_{kind}")
+    exe = os.path.join(out_dir, f"{driver}_{kind}")
     r = subprocess.run([CLANGXX, *LINK[kind], "-o", exe, *objs, "-lpthread"], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link ({kind}) failed:\n{r.stderr}")
