@@ -4,6 +4,9 @@
 //
 // Usage: drive_launches SECTION
 //   horizons   a mixture that runs as a graph, calls of different kinds in turn
+//   parts      mixtures of SIMPLE packings, in one launch and past its limits
+//   stage      the observation stage chosen by a launch's size
+//   policy     policy rollouts of every size of the fused kernels, and the two kernels
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -17,6 +20,7 @@
 
 extern "C" long fake_hip_graph_destroys_in_flight();
 extern "C" long fake_hip_live_allocations();
+extern "C" long fake_hip_launches(const char *part);
 
 namespace {
 
@@ -122,6 +126,18 @@ struct Context {
     CK(cx_get_info(c, &info));
   }
   ~Context() { cx_destroy(c); }
+  // launches of kernels named `part` that a call makes
+  template <class F>
+  long count(const char *part, F &&call) {
+    CK(cx_synchronize(c));
+    const long before = fake_hip_launches(part);
+    CK(call());
+    CK(cx_synchronize(c));
+    return fake_hip_launches(part) - before;
+  }
+  cx_status rollout(int T, cx_out_mode mode, const Traj &tr) {
+    return cx_rollout(c, T, CX_ACT_RANDOM, mode, nullptr, &tr.t);
+  }
 };
 
 // Calls of different kinds in turn, none waited for: each launch shape has a graph
@@ -150,12 +166,129 @@ void horizons() {
   }
 }
 
+// Five packings of SIMPLE classes in every block size.
+void parts() {
+  Station s8(8), s16(16), s32(32), s64(64), s128(128), odd(16);
+  odd.s.dwell_max = 4096;   // the launch's LDS holds the largest stay table and the longest day
+  for (int steps : {288, 512, 600}) {   // (600: a day too long for the tables in LDS)
+    for (Station *s : {&s8, &s16, &s32, &s64, &s128, &odd}) s->s.steps_per_episode = steps;
+    Context x({&s8, &s16, &s32, &s64, &s128, &odd}, {70, 41, 9, 3, 2, 1});
+    Traj tr(x.info, 40);
+    Dev act_in((size_t)40 * x.info.total_ports);
+    for (int wpb : {1, 2, 4, 8}) {
+      for (int c = 0; c < x.info.n_classes; ++c) {
+        cx_class_info ci{};
+        CK(cx_get_class_info(x.c, c, &ci));
+        CK(cx_set_packing(x.c, c, ci.slots == 128 || (ci.slots == 32 && wpb == 4) ? ci.slots / 2 : ci.slots, wpb));
+      }
+      for (int T : {1, 24, 40}) {
+        for (cx_out_mode m : {CX_OUT_FULL, CX_OUT_ACT_REWARD, CX_OUT_REWARD})
+          REQUIRE(x.count("k_rollout_parts<", [&] { return x.rollout(T, m, tr); }) == 1);
+        CK(cx_rollout(x.c, T, CX_ACT_EXTERNAL, CX_OUT_FULL, static_cast<uint8_t *>(act_in.p), &tr.t));
+      }
+      REQUIRE(x.count("k_rollout_parts<2>", [&] { return cx_step_ex(x.c, CX_ACT_MAX, nullptr, &tr.t); }) == 1);
+    }
+  }
+  // every record: one launch up to 10,240 waves, past them a graph; one step and
+  // calls without observations always one launch.  64-port stations take a wave
+  // each, 16-port ones a quarter of one; blocks of 4 waves.
+  for (Station *s : {&s16, &s64}) s->s.steps_per_episode = 288;
+  for (int64_t n64 : {10240 - 4, 10240}) {
+    Context x({&s16, &s64}, {16, n64});
+    Traj tr(x.info, 33);
+    const bool one = n64 + 4 <= 10240;
+    REQUIRE(x.count("k_rollout_parts<0>", [&] { return x.rollout(33, CX_OUT_FULL, tr); }) == (one ? 1 : 0));
+    REQUIRE(x.count("k_rollout_simple<64, 1, true, 0>", [&] { return x.rollout(33, CX_OUT_FULL, tr); }) == (one ? 0 : 1));
+    REQUIRE(x.count("k_rollout_parts<1>", [&] { return x.rollout(33, CX_OUT_REWARD, tr); }) == 1);
+    REQUIRE(x.count("k_rollout_parts<2>", [&] { return cx_step_ex(x.c, CX_ACT_MAX, nullptr, &tr.t); }) == 1);
+  }
+}
+
+// One SIMPLE packing: every record of 32 steps or more goes through the stage from
+// 8,192 waves (2,048 blocks of 4), below it and in shorter calls only when asked.
+void stage() {
+  const Station s64(64);
+  for (int64_t n : {8192 - 4, 8192 - 3}) {
+    Context x({&s64}, {n});
+    Traj tr(x.info, 32);
+    const long big = n == 8192 - 3;   // (a last block of one wave counts as four)
+    const char *staged = "k_rollout_simple<64, 1, true, 0>";
+    REQUIRE(x.count(staged, [&] { return x.rollout(32, CX_OUT_FULL, tr); }) == big);
+    REQUIRE(x.count(staged, [&] { return x.rollout(31, CX_OUT_FULL, tr); }) == 0);
+    REQUIRE(x.count(staged, [&] { return x.rollout(32, CX_OUT_ACT_REWARD, tr); }) == 0);
+    CK(cx_set_obs_stage(x.c, 1));
+    REQUIRE(x.count(staged, [&] { return x.rollout(31, CX_OUT_FULL, tr); }) == 1);
+    REQUIRE(x.count(staged, [&] { return x.rollout(1, CX_OUT_FULL, tr); }) == 1);
+  }
+}
+
+void policy_rollouts(const Station &st, int64_t n, int hidden, const char *kernel) {
+  Context x({&st}, {n});
+  const int in = 6 * st.s.n_ports + 4, out = st.s.n_ports * (st.s.n_levels + 1);
+  const std::vector<uint16_t> w1((size_t)in * hidden, 0x3c00), b1(hidden, 0x3c00), w2((size_t)hidden * out, 0x3c00),
+      b2(out, 0x3c00);
+  CK(cx_set_policy(x.c, hidden, w1.data(), b1.data(), w2.data(), b2.data()));
+  Traj tr(x.info, 40);
+  auto run = [&](int T, cx_out_mode m) { return cx_rollout(x.c, T, CX_ACT_POLICY, m, nullptr, &tr.t); };
+  for (cx_out_mode m : {CX_OUT_FULL, CX_OUT_ACT_REWARD, CX_OUT_REWARD}) {
+    REQUIRE(x.count(kernel, [&] { return run(40, m); }) > 0);
+    REQUIRE(x.count(kernel, [&] { return run(3, m); }) > 0);
+  }
+  CK(cx_step_ex(x.c, CX_ACT_POLICY, nullptr, &tr.t));
+  Dev logits(4 * (size_t)n * out);
+  CK(cx_policy_logits(x.c, tr.t.obs, n, static_cast<float *>(logits.p)));
+  CK(cx_policy_sample(x.c, tr.t.obs, n, 3, tr.t.actions));
+  CK(cx_rollout_policy_noalloc(x.c, 3, CX_OUT_FULL, &tr.t));
+}
+
+void policy() {
+  for (int hidden : {32, 96, 128, 256}) {
+    const int hp = hidden <= 64 ? 2 : hidden <= 128 ? 4 : 8;
+    auto name = [&](bool general, int L, int P, bool held) {
+      return std::string(general ? "k_rollout_policy_general<" : "k_rollout_policy<") + std::to_string(L) + ", " +
+             std::to_string(P) + ", " + std::to_string(hp) + ", " + (held ? "true>" : "false>");
+    };
+    // 8, 16 and 32 slots: SIMPLE, and with padding slots and uneven ports.  Blocks
+    // of 32 stations (8 lanes) or 16 (16 lanes); weights held up to 256 blocks.
+    struct {
+      int ports;
+      bool uneven;
+    } const stations[] = {{8, false}, {16, false}, {32, false}, {7, true}, {13, true}, {29, true}, {32, true}};
+    for (const auto &c : stations) {
+      const int S = c.ports <= 8 ? 8 : c.ports <= 16 ? 16 : 32;
+      for (int dwell : {2, 1024, 4096}) {
+        for (int steps : {288, 600}) {
+          Station st(c.ports, c.uneven);
+          st.s.dwell_max = dwell;
+          st.s.steps_per_episode = steps;
+          // (32 slots and a stay table of more than 1,024 entries: no LDS for the held layout)
+          const bool held = S < 32 || dwell <= 1024;
+          for (int64_t n : {1, 33})
+            policy_rollouts(st, n, hidden, name(c.uneven, S == 16 ? 16 : 8, S == 16 ? 1 : S / 8, held).c_str());
+        }
+      }
+      const Station st(c.ports, c.uneven);
+      if (S == 16) {
+        policy_rollouts(st, 4096, hidden, name(c.uneven, 16, 1, true).c_str());
+        policy_rollouts(st, 4097, hidden, name(c.uneven, 8, 2, true).c_str());
+      }
+      policy_rollouts(st, 8192, hidden, name(c.uneven, 8, S / 8, true).c_str());
+      policy_rollouts(st, 8193, hidden, name(c.uneven, 8, S / 8, false).c_str());
+    }
+  }
+  // classes of other sizes take two kernels a step
+  for (int ports : {3, 41}) policy_rollouts(Station(ports), 70, 128, "k_policy(");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   const long live0 = fake_hip_live_allocations();
   if (what == "horizons") horizons();
+  else if (what == "parts") parts();
+  else if (what == "stage") stage();
+  else if (what == "policy") policy();
   else return 2;
   std::printf("graph execs destroyed with launches in flight: %ld\n", fake_hip_graph_destroys_in_flight());
   std::printf("device allocations left: %ld\n", fake_hip_live_allocations() - live0);

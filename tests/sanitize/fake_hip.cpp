@@ -263,45 +263,47 @@ T arg(const Launch &l, size_t i) {
   return v;
 }
 
-// template arguments <L, P, SIMPLE, EXT, STAGE[, POL]> of a k_rollout instance
-void rollout_params(const std::string &n, int *L, int *P, bool *simple, bool *ext, bool *stage, bool *pol) {
+// What a rollout kernel's name says of it: packing, class kind, stage, what the
+// kernel knows of the call (mode: 1 no observation records, 2 one step), the fused
+// policy's K-steps of 32 hidden units (0: not fused) and whether it holds weights.
+struct Kernel {
+  int L = 0, P = 0, mode = 0, hp = 0;
+  bool simple = false, ext = false, stage = false, held = false;
+};
+
+Kernel parse_rollout(const std::string &n) {
   const size_t a = n.find('<');
-  int l = 0, p = 0;
-  char s1[8] = {0}, s2[8] = {0}, s3[8] = {0}, s4[8] = {0};
-  if (n.find("k_rollout_simple<") != std::string::npos) {  // SIMPLE classes: <L, P, STAGE>
-    if (a == std::string::npos || std::sscanf(n.c_str() + a, "<%d, %d, %5[a-z]>", &l, &p, s3) != 3)
-      die("cannot parse %s", n.c_str());
-    *L = l;
-    *P = p;
-    *simple = true;
-    *ext = *pol = false;
-    *stage = std::strcmp(s3, "true") == 0;
-    return;
+  const char *args = a == std::string::npos ? "" : n.c_str() + a;
+  Kernel k;
+  char s1[8] = {0}, s2[8] = {0}, s3[8] = {0};
+  auto yes = [](const char *s) { return std::strcmp(s, "true") == 0; };
+  bool ok;
+  if (n.find("k_rollout_simple<") != std::string::npos) {          // <L, P, STAGE, MODE>
+    ok = std::sscanf(args, "<%d, %d, %5[a-z], %d>", &k.L, &k.P, s1, &k.mode) == 4;
+    k.simple = true;
+    k.stage = yes(s1);
+  } else if (n.find("k_rollout_policy") != std::string::npos) {    // <L, P, HP, HELD>, SIMPLE or _general
+    ok = std::sscanf(args, "<%d, %d, %d, %5[a-z]>", &k.L, &k.P, &k.hp, s1) == 4;
+    k.simple = n.find("k_rollout_policy_general<") == std::string::npos;
+    k.stage = true;
+    k.held = yes(s1);
+  } else {                                                         // <L, P, SIMPLE, EXT, STAGE, MODE>
+    ok = std::sscanf(args, "<%d, %d, %5[a-z], %5[a-z], %5[a-z], %d>", &k.L, &k.P, s1, s2, s3, &k.mode) == 6;
+    k.simple = yes(s1);
+    k.ext = yes(s2);
+    k.stage = yes(s3);
   }
-  if (n.find("k_rollout_policy<") != std::string::npos) {  // the fused policy rollout: <L, P>
-    if (a == std::string::npos || std::sscanf(n.c_str() + a, "<%d, %d>", &l, &p) != 2) die("cannot parse %s", n.c_str());
-    *L = l;
-    *P = p;
-    *simple = *stage = *pol = true;
-    *ext = false;
-    return;
-  }
-  const int got = a == std::string::npos ? 0
-                                         : std::sscanf(n.c_str() + a, "<%d, %d, %5[a-z], %5[a-z], %5[a-z], %5[a-z]>",
-                                                       &l, &p, s1, s2, s3, s4);
-  if (got < 5) die("cannot parse %s", n.c_str());
-  *L = l;
-  *P = p;
-  *simple = std::strcmp(s1, "true") == 0;
-  *ext = std::strcmp(s2, "true") == 0;
-  *stage = std::strcmp(s3, "true") == 0;
-  *pol = got == 6 && std::strcmp(s4, "true") == 0;
+  if (!ok) die("cannot parse %s", n.c_str());
+  return k;
 }
 
 void check_class(const cx::ClassDev *cls, const std::string &w) {
   need(cls, sizeof(cx::ClassDev), "class block", w);
   const cx::ClassDev &C = *cls;
-  need(C.slot_port, 4 * (size_t)C.S, "slot_port", w);
+  for (const void *slots : {(const void *)C.slot_port, (const void *)C.slot_pmax, (const void *)C.slot_inv_pmax,
+                            (const void *)C.slot_inv_eta, (const void *)C.slot_lb, (const void *)C.slot_pdis,
+                            (const void *)C.slot_eta, (const void *)C.slot_dc})
+    need(slots, 4 * (size_t)C.S, "per-slot constants", w);
   need(C.slot_cap, 4 * (size_t)C.S * C.D, "slot_cap", w);
   need(C.tpois, 4 * (size_t)C.steps_ep * cx::kPoisStride, "arrival thresholds", w);
   need(C.tdwell, (size_t)4 << C.dwell_log2, "stay thresholds", w);
@@ -309,66 +311,79 @@ void check_class(const cx::ClassDev *cls, const std::string &w) {
   if (C.n_days > 0) need(C.price_days, 4 * (size_t)C.n_days * C.steps_ep, "price days", w);
 }
 
-void run_rollout(const Launch &l, const KernelInfo &k) {
-  int L, P;
-  bool simple, ext, stage, pol;
-  rollout_params(k.name, &L, &P, &simple, &ext, &stage, &pol);
-  const cx::LaunchArgs a = arg<cx::LaunchArgs>(l, 0);
-  const std::string w0 = k.name;
-  if (l.block.x % 64 != 0 || l.block.x == 0 || l.block.x > 512 || l.block.y != 1 || l.grid.y != 1)
-    die("%s: launch shape %u x %u", w0.c_str(), l.grid.x, l.block.x);
-  if (pol) {
-    // the fused policy rollout: 4 waves of 8-lane stations, the stage, the
-    // hidden units, the BF16 observations and the levels inside the LDS
-    const cx::LaunchArgs::Pol &q = a.pol;
-    if (L != 8 || !simple || ext || !stage || (int)l.block.x != 64 * cx::kPolRolloutWaves)
-      die("%s: fused policy launch of %u threads", w0.c_str(), l.block.x);
-    if (a.mode != CX_ACT_POLICY || a.per_segment) die("%s: mode %d", w0.c_str(), a.mode);
-    if (q.K1 < 1 || q.K1 > 8 || q.HP < 1 || q.HP > 8 || q.R < 1 || q.R > 3 || q.G < 1 || q.L1 < 2 || q.L1 > 4 * q.R)
-      die("%s: MLP sizes K1 %d HP %d R %d G %d L1 %d", w0.c_str(), q.K1, q.HP, q.R, q.G, q.L1);
-    if (q.in_dim > 32 * q.K1) die("%s: in_dim %d > 32 K1", w0.c_str(), q.in_dim);
-    const size_t stage_end = (size_t)a.stage_off + 4 * (size_t)a.stage_floats;
-    const size_t hb_end = (size_t)q.hb_off + (size_t)8 * (cx::kPolRolloutEnvs / 16) * 64 * 16;
-    const size_t xb_end = (size_t)q.xb_off + (size_t)cx::kPolRolloutEnvs * 16 * cx::kPolXbRow;
-    if (a.stage_floats < cx::kPolRolloutEnvs * q.in_dim) die("%s: stage of %d floats", w0.c_str(), a.stage_floats);
-    if (q.hb_off < a.stage_off || std::max(stage_end, hb_end) > (size_t)q.xb_off || xb_end > (size_t)q.act_off)
-      die("%s: LDS regions overlap (stage %d+%zu, hb %d, xb %d, act %d)", w0.c_str(), a.stage_off,
-          stage_end - a.stage_off, q.hb_off, q.xb_off, q.act_off);
-    if ((q.xb_off | q.hb_off | a.stage_off) & 15) die("%s: LDS regions not 16-byte aligned", w0.c_str());
-    // padded fragments: 16 hidden tiles x 8 K-steps; G x 3 level tiles x 8 K-steps
-    need(q.w1f, 16 * (size_t)16 * 8 * 64, "W1 fragments", w0);
-    need(q.b1, 4 * (size_t)256, "b1", w0);
-    need(q.w2f, 16 * (size_t)q.G * 3 * 8 * 64, "W2 fragments", w0);
-    need(q.b2f, 4 * 16 * (size_t)q.G * 3, "b2", w0);
+// A block's regions of dynamic LDS: inside what the launch asks for, and apart.
+struct Lds {
+  struct Region {
+    size_t begin, end;
+    const char *what;
+  };
+  std::vector<Region> r;
+  void add(int64_t begin, size_t bytes, const char *what) {
+    if (bytes > 0) r.push_back({(size_t)begin, (size_t)begin + bytes, what});
   }
-  if (a.n_segs < 1) die("%s: no segments", w0.c_str());
-  need(a.segs, sizeof(cx::SegDev) * (size_t)a.n_segs, "segment table", w0);
-  std::vector<cx::SegDev> segs(a.n_segs);
-  std::memcpy(segs.data(), a.segs, sizeof(cx::SegDev) * segs.size());  // as the kernel reads it, now
-  const int W = (int)l.block.x / 64, SPW = 64 / L;
-  const size_t table_lds = a.lds_tdwell ? 0 : 0;
-  (void)table_lds;
-  for (unsigned b = 0; b < l.grid.x; ++b) {
-    int lo = 0, hi = a.n_segs - 1;
+  void check(size_t lds, const std::string &w) const {
+    for (size_t i = 0; i < r.size(); ++i) {
+      if (r[i].end > lds) die("%s: %s at [%zu, %zu) past the launch's %zu bytes of LDS", w.c_str(), r[i].what,
+                              r[i].begin, r[i].end, lds);
+      for (size_t j = 0; j < i; ++j)
+        if (r[i].begin < r[j].end && r[j].begin < r[i].end)
+          die("%s: %s [%zu, %zu) overlaps %s [%zu, %zu)", w.c_str(), r[i].what, r[i].begin, r[i].end, r[j].what,
+              r[j].begin, r[j].end);
+    }
+  }
+};
+
+// The fused policy rollout's arguments: sizes, the padded weight fragments (W1 16
+// hidden tiles x 8 K-steps, W2 G x 3 level tiles x 8 K-steps of 1 KiB).
+void check_policy(const Launch &l, const Kernel &k, const cx::LaunchArgs &a, const std::string &w) {
+  const cx::LaunchArgs::Pol &q = a.pol;
+  if ((k.L != 8 && (k.L != 16 || k.P != 1 || !k.held)) || (int)l.block.x != 64 * cx::kPolRolloutWaves)
+    die("%s: fused policy launch of %u threads", w.c_str(), l.block.x);
+  if (a.mode != CX_ACT_POLICY || a.per_segment) die("%s: mode %d", w.c_str(), a.mode);
+  if (q.G < 1 || q.L1 < 2 || q.L1 > 12 || q.in_dim < 1 || q.in_dim > 32 * ((6 * k.L * k.P + 4 + 31) / 32))
+    die("%s: MLP sizes in %d G %d L1 %d", w.c_str(), q.in_dim, q.G, q.L1);
+  if (q.HP > k.hp) die("%s: %d K-steps of hidden units in a kernel of %d", w.c_str(), q.HP, k.hp);
+  // port groups of a wave whose fragments a kernel with all weights held has
+  const int held_groups = std::max(1, k.L * k.P / 16);
+  if (k.held && held_groups * k.hp <= 8 && cx::kPolRolloutWaves * held_groups < q.G)
+    die("%s: %d port groups, %d held a wave", w.c_str(), q.G, held_groups);
+  if ((q.xb_off | q.hb_off | a.stage_off | a.day_off) & 15) die("%s: LDS regions not 16-byte aligned", w.c_str());
+  need(q.w1f, 1024 * (size_t)16 * 8, "W1 fragments", w);
+  need(q.b1, 4 * (size_t)256, "b1", w);
+  need(q.w2f, 1024 * (size_t)q.G * 3 * 8, "W2 fragments", w);
+  need(q.b2f, 4 * 16 * (size_t)q.G * 3, "b2", w);
+}
+
+// Blocks b of [0, n_blocks) of one packing over segments [0, n_segs) of the table.
+void check_blocks(const Launch &l, const Kernel &k, const cx::LaunchArgs &a, const cx::SegDev *table, int n_segs,
+                  int n_blocks, const std::string &w0) {
+  const int L = k.L, P = k.P, W = (int)l.block.x / 64, SPW = 64 / L;
+  const bool pol = k.hp > 0;
+  if (n_segs < 1) die("%s: no segments", w0.c_str());
+  need(table, sizeof(cx::SegDev) * (size_t)n_segs, "segment table", w0);
+  std::vector<cx::SegDev> segs(n_segs);
+  std::memcpy(segs.data(), table, sizeof(cx::SegDev) * segs.size());  // as the kernel reads it, now
+  int64_t envs = 0;
+  for (const cx::SegDev &sg : segs) envs += sg.n_envs;
+  for (int b = 0; b < n_blocks; ++b) {
+    int lo = 0, hi = n_segs - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (segs[mid].block_begin <= (int)b) lo = mid;
+      if (segs[mid].block_begin <= b) lo = mid;
       else hi = mid - 1;
     }
     const cx::SegDev &sg = segs[lo];
     char wb[512];
-    std::snprintf(wb, sizeof wb, "%s block %u (segment %d)", w0.c_str(), b, lo);
+    std::snprintf(wb, sizeof wb, "%s block %d (segment %d)", w0.c_str(), b, lo);
     const std::string w = wb;
-    if (sg.block_begin > (int)b) die("%s: no segment starts at or before the block", w.c_str());
+    if (sg.block_begin > b) die("%s: no segment starts at or before the block", w.c_str());
     check_class(sg.cls, w);
     const cx::ClassDev &C = *sg.cls;
-    if (a.lds_tdwell && l.lds < ((size_t)4 << C.dwell_log2)) die("%s: LDS %zu < stay table", w.c_str(), l.lds);
     if (C.S != L * P) die("%s: class has %d slots, kernel packs %d x %d", w.c_str(), C.S, L, P);
     if (sg.pack != cx::pack_id(L, P)) die("%s: segment packing %d, kernel %d", w.c_str(), sg.pack, cx::pack_id(L, P));
-    const bool kind_ext = C.kind == cx::kKindExt;
-    if (kind_ext != ext) die("%s: class kind %d in a kernel with EXT = %d", w.c_str(), C.kind, (int)ext);
-    if (simple && C.simple != 1) die("%s: non-SIMPLE class in a SIMPLE kernel", w.c_str());
-    const int g_blk0 = ((int)b - sg.block_begin) * W;
+    if ((C.kind == cx::kKindExt) != k.ext) die("%s: class kind %d in a kernel with EXT = %d", w.c_str(), C.kind, (int)k.ext);
+    if (k.simple && (C.simple != 1 || C.n_ports != C.S)) die("%s: non-SIMPLE class in a SIMPLE kernel", w.c_str());
+    const int g_blk0 = (b - sg.block_begin) * W;
     if (g_blk0 >= sg.n_groups) {
       if (pol) die("%s: idle block in a fused policy launch", w.c_str());
       continue;  // idle block
@@ -378,22 +393,24 @@ void run_rollout(const Launch &l, const KernelInfo &k) {
     const int64_t e1 = std::min<int64_t>(sg.n_envs, (int64_t)(g_blk0 + n_run) * SPW);
     if (e0 >= e1) die("%s: block runs no env", w.c_str());
     const int64_t n = e1 - e0, S = C.S;
+    envs -= n;
     need(sg.q + e0 * S, 8 * n * S, "q", w);
     need(sg.u + e0 * S, 4 * n * S, "u", w);
     need(sg.cap + e0 * S, 4 * n * S, "capacity", w);
     need(sg.p_last + e0 * S, 4 * n * S, "last power", w);
     need(sg.dwell + e0 * S, 2 * n * S, "dwell", w);
     need(sg.ret + e0, 8 * n, "return", w);
-    if (ext && C.has_batt) {
-      need(sg.bsoc + e0, 8 * n, "battery SoC", w);
-      need(sg.bp + e0, 4 * n, "battery power", w);
+    if (k.ext) {
+      need(C.model_thresh, 4 * 8, "car model thresholds", w);
+      need(C.model_data, 4 * 24, "car models", w);
+      if (C.has_batt) {
+        need(sg.bsoc + e0, 8 * n, "battery SoC", w);
+        need(sg.bp + e0, 4 * n, "battery power", w);
+      }
+      if (C.has_users) need(sg.utype + e0 * S, (size_t)(n * S), "user types", w);
+      if (C.n_models > 0) need(sg.rbar + e0 * S, 4 * n * S, "car rates", w);
     }
-    if (ext && C.has_users) need(sg.utype + e0 * S, (size_t)(n * S), "user types", w);
-    if (ext && C.n_models > 0) need(sg.rbar + e0 * S, 4 * n * S, "car rates", w);
     if (pol) {
-      if (C.n_ports != S || C.S != 8 * P) die("%s: fused policy class of %d ports in %d slots", w.c_str(), C.n_ports, C.S);
-      if ((size_t)cx::kPolRolloutEnvs * S > (size_t)l.lds - (size_t)a.pol.act_off)
-        die("%s: LDS %zu too small for the levels", w.c_str(), l.lds);
       if (a.pol.in_dim != C.obs_dim) die("%s: MLP input %d, observation %d", w.c_str(), a.pol.in_dim, C.obs_dim);
       if (4 * a.pol.G < C.n_ports) die("%s: %d port groups for %d ports", w.c_str(), a.pol.G, C.n_ports);
       need(a.pol.obs0 + sg.obs_off + e0 * C.obs_dim, 4 * (size_t)(n * C.obs_dim), "start observations", w);
@@ -414,18 +431,40 @@ void run_rollout(const Launch &l, const KernelInfo &k) {
     const bool w_obs = out_mode == CX_OUT_FULL && obs;
     const bool w_act = (out_mode == CX_OUT_FULL || out_mode == CX_OUT_ACT_REWARD) && act;
     const int od = C.obs_dim, na = C.n_act;
+    if (k.mode == 2 && T != 1) die("%s: %d steps in the kernel of one", w.c_str(), T);
+    if (k.mode == 1 && w_obs) die("%s: observations asked of a kernel without them", w.c_str());
     if ((uint64_t)sg.n_envs * (uint64_t)od * 4 >= (1ull << 32)) die("%s: 32-bit observation offsets overflow", w.c_str());
+    // the block's LDS
+    Lds lds;
+    lds.add(0, (size_t)4 << C.dwell_log2, "stay table");
+    const bool days = k.mode != 2 && (k.held ? a.day_off > 0 : !pol) && C.steps_ep <= cx::kLdsExoSteps && T >= cx::kLdsExoMinT;
+    if (days) lds.add(a.day_off, 20 * (size_t)C.steps_ep, "day tables");
+    if (k.ext) lds.add(a.car_off, cx::kCarTabBytes, "car tables");
+    if (pol) {
+      const int E = cx::kPolRolloutWaves * SPW;
+      // (the stage holds the start observation whatever is recorded)
+      const int pad = k.simple ? 0 : 3;
+      if (a.stage_floats < pad + E * od) die("%s: stage of %d floats for %d", w.c_str(), a.stage_floats, pad + E * od);
+      lds.add(a.pol.xb_off, (size_t)E * 16 * cx::kPolXbRow, "BF16 observations");
+      lds.add(a.pol.act_off, (size_t)E * C.n_ports, "levels");
+      Lds hidden = lds;   // over the stage or apart from it
+      hidden.add(a.pol.hb_off, (size_t)k.hp * (E / 16) * 1024, "hidden units");
+      hidden.check(l.lds, w);
+      if (cx::policy_dual((int)S, k.held)) lds = hidden;
+      lds.add(a.stage_off, 4 * (size_t)a.stage_floats, "observation stage");
+    } else if (k.stage && w_obs) {
+      if (a.stage_floats < 3 + (int)(n * od)) die("%s: stage of %d floats for %d", w.c_str(), a.stage_floats, (int)(n * od));
+      if (a.stage_off & 15) die("%s: stage not 16-byte aligned", w.c_str());
+      lds.add(a.stage_off, (W == 1 ? 4 : 8) * (size_t)a.stage_floats, "observation stage");
+    }
+    lds.check(l.lds, w);
     for (int t : {0, T - 1}) {
       if (w_obs) {
         float *base = obs + sg.obs_off + (int64_t)t * os;
-        if (stage) {
+        if (k.stage) {
           const int pad = (int)((reinterpret_cast<uintptr_t>(base + e0 * od) >> 2) & 3u);
-          if (pol && pad != 0) die("%s: fused policy observations not 16-byte aligned", w.c_str());
+          if (pol && k.simple && pad != 0) die("%s: fused policy observations not 16-byte aligned", w.c_str());
           const int nf = (int)(n * od);
-          const size_t need_lds = (size_t)a.stage_off + (pol ? 4 : 8) * (size_t)a.stage_floats;
-          if (a.stage_floats < pad + nf) die("%s: stage of %d floats for %d", w.c_str(), a.stage_floats, pad + nf);
-          if (l.lds < need_lds) die("%s: LDS %zu < %zu with the stages", w.c_str(), l.lds, need_lds);
-          if (a.stage_off < ((int32_t)4 << C.dwell_log2)) die("%s: stage overlaps the stay table", w.c_str());
           // 16-byte chunks from the aligned address below the run's first float
           const int c_end = (pad + nf) >> 2;
           char *chunk0 = reinterpret_cast<char *>(base + e0 * od) - 4 * pad;
@@ -440,28 +479,87 @@ void run_rollout(const Launch &l, const KernelInfo &k) {
       if (done) need(done + sg.env_off + (int64_t)t * es + e0, (size_t)n, "done flags", w);
     }
   }
+  if (envs != 0) die("%s: %lld envs run by no block or by two", w0.c_str(), (long long)envs);
 }
 
+void check_shape(const Launch &l, const std::string &w) {
+  if (l.block.x % 64 != 0 || l.block.x == 0 || l.block.x > 512 || l.block.y != 1 || l.grid.y != 1)
+    die("%s: launch shape %u x %u", w.c_str(), l.grid.x, l.block.x);
+}
+
+void run_rollout(const Launch &l, const KernelInfo &info) {
+  const Kernel k = parse_rollout(info.name);
+  const cx::LaunchArgs a = arg<cx::LaunchArgs>(l, 0);
+  check_shape(l, info.name);
+  if (k.hp > 0) check_policy(l, k, a, info.name);
+  check_blocks(l, k, a, a.segs, a.n_segs, (int)l.grid.x, info.name);
+}
+
+// Several SIMPLE groups in one launch: part i has blocks [block_begin, +n_blocks) of
+// the grid, its own range of the segment table and its packing.
+void run_parts(const Launch &l, const KernelInfo &info) {
+  const cx::LaunchArgs a = arg<cx::LaunchArgs>(l, 0);
+  const std::string &w = info.name;
+  check_shape(l, w);
+  int mode = -1;
+  if (std::sscanf(w.c_str() + w.find('<'), "<%d>", &mode) != 1) die("cannot parse %s", w.c_str());
+  if (a.per_segment) die("%s: per-segment launch", w.c_str());
+  if (a.n_parts < 1 || a.n_parts > cx::LaunchArgs::kMaxParts) die("%s: %d parts", w.c_str(), a.n_parts);
+  int64_t end = 0;
+  for (int i = 0; i < a.n_parts; ++i) {
+    const cx::LaunchArgs::Part &p = a.part[i];
+    if (p.block_begin < end || p.block_begin % 8 != 0 || p.n_blocks < 1) die("%s: part %d at block %d", w.c_str(), i, p.block_begin);
+    end = (int64_t)p.block_begin + p.n_blocks;
+    Kernel k;
+    k.P = p.pack / 100;
+    k.L = p.pack % 100;
+    k.simple = true;
+    k.mode = mode;
+    if ((k.P != 1 && k.P != 2) || cx::part_id(k.L, k.P) != p.pack) die("%s: part %d packing %d", w.c_str(), i, p.pack);
+    check_blocks(l, k, a, a.segs + p.seg_begin, p.n_segs, p.n_blocks, w + " part " + std::to_string(i));
+  }
+  if (end != l.grid.x) die("%s: %u blocks for %lld", w.c_str(), l.grid.x, (long long)end);
+}
+
+// The standalone policy kernel: 4 waves and 32 observations a block, padded weight
+// fragments as for the fused rollout.
 void run_policy(const Launch &l) {
   const cx::PolicyArgs a = arg<cx::PolicyArgs>(l, 0);
   const std::string w = "k_policy";
   if (a.n <= 0) die("k_policy: n = %lld", (long long)a.n);
+  if (l.block.x != 256) die("k_policy: %u threads", l.block.x);
+  if (a.HP < 1 || a.HP > 8 || a.K1 < 1 || a.K1 > 8 || a.in_dim > 32 * a.K1 || a.L1 > 12 || 4 * a.G < a.N)
+    die("k_policy: K1 %d HP %d G %d L1 %d in %d", a.K1, a.HP, a.G, a.L1, a.in_dim);
   need(a.obs, 4 * (size_t)(a.n * a.in_dim), "observations", w);
-  need(a.w1f, 16 * (size_t)(2 * a.HP) * a.K1 * 64, "W1 fragments", w);
-  need(a.b1, 4 * 32 * (size_t)a.HP, "b1", w);
-  need(a.w2f, 16 * (size_t)a.G * a.R * a.HP * 64, "W2 fragments", w);
-  need(a.b2f, 4 * 16 * (size_t)a.G * a.R, "b2", w);
+  need(a.w1f, 1024 * (size_t)16 * 8, "W1 fragments", w);
+  need(a.b1, 4 * (size_t)256, "b1", w);
+  need(a.w2f, 1024 * (size_t)a.G * 3 * 8, "W2 fragments", w);
+  need(a.b2f, 4 * 16 * (size_t)a.G * 3, "b2", w);
   if (a.act) need(a.act, (size_t)(a.n * a.N), "levels", w);
   if (a.logits) need(a.logits, 4 * (size_t)(a.n * a.N * a.L1), "logits", w);
-  const int64_t waves = (a.n + 31) / 32;
-  if ((int64_t)l.grid.x * 8 < waves) die("k_policy: %u blocks for %lld waves", l.grid.x, (long long)waves);
+  if ((int64_t)l.grid.x != (a.n + 31) / 32) die("k_policy: %u blocks for %lld rows", l.grid.x, (long long)a.n);
+  // 32 rows of BF16 observations (and over them 32 N level bytes or a tile's logits),
+  // then the hidden units
+  const size_t xb = 32 * 16 * (size_t)cx::kPolXbRow;
+  if (l.lds < xb + 8 * 2 * 1024) die("k_policy: %zu bytes of LDS", l.lds);
+  if (32 * (size_t)a.N > xb) die("k_policy: %d ports", a.N);
 }
+
+std::mutex lmu;                       // guards launches
+std::map<std::string, long> launches; // kernels run so far, by name
 
 void run_kernel(const Launch &l) {
   const KernelInfo &k = kernel(l.func);
-  if (k.name.find("k_rollout<") != std::string::npos || k.name.find("k_rollout_policy<") != std::string::npos ||
-      k.name.find("k_rollout_simple<") != std::string::npos) {
+  {
+    std::lock_guard<std::mutex> lk(lmu);
+    ++launches[k.name];
+  }
+  if (k.name.find("k_rollout<") != std::string::npos || k.name.find("k_rollout_simple<") != std::string::npos ||
+      k.name.find("k_rollout_policy<") != std::string::npos ||
+      k.name.find("k_rollout_policy_general<") != std::string::npos) {
     run_rollout(l, k);
+  } else if (k.name.find("k_rollout_parts<") != std::string::npos) {
+    run_parts(l, k);
   } else if (k.name.find("k_policy(") != std::string::npos) {
     run_policy(l);
   } else if (k.name.find("k_reset_obs(") != std::string::npos) {
@@ -555,7 +653,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t) {
   if (g.x == 0 || b.x == 0) return ret(hipErrorInvalidConfiguration);
-  if (lds > (160u << 10)) return ret(hipErrorInvalidValue);
+  if (lds > (64u << 10)) return ret(hipErrorInvalidValue);   // (without the function's attribute raised)
   Launch l = make_launch(f, g, b, args, lds);
   dev().push([l] { run_kernel(l); });
   return hipSuccess;
@@ -801,6 +899,13 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t ex) {
 }
 
 extern "C" long fake_hip_graph_destroys_in_flight() { return n_graph_destroy_in_flight.load(); }
+// Launches run so far of kernels whose name contains `part`.
+extern "C" long fake_hip_launches(const char *part) {
+  std::lock_guard<std::mutex> lk(lmu);
+  long n = 0;
+  for (const auto &k : launches) n += k.first.find(part) != std::string::npos ? k.second : 0;
+  return n;
+}
 extern "C" long fake_hip_live_allocations() {
   std::lock_guard<std::mutex> lk(amu);
   long n = 0;
