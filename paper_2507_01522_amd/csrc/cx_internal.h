@@ -205,6 +205,8 @@ struct LaunchGroup {
   int wpb = 1;             // waves per block: the context's choice, halved until the LDS fits
 };
 
+// Threads of one launch (the runtime's limit).
+constexpr int64_t kMaxLaunchThreads = 0xFFFFFFFF;
 // LDS a block may take for its tables and the two observation stages.
 constexpr size_t kMaxBlockLds = 64 << 10;
 // Per-step tables of a day kept in LDS when a day has at most this many steps:

@@ -233,10 +233,20 @@ __global__ void k_observe(const ClassDev *cls, int64_t n_envs, const double *q, 
 }
 
 hipError_t launch_policy(const PolicyArgs &a, hipStream_t st) {
-  if (a.n <= 0) return hipSuccess;
-  const int64_t blocks = (a.n + 16 * kPolNT - 1) / (16 * kPolNT);
-  hipLaunchKernelGGL(k_policy, dim3((unsigned)blocks), dim3(64 * kPolWaves), kPolLds, st, a);
-  return hipGetLastError();
+  // a launch has fewer than 2^32 threads: 537 M rows each
+  constexpr int64_t kRows = 16 * kPolNT, kMaxRows = kMaxLaunchThreads / (64 * kPolWaves) * kRows;
+  for (int64_t r = 0; r < a.n; r += kMaxRows) {
+    PolicyArgs b = a;
+    b.n = std::min(a.n - r, kMaxRows);
+    b.obs += r * a.in_dim;
+    if (b.act) b.act += r * a.N;
+    if (b.logits) b.logits += r * a.N * a.L1;
+    b.env0 += r;
+    hipLaunchKernelGGL(k_policy, dim3((unsigned)((b.n + kRows - 1) / kRows)), dim3(64 * kPolWaves), kPolLds, st, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_observe(const cx_ctx *ctx, float *obs, hipStream_t st) {

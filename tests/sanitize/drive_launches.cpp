@@ -7,6 +7,7 @@
 //   parts      mixtures of SIMPLE packings, in one launch and past its limits
 //   stage      the observation stage chosen by a launch's size
 //   policy     policy rollouts of every size of the fused kernels, and the two kernels
+//   grids      calls of more than 2^32 threads
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -280,6 +281,20 @@ void policy() {
   for (int ports : {3, 41}) policy_rollouts(Station(ports), 70, 128, "k_policy(");
 }
 
+// A launch has fewer than 2^32 threads.
+void grids() {
+  // the policy's levels for 540 M observations of one port (21 GB)
+  const Station st(1);
+  Context x({&st}, {1});
+  const int in = 10, out = 11, hidden = 32;
+  const std::vector<uint16_t> w1(in * hidden), b1(hidden), w2(hidden * out), b2(out);
+  CK(cx_set_policy(x.c, hidden, w1.data(), b1.data(), w2.data(), b2.data()));
+  const int64_t n = 540'000'001;
+  const Dev obs((size_t)n * in * 4), act((size_t)n);
+  CK(cx_policy_sample(x.c, static_cast<const float *>(obs.p), n, 3, static_cast<uint8_t *>(act.p)));
+  CK(cx_synchronize(x.c));
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -289,6 +304,7 @@ int main(int argc, char **argv) {
   else if (what == "parts") parts();
   else if (what == "stage") stage();
   else if (what == "policy") policy();
+  else if (what == "grids") grids();
   else return 2;
   std::printf("graph execs destroyed with launches in flight: %ld\n", fake_hip_graph_destroys_in_flight());
   std::printf("device allocations left: %ld\n", fake_hip_live_allocations() - live0);

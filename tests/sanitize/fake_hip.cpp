@@ -547,12 +547,14 @@ void run_policy(const Launch &l) {
 
 std::mutex lmu;                       // guards launches
 std::map<std::string, long> launches; // kernels run so far, by name
+bool only_count = false;              // launches are counted, not checked
 
 void run_kernel(const Launch &l) {
   const KernelInfo &k = kernel(l.func);
   {
     std::lock_guard<std::mutex> lk(lmu);
     ++launches[k.name];
+    if (only_count) return;
   }
   if (k.name.find("k_rollout<") != std::string::npos || k.name.find("k_rollout_simple<") != std::string::npos ||
       k.name.find("k_rollout_policy<") != std::string::npos ||
@@ -654,6 +656,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t) {
   if (g.x == 0 || b.x == 0) return ret(hipErrorInvalidConfiguration);
   if (lds > (64u << 10)) return ret(hipErrorInvalidValue);   // (without the function's attribute raised)
+  if ((uint64_t)g.x * b.x >> 32) return ret(hipErrorInvalidConfiguration);
   Launch l = make_launch(f, g, b, args, lds);
   dev().push([l] { run_kernel(l); });
   return hipSuccess;
@@ -899,6 +902,11 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t ex) {
 }
 
 extern "C" long fake_hip_graph_destroys_in_flight() { return n_graph_destroy_in_flight.load(); }
+extern "C" void fake_hip_only_count(bool on) {
+  dev().sync();
+  std::lock_guard<std::mutex> lk(lmu);
+  only_count = on;
+}
 // Launches run so far of kernels whose name contains `part`.
 extern "C" long fake_hip_launches(const char *part) {
   std::lock_guard<std::mutex> lk(lmu);

@@ -13,7 +13,7 @@ def driver(tmp_path_factory):
     return SB.build("asan", str(tmp_path_factory.mktemp("launches")), "drive_launches")
 
 
-@pytest.mark.parametrize("section", ["horizons", "parts", "stage", "policy"])
+@pytest.mark.parametrize("section", ["horizons", "parts", "stage", "policy", "grids"])
 def test_launches(driver, section):
     rc, out = run([driver, section], {"ASAN_OPTIONS": "detect_leaks=1"})
     assert rc == 0 and "DRIVE OK" in out, out[-4000:]
