@@ -1793,7 +1793,10 @@ namespace {
 constexpr int64_t kPartsMaxWaves = 10240;
 bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st, hipError_t *e) {
   if (n_groups < 2 || n_groups > LaunchArgs::kMaxParts || a.per_segment) return false;
-  if (launch_mode(a) == kModeAny && total_waves(groups, n_groups) > kPartsMaxWaves) return false;
+  const int64_t waves = total_waves(groups, n_groups);
+  // (and what the gaps between the parts add must fit one launch too)
+  if (64 * (waves + 8 * n_groups * groups[0].wpb) > kMaxLaunchThreads) return false;
+  if (launch_mode(a) == kModeAny && waves > kPartsMaxWaves) return false;
   LaunchArgs b = a;
   int blocks = 0, dwell = 1, days = 0;
   b.n_parts = 0;

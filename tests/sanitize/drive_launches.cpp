@@ -18,10 +18,12 @@
 #include <vector>
 
 #include "cx.h"
+#include "cx_internal.h"
 
 extern "C" long fake_hip_graph_destroys_in_flight();
 extern "C" long fake_hip_live_allocations();
 extern "C" long fake_hip_launches(const char *part);
+extern "C" void fake_hip_only_count(bool on);
 
 namespace {
 
@@ -293,6 +295,27 @@ void grids() {
   const Dev obs((size_t)n * in * 4), act((size_t)n);
   CK(cx_policy_sample(x.c, static_cast<const float *>(obs.p), n, 3, static_cast<uint8_t *>(act.p)));
   CK(cx_synchronize(x.c));
+  // two packings of 40 M blocks of a wave each, which fit one by one
+  const cx::SegDev segs[2] = {};
+  cx::LaunchArgs a{};
+  a.segs = segs;
+  a.T = 1;
+  a.mode = CX_ACT_RANDOM;
+  a.out_mode = CX_OUT_REWARD;
+  cx::LaunchGroup g[2];
+  for (int i = 0; i < 2; ++i) {
+    g[i].kind = cx::kKindSimple;
+    g[i].pack = cx::pack_id(i ? 64 : 32, 1);
+    g[i].seg_begin = i;
+    g[i].n_segs = 1;
+    g[i].n_blocks = 40'000'000;
+    g[i].wpb = 1;
+  }
+  fake_hip_only_count(true);
+  const long before = fake_hip_launches("k_rollout");
+  REQUIRE(cx::launch_groups(a, g, 2, nullptr) == hipSuccess);
+  fake_hip_only_count(false);
+  REQUIRE(fake_hip_launches("k_rollout") == before + 2);
 }
 
 }  // namespace
