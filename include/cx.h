@@ -376,11 +376,14 @@ cx_status cx_get_tables(const cx_ctx *ctx, int32_t cls, uint32_t *tpois_host, ui
  * block (1..8).  Results do not depend on it beyond FP32 rounding order. */
 cx_status cx_set_packing(cx_ctx *ctx, int32_t cls, int32_t lanes_per_station, int32_t waves_per_block);
 
-/* on = 1: classes without padding slots, with one port maximum and efficiency
- * and one block size per tree level write their observation records through an
- * LDS stage of each block, as 16-byte stores of whole record runs; on = 0 (the
- * default): every lane stores its own values, except in rollouts of at least as
- * many waves as the GPU holds at once, where the stage is always the faster.
+/* on = 1: in every rollout, classes without padding slots, with one port maximum
+ * and efficiency and one block size per tree level write their observation records
+ * through an LDS stage of each block, as 16-byte stores of whole record runs.
+ * on = 0 (the default): every lane stores its own values, except in rollouts of 32
+ * steps or more and 8,192 waves or more (a wave holds 64 / lanes_per_station
+ * stations), where the stage is the faster; several such classes' packings share
+ * one launch without it up to 10,240 waves.  One step of several packings shares
+ * one launch without the stage whatever on is.
  * The records are bit for bit the same either way; which is faster depends on
  * the launch.  CX_E_INVALID unless on is 0 or 1. */
 cx_status cx_set_obs_stage(cx_ctx *ctx, int32_t on);

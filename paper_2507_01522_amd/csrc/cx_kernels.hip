@@ -1804,6 +1804,8 @@ bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, 
     const LaunchGroup &g = groups[i];
     if ((g.kind != kKindSimple && g.kind != kKindSimpleStaged) || pack_per_lane(g.pack) > 2 || g.wpb != groups[0].wpb)
       return false;
+    // a caller that asks for the stage gets it in every rollout that records observations
+    if (g.kind == kKindSimpleStaged && launch_mode(a) == kModeAny) return false;
     if (g.n_blocks <= 0) continue;
     blocks = (blocks + 7) & ~7;
     b.part[b.n_parts++] = {blocks, g.n_blocks, g.seg_begin, g.n_segs,

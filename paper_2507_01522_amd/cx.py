@@ -301,9 +301,9 @@ class Env:
         check(lib().cx_set_packing(self.h, cls, lanes, waves_per_block))
 
     def set_obs_stage(self, on: bool):
-        """Observations through each block's LDS stage (SIMPLE classes)
-        or stored lane by lane (large launches take the stage in any case);
-        same records."""
+        """Rollouts' observations through each block's LDS stage (SIMPLE
+        classes) or stored lane by lane (large launches take the stage in any
+        case); same records."""
         check(lib().cx_set_obs_stage(self.h, 1 if on else 0))
 
     def autotune(self, T_probe: int = 32, cache_path: Optional[str] = None):

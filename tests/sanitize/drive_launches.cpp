@@ -190,6 +190,16 @@ void parts() {
         CK(cx_rollout(x.c, T, CX_ACT_EXTERNAL, CX_OUT_FULL, static_cast<uint8_t *>(act_in.p), &tr.t));
       }
       REQUIRE(x.count("k_rollout_parts<2>", [&] { return cx_step_ex(x.c, CX_ACT_MAX, nullptr, &tr.t); }) == 1);
+      // the stage asked for: rollouts that record observations take it, each packing
+      // its own kernel; other calls have none
+      CK(cx_set_obs_stage(x.c, 1));
+      for (int T : {2, 24, 40}) {
+        REQUIRE(x.count("k_rollout_parts<", [&] { return x.rollout(T, CX_OUT_FULL, tr); }) == 0);
+        REQUIRE(x.count(", true, 0>", [&] { return x.rollout(T, CX_OUT_FULL, tr); }) >= 5);   // k_rollout_simple<., ., true, 0>
+        REQUIRE(x.count("k_rollout_parts<1>", [&] { return x.rollout(T, CX_OUT_ACT_REWARD, tr); }) == 1);
+      }
+      REQUIRE(x.count("k_rollout_parts<2>", [&] { return x.rollout(1, CX_OUT_FULL, tr); }) == 1);
+      CK(cx_set_obs_stage(x.c, 0));
     }
   }
   // every record: one launch up to 10,240 waves, past them a graph; one step and
