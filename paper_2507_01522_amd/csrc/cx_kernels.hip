@@ -902,21 +902,35 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
       // the levels below (a scaled block contributes its limit); so each level
       // is checked when its block size is reached.  A slot's final factor is
       // the product of the factors of the nodes on its path.
-      // Blocks smaller than a lane's P slots (rare: such levels take a path of
-      // their own) have a factor per slot, larger ones one factor for the lane.
+      // Blocks smaller than a lane's P slots (rare: such trees take a path of
+      // their own) have a factor per slot, which the larger ones' then multiply, as
+      // with one slot per lane (a slot's factors from the deepest node up); without
+      // them all factors are the lane's.
       float F[P], r;
-#pragma unroll
-      for (int j = 0; j < P; ++j) F[j] = 1.0f;
       auto limit = [&](float &load, float &f, float c) {
         const bool over = load > c;
         f = over ? f * (c * frcp(load)) : f;
         load = over ? c : load;
+      };
+      // the levels of blocks of P slots and more; factor(c): one of them, of limit c
+      auto climb = [&](auto factor) {
+#pragma unroll
+        for (int k = 0; k < LOGL; ++k) {
+          if ((levels >> (k + LOGP)) & 1u) {  // a level of blocks of P 2^k slots (wave-uniform)
+            // a real (scalar) branch: most sizes have no level, and computing the
+            // check for every one and selecting would cost more than it saves
+            asm volatile("");
+            factor(blk_cap[k + LOGP]);
+          }
+          r = xsum_k<L>(r, k);
+        }
       };
       if (P > 1 && (levels & ((1u << LOGP) - 1u))) {
         float v[P];
 #pragma unroll
         for (int j = 0; j < P; ++j) {
           v[j] = pw[j];
+          F[j] = 1.0f;
           if (levels & 1u) limit(v[j], F[j], blk_cap[0]);
         }
         if constexpr (P == 2) {
@@ -933,30 +947,27 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
         } else {
           r = v[0];
         }
-      } else if constexpr (P == 1) {
-        r = pw[0];
-      } else if constexpr (P == 2) {
-        r = pw[0] + pw[1];
-      } else {
-        r = (pw[0] + pw[1]) + (pw[2] + pw[3]);
-      }
-      float f = 1.0f;
+        climb([&](float c) {
+          float g = 1.0f;
+          limit(r, g, c);
 #pragma unroll
-      for (int k = 0; k < LOGL; ++k) {
-        if ((levels >> (k + LOGP)) & 1u) {  // a level of blocks of P 2^k slots (wave-uniform)
-          // a real (scalar) branch: most sizes have no level, and computing the
-          // check for every one and selecting would cost more than it saves
-          asm volatile("");
-          limit(r, f, blk_cap[k + LOGP]);
-        }
-        r = xsum_k<L>(r, k);
+          for (int j = 0; j < P; ++j) F[j] *= g;
+        });
+      } else {
+        if constexpr (P == 1) r = pw[0];
+        if constexpr (P == 2) r = pw[0] + pw[1];
+        if constexpr (P == 4) r = (pw[0] + pw[1]) + (pw[2] + pw[3]);
+        float f = 1.0f;
+        climb([&](float c) { limit(r, f, c); });
+#pragma unroll
+        for (int j = 0; j < P; ++j) F[j] = f;
       }
       // the root: the whole station, delivered energy its scaled load (App. A.3)
       const float tot = r;
       const bool over = tot > c_root;
       const float fr = over ? c_root * frcp(tot) : 1.0f;
 #pragma unroll
-      for (int j = 0; j < P; ++j) pw[j] *= (P == 1 ? f : F[j] * f) * fr;
+      for (int j = 0; j < P; ++j) pw[j] *= F[j] * fr;
       e_net = dt * (over ? c_root : tot);
       e_grid = e_net * inv_eta_u;
     } else {
