@@ -328,7 +328,7 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 // each wave reads its weight fragments from device memory (L2) straight into
 // the matrix-core operands.  K1 (K-steps of 32 features) and HP (K-steps of 32
 // hidden units: 2, 4 or 8) are the class's and the policy's sizes rounded up;
-// the weights are padded with zeros, so such steps add exact zeros.
+// the second product's weights of the padding are zeros, so it adds exact zeros.
 // LDS: hb (HP x 2 hidden-unit fragments, over the stage once it has been
 // read), xb (the observations in BF16, 256 features per env, zero past in_dim,
 // rows 33 fragments apart so that the 16 envs of a tile fall in different

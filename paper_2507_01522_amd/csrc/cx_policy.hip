@@ -30,8 +30,9 @@ struct PolicyRt {
   int hidden = 0, in_dim = 0, N = 0, L1 = 0;
   int K1 = 0, HP = 0, R = 0, G = 0;
   // weights in fragment order and FP32 biases, padded to the largest sizes
-  // (zeros; -inf for the biases of levels past the class's): W1^T [16 tiles][8
-  // K-steps][64], b1 [256], W2^T [G][3][8][64], b2 [G][3][16]
+  // (features and W2 with zeros, hidden units with copies of the first, the biases
+  // of levels past the class's -inf): W1^T [16 tiles][8 K-steps][64], b1 [256], W2^T
+  // [G][3][8][64], b2 [G][3][16]
   void *mem = nullptr;
   const u32x4 *w1p = nullptr;
   const float *b1p = nullptr;
@@ -549,19 +550,23 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
     return fail_status(CX_E_INVALID, "cx_set_policy: observations longer than 256 (more than 42 ports)");
   if (L1 > 4 * kPolR) return fail_status(CX_E_INVALID, "cx_set_policy: at most 11 levels per port");
   const int K1 = (in_dim + 31) / 32, HP = hidden / 32, R = (L1 + 3) / 4, G = (N + 3) / 4;
+  const int HP_kernel = HP <= 2 ? 2 : HP <= 4 ? 4 : 8;   // what the kernels are built for
   const int out_dim = N * L1;
   // W1^T fragments: tile m (hidden 16m..16m+15), K-step s at (m * 8 + s), lane l
-  // -> hidden 16m + l % 16, features 32s + 8 (l / 16) + j
+  // -> hidden 16m + l % 16, features 32s + 8 (l / 16) + j.  Hidden units past the
+  // policy's are copies of its first, with weights 0 in W2: zeros would make 0 x inf
+  // of an infinite observation, whose own hidden units are +-1.
   std::vector<uint16_t> w1p((size_t)2 * kPolHP * kPolK1 * 64 * 8, 0);
-  for (int m = 0; m < 2 * HP; ++m)
+  for (int m = 0; m < 2 * HP_kernel; ++m)
     for (int s = 0; s < K1; ++s)
       for (int l = 0; l < 64; ++l)
         for (int j = 0; j < 8; ++j) {
           const int f = 32 * s + 8 * (l >> 4) + j, hu = 16 * m + (l & 15);
-          if (f < in_dim) w1p[(((size_t)m * kPolK1 + s) * 64 + l) * 8 + j] = w1[(size_t)f * hidden + hu];
+          if (f < in_dim)
+            w1p[(((size_t)m * kPolK1 + s) * 64 + l) * 8 + j] = w1[(size_t)f * hidden + (hu < hidden ? hu : 0)];
         }
   std::vector<float> b1p((size_t)32 * kPolHP, 0.f);
-  for (int j = 0; j < hidden; ++j) b1p[j] = (float)bf16_to_double(b1[j]);
+  for (int j = 0; j < 32 * HP_kernel; ++j) b1p[j] = (float)bf16_to_double(b1[j < hidden ? j : 0]);
   // W2^T fragments: tile (grp, r), K-step s at ((grp * 3 + r) * 8 + s), lane l ->
   // row l % 16 = port 4 grp + (l % 16) / 4, level 4 r + l % 4; slot j -> hidden
   // unit in the order the first product leaves them in a lane.  Levels past the
