@@ -184,7 +184,7 @@ struct LaunchArgs {
     const u32x4 *w1f;     // [16][8][64] fragments of W1^T
     const float *b1;      // [256]
     const u32x4 *w2f;     // [G][3][8][64] fragments of W2^T
-    const float *b2f;     // [G][3][16]; -inf for levels past the class's
+    const float *b2f;     // [G][3][16]; the lowest float for levels past the class's
     int32_t in_dim, K1, HP, R, G, L1;
     int32_t hb_off, xb_off, act_off;  // LDS byte offsets
   } pol;
@@ -319,7 +319,7 @@ struct PolicyArgs {
   const u32x4 *w1f;  // [16][8][64] fragments of W1^T
   const float *b1;   // [256]
   const u32x4 *w2f;  // [G][3][8][64] fragments of W2^T
-  const float *b2f;  // [G][3][16]; -inf for levels past the class's
+  const float *b2f;  // [G][3][16]; the lowest float for levels past the class's
   // what the launch writes: one of the two
   uint8_t *act;      // [n][N] or NULL
   float *logits;     // [n][N * L1] or NULL

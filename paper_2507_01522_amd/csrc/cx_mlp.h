@@ -69,10 +69,12 @@ __device__ __forceinline__ uint32_t draw_word(U4 w, int port) {
 }
 
 // The level drawn from softmax of a port's logits (level 4 r + i in c[r][i],
-// L1 levels; the levels past them have bias -inf and weights 0, so their
-// logits are -inf and their softmax weights exactly 0): the first level whose
+// L1 levels; the levels past them have the lowest float for a bias and weights 0,
+// so their softmax weights are exactly 0): the first level whose
 // cumulative softmax weight exceeds u times the total, i.e. the inverse of the
-// distribution function at u.  The weights are 2^(z log2 e - zmax log2 e) (one
+// distribution function at u (the last level where all of a port's logits are
+// below -2.36e38 and the weights overflow; level 0 where a logit is NaN or none is
+// finite).  The weights are 2^(z log2 e - zmax log2 e) (one
 // fused multiply-add each); the running sums kept as they are formed are the
 // cumulative weights.  Straight-line code, no test per level: with the levels
 // in use selected one by one the draw took 110 vector and 35 scalar

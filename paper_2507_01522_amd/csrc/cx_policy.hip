@@ -31,8 +31,8 @@ struct PolicyRt {
   int K1 = 0, HP = 0, R = 0, G = 0;
   // weights in fragment order and FP32 biases, padded to the largest sizes
   // (features and W2 with zeros, hidden units with copies of the first, the biases
-  // of levels past the class's -inf): W1^T [16 tiles][8 K-steps][64], b1 [256], W2^T
-  // [G][3][8][64], b2 [G][3][16]
+  // of levels past the class's with the lowest float): W1^T [16 tiles][8 K-steps][64],
+  // b1 [256], W2^T [G][3][8][64], b2 [G][3][16]
   void *mem = nullptr;
   const u32x4 *w1p = nullptr;
   const float *b1p = nullptr;
@@ -570,7 +570,8 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
   // W2^T fragments: tile (grp, r), K-step s at ((grp * 3 + r) * 8 + s), lane l ->
   // row l % 16 = port 4 grp + (l % 16) / 4, level 4 r + l % 4; slot j -> hidden
   // unit in the order the first product leaves them in a lane.  Levels past the
-  // class's have weights 0 and bias -inf: the draw never takes them.
+  // class's have weights 0 and the lowest bias, whose softmax weight is 0 (not -inf:
+  // beside a port whose own logits are all that low, it would be the NaN of inf - inf).
   std::vector<uint16_t> w2p((size_t)G * kPolR * kPolHP * 64 * 8, 0);
   std::vector<float> b2p((size_t)G * kPolR * 16, 0.f);
   for (int grp = 0; grp < G; ++grp)
@@ -578,7 +579,7 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
       const int tile = grp * kPolR + r;
       for (int row = 0; row < 16; ++row) {
         const int port = 4 * grp + (row >> 2), lev = 4 * r + (row & 3);
-        if (lev >= L1) b2p[(size_t)tile * 16 + row] = -std::numeric_limits<float>::infinity();
+        if (lev >= L1) b2p[(size_t)tile * 16 + row] = -std::numeric_limits<float>::max();
         else if (port < N) b2p[(size_t)tile * 16 + row] = (float)bf16_to_double(b2[port * L1 + lev]);
       }
       for (int s = 0; s < HP; ++s)

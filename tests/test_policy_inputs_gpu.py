@@ -44,3 +44,26 @@ def test_infinite_observation(cxm, hidden, ports):
     assert (h.abs() == 1).all()
     err = (env.policy_logits(obs.cuda()).cpu().double() - (h @ w2 + b2)).abs()
     assert (err <= 1.6e-5 * (h.abs() @ w2.abs() + b2.abs())).all()
+
+
+@pytest.mark.parametrize("bias", ["lowest", "-inf"])
+@pytest.mark.parametrize("n_levels", [1, 3, 6, 10, 11])
+def test_masked_port(cxm, n_levels, bias):
+    """A port whose every level has the lowest finite bias: all of its weights
+    overflow alike, and the draw takes the last level, as without padding levels (11
+    levels and 0).  With biases of -inf no weight is a number, and it takes level 0.
+    The other ports draw what they draw without the mask."""
+    spec = W.fanout4_tree(16, 2).replace(n_levels=n_levels)
+    w1, b1, w2, b2 = W.policy_weights(16, hidden=64, n_levels=n_levels, std=0.2, seed=7)
+    env = cxm.Env(spec, n_envs=1, seed=3)
+    obs = torch.rand(200, spec.obs_dim, generator=torch.Generator().manual_seed(5)).cuda()
+    env.set_policy(64, (w1, b1, w2, b2))
+    free = env.policy_sample(obs, 9).cpu().numpy()
+    masked = [2, 7]
+    b2 = b2.reshape(16, n_levels + 1).copy()
+    b2[masked] = {"lowest": 0xFF7F, "-inf": 0xFF80}[bias]   # in BF16
+    env.set_policy(64, (w1, b1, w2, b2.reshape(-1)))
+    got = env.policy_sample(obs, 9).cpu().numpy()
+    assert (got[:, masked] == (n_levels if bias == "lowest" else 0)).all()
+    rest = np.setdiff1d(np.arange(16), masked)
+    assert np.array_equal(got[:, rest], free[:, rest])
