@@ -155,7 +155,6 @@ struct LaunchArgs {
   int32_t T, t_day0;
   uint32_t g0;
   int32_t mode, out_mode;
-  int32_t lds_tdwell;   // 1: stage the stay thresholds in LDS (set per launch group)
   // observation records staged in LDS (set per launch group): byte offset of
   // the two stage buffers in the dynamic LDS and floats per buffer (0: each
   // lane stores its observation values to HBM itself)
@@ -185,7 +184,7 @@ struct LaunchArgs {
     const float *b1;      // [256]
     const u32x4 *w2f;     // [G][3][8][64] fragments of W2^T
     const float *b2f;     // [G][3][16]; the lowest float for levels past the class's
-    int32_t in_dim, K1, HP, R, G, L1;
+    int32_t in_dim, HP, G, L1;   // HP: chooses the kernel
     int32_t hb_off, xb_off, act_off;  // LDS byte offsets
   } pol;
 };
@@ -313,7 +312,7 @@ struct RolloutGraphs {
 struct PolicyArgs {
   const float *obs;  // [n][in_dim]
   int64_t n;
-  int32_t in_dim, K1, HP, R, G, N, L1;
+  int32_t in_dim, K1, HP, G, N, L1;
   uint32_t g;        // global step of the draws
   // fragments padded to the largest sizes (as for the fused rollout)
   const u32x4 *w1f;  // [16][8][64] fragments of W1^T
@@ -330,8 +329,8 @@ struct PolicyArgs {
 // Host-side launchers (defined in cx_kernels.hip).  `a.segs` is the base of
 // the device segment table; each group launches with its own slice.
 hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st);
-hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, int hp, bool held,
-                                 int n_blocks, size_t lds, hipStream_t st);
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, bool held, int n_blocks,
+                                 size_t lds, hipStream_t st);
 hipError_t graph_rollout(RolloutGraphs &gs, const LaunchArgs &a, const LaunchGroup *groups, int n_groups,
                          hipStream_t st);
 void graph_destroy(RolloutGraphs &gs);

@@ -1526,7 +1526,7 @@ __device__ __forceinline__ int xcd_block(int i, int n) {
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD = false, int MODE = kModeAny>
 __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *segs, int n_segs, int b) {
   constexpr bool POL = HPOL > 0;
-  extern __shared__ uint32_t lds_tdwell[];
+  extern __shared__ uint32_t block_lds[];
   CX_KONST SegDev *const seg0 = konst(segs);
   int lo = 0, hi = n_segs - 1;
   while (lo < hi) {
@@ -1552,9 +1552,9 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   const lds_u32x4 *exo_tp = nullptr;
   const int steps = C.steps_ep;
   if (MODE != kModeStep && (HELD ? a.day_off > 0 : !POL) && steps <= kLdsExoSteps && dy.T >= kLdsExoMinT) {
-    exo_tp = (const lds_u32x4 *)((lds_char *)lds_tdwell + a.day_off);
+    exo_tp = (const lds_u32x4 *)((lds_char *)block_lds + a.day_off);
   }
-  lds_u32 *const car_tab = EXT ? (lds_u32 *)((lds_char *)lds_tdwell + a.car_off) : nullptr;
+  lds_u32 *const car_tab = EXT ? (lds_u32 *)((lds_char *)block_lds + a.car_off) : nullptr;
   // every wave of the block helps load them, those past the last env too; the
   // others ask for their state first, so that a short launch waits once (one step
   // of 65,536 uneven stations 50.3 -> 46.5 us) and nothing is still on its way
@@ -1562,7 +1562,7 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   // the return's load: a day of 64 16-port stations 226 -> 210 us)
   const auto fill_tables = [&] {
     const int n_stay = 1 << C.dwell_log2;
-    for (int i = threadIdx.x; i < n_stay; i += blockDim.x) lds_tdwell[i] = gld(C.tdwell, i);
+    for (int i = threadIdx.x; i < n_stay; i += blockDim.x) block_lds[i] = gld(C.tdwell, i);
     if (exo_tp) {
       lds_u32x4 *tp = const_cast<lds_u32x4 *>(exo_tp);
       lds_float *pr = reinterpret_cast<lds_float *>(tp + steps);
@@ -1588,10 +1588,10 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
     return;
   }
   const int n_run = min(W, n_groups - g_blk0);  // waves of the block that run
-  lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)lds_tdwell + a.stage_off) : nullptr;
+  lds_float *stage = a.stage_floats > 0 ? (lds_float *)((lds_char *)block_lds + a.stage_off) : nullptr;
   run_group<L, P, SIMPLE, EXT, STAGE, HPOL, HELD, MODE>(
-      fill_tables, sgp, dy, group, (const lds_u32 *)lds_tdwell, exo_tp, car_tab, stage, W == 1 ? 0 : a.stage_floats,
-      g_blk0, n_run, &a.pol, (lds_char *)lds_tdwell);
+      fill_tables, sgp, dy, group, (const lds_u32 *)block_lds, exo_tp, car_tab, stage, W == 1 ? 0 : a.stage_floats,
+      g_blk0, n_run, &a.pol, (lds_char *)block_lds);
 }
 
 // Waves per SIMD extended classes are held to.  One slot per lane: five, 96
@@ -1771,8 +1771,6 @@ LaunchArgs group_args(const LaunchArgs &a, const LaunchGroup &g, int kind, int64
   LaunchArgs b = a;
   b.segs = a.segs + g.seg_begin;
   b.n_segs = g.n_segs;
-  b.lds_tdwell = 1;  // staging the table costs one load per thread and beats device-memory
-                     // bisection even for one-step launches
   const bool stages =
       kind == kKindSimpleStaged && (a.per_segment || (a.out_mode == CX_OUT_FULL && a.obs != nullptr));
   const LdsPlan p = lds_plan(g.wpb, g.pack, g.max_obs_dim, g.max_dwell_log2, g.max_day_steps, stages,
@@ -1829,7 +1827,6 @@ bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, 
     *e = hipSuccess;
     return true;
   }
-  b.lds_tdwell = 1;
   const LdsPlan p = lds_plan(groups[0].wpb, groups[0].pack, 0, dwell, a.T >= kLdsExoMinT ? days : 0, false, false);
   b.day_off = p.day_off;
   b.pace = 1;
@@ -1864,12 +1861,13 @@ hipError_t launch_groups(const LaunchArgs &a, const LaunchGroup *groups, int n_g
 
 // The fused policy rollout of one class: stations of 8 lanes (8, 16 or 32
 // slots), 4 waves per block (32 stations, two 16-env tiles of the MLP), or of 16
-// lanes (16 stations, one tile).  hp:
+// lanes (16 stations, one tile).  a.pol.HP:
 // K-steps of 32 hidden units; the kernels are built for 2, 4 and 8 (a policy
 // of 64 hidden units does a quarter of the matrix work of one of 256).
-hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, int hp, bool held,
-                                 int n_blocks, size_t lds, hipStream_t st) {
+hipError_t launch_policy_rollout(const LaunchArgs &a, bool simple, int lanes, int per_lane, bool held, int n_blocks,
+                                 size_t lds, hipStream_t st) {
   if (n_blocks <= 0) return hipSuccess;
+  const int hp = a.pol.HP;
   // stations of 8 lanes with 1, 2 and 4 slots per lane, the same with their
   // weights held, and of 16 lanes, always held
 #define CX_POL(K, L, P, H) {&K<L, P, 2, H>, &K<L, P, 4, H>, &K<L, P, 8, H>}

@@ -28,7 +28,7 @@ namespace cx {
 
 struct PolicyRt {
   int hidden = 0, in_dim = 0, N = 0, L1 = 0;
-  int K1 = 0, HP = 0, R = 0, G = 0;
+  int K1 = 0, HP = 0, G = 0;
   // weights in fragment order and FP32 biases, padded to the largest sizes
   // (features and W2 with zeros, hidden units with copies of the first, the biases
   // of levels past the class's with the lowest float): W1^T [16 tiles][8 K-steps][64],
@@ -270,7 +270,7 @@ PolicyArgs policy_args(const cx_ctx *ctx, const float *obs, int64_t n) {
   PolicyArgs a{};
   a.obs = obs;
   a.n = n;
-  a.in_dim = p.in_dim; a.K1 = p.K1; a.HP = p.HP; a.R = p.R; a.G = p.G; a.N = p.N; a.L1 = p.L1;
+  a.in_dim = p.in_dim; a.K1 = p.K1; a.HP = p.HP; a.G = p.G; a.N = p.N; a.L1 = p.L1;
   a.w1f = p.w1p; a.b1 = p.b1p; a.w2f = p.w2p; a.b2f = p.b2p;
   a.seed = ctx->seed;
   a.env0 = ctx->classes[0].env_begin;
@@ -474,7 +474,6 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.act = ret_act ? out->actions : nullptr;
   a.reward = out ? out->reward : nullptr;
   a.done = out ? out->done : nullptr;
-  a.lds_tdwell = 1;
   a.stage_off = stage_off;
   a.stage_floats = stage_floats;
   // launches with held weights keep the day's tables in LDS too, where they fit:
@@ -491,12 +490,10 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.pol.w2f = p.w2p;
   a.pol.b2f = p.b2p;
   a.pol.in_dim = p.in_dim;
-  a.pol.K1 = p.K1;
   a.pol.HP = p.HP;
-  a.pol.R = p.R;
   a.pol.G = p.G;
   a.pol.L1 = p.L1;
-  if ((e = launch_policy_rollout(a, c.host_view.kind == kKindSimple, p.lanes, c.comp.S / p.lanes, p.HP, held,
+  if ((e = launch_policy_rollout(a, c.host_view.kind == kKindSimple, p.lanes, c.comp.S / p.lanes, held,
                                  p.n_blocks, lds, ctx->stream)) != hipSuccess)
     return hip_fail(ctx, e, "policy rollout kernel");
   advance_clock(ctx, T);
@@ -549,7 +546,7 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
   if (in_dim > 32 * kPolK1)
     return fail_status(CX_E_INVALID, "cx_set_policy: observations longer than 256 (more than 42 ports)");
   if (L1 > 4 * kPolR) return fail_status(CX_E_INVALID, "cx_set_policy: at most 11 levels per port");
-  const int K1 = (in_dim + 31) / 32, HP = hidden / 32, R = (L1 + 3) / 4, G = (N + 3) / 4;
+  const int K1 = (in_dim + 31) / 32, HP = hidden / 32, G = (N + 3) / 4;
   const int HP_kernel = HP <= 2 ? 2 : HP <= 4 ? 4 : 8;   // what the kernels are built for
   const int out_dim = N * L1;
   // W1^T fragments: tile m (hidden 16m..16m+15), K-step s at (m * 8 + s), lane l
@@ -617,7 +614,7 @@ cx_status cx_set_policy(cx_ctx *ctx, int32_t hidden, const uint16_t *w1, const u
   PolicyRt *old = ctx->policy;
   PolicyRt *p = new PolicyRt();
   p->hidden = hidden; p->in_dim = in_dim; p->N = N; p->L1 = L1;
-  p->K1 = K1; p->HP = HP; p->R = R; p->G = G;
+  p->K1 = K1; p->HP = HP; p->G = G;
   p->mem = mem;
   p->w1p = reinterpret_cast<const u32x4 *>(b);
   p->b1p = reinterpret_cast<const float *>(b + o_b1p);
