@@ -419,9 +419,10 @@ __device__ __forceinline__ void policy_phase(const LaunchArgs::Pol &pl, const ld
 // or that it is one step (the loop, the draws ahead and the barrier fold away).
 // One kernel for all held the registers of the longest: one step of a SIMPLE class
 // needs 44-54 VGPRs (eight waves per SIMD), a rollout without observations 60-80.
-// One step of 65,536 uneven stations 46.3 -> 38.0 us, of V2G ones 36.8 -> 32.0, of
-// 64 7.0 -> 6.8.  144 steps, rewards only: uneven 933 -> 833 us, V2G 820 -> 663,
-// table-driven 768 -> 611; 288 steps of 20,011 uneven 550 -> 500.
+// One step of 65,536 uneven stations 48.8 -> 44.5 us (46.3 -> 38.0 where state and
+// records stay in the caches), of 64 stations 5.53 -> 5.22; of V2G ones, in the
+// caches, 36.8 -> 32.0.  144 steps, rewards only: uneven 933 -> 833 us, V2G 820 -> 663,
+// table-driven 768 -> 611; 288 steps of 20,011 uneven 526 -> 472.
 enum { kModeAny = 0, kModeNoObs = 1, kModeStep = 2 };
 template <int L, int P, bool SIMPLE, bool EXT, bool STAGE, int HPOL, bool HELD, int MODE, class Fill>
 __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *sgp, const Dyn &dy, int group,
@@ -1557,7 +1558,7 @@ __device__ __forceinline__ void rollout_body(const LaunchArgs &a, const SegDev *
   lds_u32 *const car_tab = EXT ? (lds_u32 *)((lds_char *)block_lds + a.car_off) : nullptr;
   // every wave of the block helps load them, those past the last env too; the
   // others ask for their state first, so that a short launch waits once (one step
-  // of 65,536 uneven stations 50.3 -> 46.5 us) and nothing is still on its way
+  // of 65,536 uneven stations 54.4 -> 48.8 us) and nothing is still on its way
   // when the steps begin (a step had waited for its records at the first use of
   // the return's load: a day of 64 16-port stations 226 -> 210 us)
   const auto fill_tables = [&] {
@@ -1607,9 +1608,11 @@ __attribute__((amdgpu_waves_per_eu(EXT ? ext_waves(P, MODE) : 1))) void k_rollou
   rollout_body<L, P, SIMPLE, EXT, STAGE, 0, false, MODE>(a, a.segs, a.n_segs, xcd_block(blockIdx.x, gridDim.x));
 }
 
-// SIMPLE classes of 1 or 2 slots per lane: 64-75 VGPRs at one slot per lane (six to
-// eight waves per SIMD), 78-91 at two (five or six), with their constants in
-// scalar registers and nothing spilled; the bound keeps every one at five waves at
+// SIMPLE classes of 1 or 2 slots per lane, with observation records: 64-75 VGPRs at
+// one slot per lane (six to eight waves per SIMD), 80-91 at two (five or six), with
+// their constants in scalar registers and no vector register spilled (of the scalar
+// ones, to lanes of a vector register: 2-6 with the stage, 14 at 64 lanes and two
+// slots, 2 there without it); the bound keeps every one at five waves at
 // least.  Every record, 65,536 uneven stations x 288 steps: 3.74
 // ms with the constants in vector registers (96, some spilled), 3.48 now; rewards
 // only 2.25 and 1.60.
@@ -1627,9 +1630,11 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeNoObs ? 6 : CX_SIMPLE_WAVES))) v
 // the weights' way from L2 bounds it (304 KB a block and step at 32 ports and 256
 // hidden units: 16 of the 31 us a step of 65,536 stations takes).  HELD: one
 // block per CU with the weights in registers and the day's tables in LDS, so
-// that no step loads anything from device memory; it is bound by the length of
-// one step's chain (10 DC + 6 AC ports, 256 hidden units, every record, 4,096 x
-// 288 steps: 1,770 -> 804 us, 2.8 us a step).
+// that a step loads nothing from device memory (but the second product's weights at
+// 32 slots and 256 hidden units, which come round a ring, and the tables of a day
+// of more than 512 steps, of a call of fewer than 32 or where LDS is short); it is
+// bound by the length of one step's chain (10 DC + 6 AC ports, 256 hidden units,
+// every record, 4,096 x 288 steps: 1,770 -> 766 us, 2.65 us a step).
 template <int L, int P, int HP, bool HELD>
 __global__ __launch_bounds__(64 * kPolRolloutWaves)
 __attribute__((amdgpu_waves_per_eu(HELD ? 1 : 3))) void k_rollout_policy(LaunchArgs a) {
@@ -1647,7 +1652,8 @@ __attribute__((amdgpu_waves_per_eu(HELD ? 1 : P == 4 ? 2 : 3))) void k_rollout_p
 // Several groups of SIMPLE classes in one launch (a.part: each group's blocks, at
 // a multiple of 8 so that they are dealt to the XCDs as in a launch of their
 // own).  For launches too short to fill the chip one group at a time: one step
-// of 65,536 uneven stations took five kernels one after the other (74 us, now 38).
+// of 65,536 uneven stations takes 68.4 us as five kernels one after the other, so
+// 40.3 (65.6 and 37.3 where state and records stay in the caches).
 template <int MODE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE == kModeNoObs ? 6 : 1))) void k_rollout_parts(LaunchArgs a) {
   int i = 0;
@@ -1798,7 +1804,7 @@ namespace {
 // launch against the graph: 2,000 0.49 (0.30) / 0.80 (0.54) ms, 10,000 0.59 (0.35)
 // / 0.87 (0.53), 20,000 (8,400 waves) 1.16 (0.57) / 1.20 (0.60), 28,000 (11,700)
 // 1.58 (0.70) / 1.52 (0.73), 65,536 (27,300) 3.57 (1.46) / 3.55 (1.51).  One step:
-// 300 stations 35 -> 8.5 us, 65,536 74 -> 38.  False: not such a launch.
+// 300 stations 31.1 -> 8.3 us, 65,536 68.4 -> 40.3.  False: not such a launch.
 constexpr int64_t kPartsMaxWaves = 10240;
 bool launch_parts(const LaunchArgs &a, const LaunchGroup *groups, int n_groups, hipStream_t st, hipError_t *e) {
   if (n_groups < 2 || n_groups > LaunchArgs::kMaxParts || a.per_segment) return false;

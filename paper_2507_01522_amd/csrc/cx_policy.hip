@@ -476,8 +476,9 @@ cx_status fused_rollout(cx_ctx *ctx, int32_t T, cx_out_mode out_mode, const cx_t
   a.done = out ? out->done : nullptr;
   a.stage_off = stage_off;
   a.stage_floats = stage_floats;
-  // launches with held weights keep the day's tables in LDS too, where they fit:
-  // their steps then load nothing from device memory and wait for no record
+  // launches with held weights keep the day's tables in LDS too, where they fit: a
+  // step with all weights held then loads nothing from device memory and waits for no
+  // record
   const size_t days = (size_t)ctx->steps_ep * 20;
   if (held && ctx->steps_ep <= kLdsExoSteps && lds + days <= kMaxBlockLds) {
     a.day_off = (int32_t)lds;

@@ -334,8 +334,8 @@ static void poisson_rows(const double *mean, int n, uint32_t *rows) {
 // ceil(2^32 F) is wanted, so erfc itself is called once for a run of
 // neighbouring k and the others take the Taylor series of erfc around the run's
 // middle: with |h| <= 1/16 and terms up to h^9 the remainder is below
-// 1.09 sqrt(2^9 9!) / 10! h^10 / sqrt(pi) < 2e-15 (Cramer's bound on the
-// Hermite functions), 1e-5 of a threshold.  Where 2^32 F comes out within 1e-3
+// 1.09 sqrt(2^9 9!) / 10! h^10 / sqrt(pi) < 2.2e-15 (Cramer's bound on the
+// Hermite functions), below 1e-5 of a threshold.  Where 2^32 F comes out within 1e-3
 // of a whole number the call decides, so every entry is the one that erfc gives.
 // 1023 entries at the default dwell: 40 us with a call each, 13 us so.
 static void dwell_thresholds(const SpecCopy &sc, uint32_t *t) {
