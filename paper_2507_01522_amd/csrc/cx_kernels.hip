@@ -661,6 +661,17 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
 
   // every lane's P slots hold P adjacent ports (no padding slots)
   [[maybe_unused]] const bool adjacent = NOPAD || S == N;
+  // With four slots per lane a class with padding slots stores the observations of
+  // the lanes whose ports are adjacent at once too, the others' one by one: stored one
+  // by one from all lanes, 16 bytes apart, 96 steps of 20,000 31-port stations at 8
+  // lanes took 734 us, so 546 (583 with slots L apart).  (With two slots, 8 bytes
+  // apart, the test costs what it saves.)
+  constexpr bool SOME = P == 4 && !NOPAD && !POL;
+  [[maybe_unused]] bool whole = SOME && !adjacent;
+  if constexpr (SOME) {
+#pragma unroll
+    for (int j = 0; j < P; ++j) whole = whole && port[j] >= 0 && port[j] == port[0] + j;
+  }
   // (from LDS: a load from device memory would wait for the records in flight)
   [[maybe_unused]] auto car_model = [&](uint32_t w) {
     int m = 0;
@@ -1287,9 +1298,8 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
                         : 0;
     if (active) {
       if (MODE != kModeNoObs && (POL || (flags & kWObs))) {
-        // put(feature offset, port's offset, value) writes one value; with every
-        // lane's ports adjacent (slot s = port s), put_lane writes a lane's P values
-        // of a feature at once
+        // put(feature offset, port's offset, value) writes one value; put_lane the
+        // P values of a feature of a lane whose ports are adjacent at once
         int n_occ = 0;
         if constexpr (P == 1) {
           n_occ = __popcll(ballot(CX_OCCUPIED(0) && (NOPAD || port[0] >= 0)) & smask);
@@ -1316,7 +1326,7 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
             f[5][j] = occ ? plast[j] * inv_pmax[j] : 0.0f;
           }
           const uint32_t Nb = 4u * (uint32_t)N;
-          if (P > 1 && adjacent) {
+          const auto put_at_once = [&] {
 #pragma unroll
             for (int i = 0; i < 6; ++i) put_lane((uint32_t)i * Nb, 4u * (uint32_t)port[0], f[i]);
             if constexpr (EXT) {
@@ -1327,6 +1337,11 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
                 put_lane(4u * (uint32_t)C.user_obs, 4u * (uint32_t)port[0], c);
               }
             }
+          };
+          if (P > 1 && adjacent) {
+            put_at_once();
+          } else if (SOME && whole) {
+            put_at_once();
           } else {
 #pragma unroll
             for (int j = 0; j < P; ++j) {
