@@ -819,15 +819,25 @@ __device__ __forceinline__ void run_group(Fill &&fill_tables, CX_KONST SegDev *s
     } else {
       // this step's bytes were asked for a step ago (the wait for them is then
       // no wait for the records of this step); the next step's are asked for now
+      // (SIMPLE classes: a lane's bytes at once, at any address)
+      typedef uint16_t __attribute__((aligned(1))) u16a1;
+      typedef uint32_t __attribute__((aligned(1))) u32a1;
 #define CX_ASK(row)                                                                                    \
   do {                                                                                                 \
-    _Pragma("unroll") for (int j = 0; j < P; ++j)                                                      \
-        k_in[j] = active && port[j] >= 0 ? (int)gl_at(row, act_bo + (uint32_t)port[j]) : 0;            \
+    if constexpr (NOPAD && P == 2) {                                                                   \
+      k_in[0] = active ? (int)gl_at((const u16a1 *)(row), act_bo + (uint32_t)port[0]) : 0;             \
+    } else if constexpr (NOPAD && P == 4) {                                                            \
+      k_in[0] = active ? (int)gl_at((const u32a1 *)(row), act_bo + (uint32_t)port[0]) : 0;             \
+    } else {                                                                                           \
+      _Pragma("unroll") for (int j = 0; j < P; ++j)                                                    \
+          k_in[j] = active && port[j] >= 0 ? (int)gl_at(row, act_bo + (uint32_t)port[j]) : 0;          \
+    }                                                                                                  \
     if constexpr (EXT) kb_in = batt && active ? (int)gl_at(row, act_bo + (uint32_t)N) : 0;             \
   } while (0)
       if (t == 0) CX_ASK(ai_t);
 #pragma unroll
-      for (int j = 0; j < P; ++j) k[j] = min(k_in[j], n_levels + n_neg);
+      for (int j = 0; j < P; ++j)
+        k[j] = min(NOPAD && P > 1 ? (int)__builtin_amdgcn_ubfe((uint32_t)k_in[0], 8 * j, 8) : k_in[j], n_levels + n_neg);
       if constexpr (EXT) kb = min(kb_in, 2 * n_levels);
       if (t + 1 < T) CX_ASK(ai_t + act_step);
 #undef CX_ASK
