@@ -180,6 +180,112 @@ __global__ __launch_bounds__(64 * kPolWaves) void k_policy(PolicyArgs a) {
   policy_sizes<kPolWaves, kPolNT>(a, xb, xb + 16 * kPolNT * kPolXbRow);
 }
 
+// Stations of up to 8 ports: one or two port groups leave most waves of such a
+// block idle at the draw, and its barriers are most of its time.  Here a wave takes
+// 16 NT observations through both products by itself: its lanes load them as the
+// first product reads them, and the hidden units it leaves in a lane are what the
+// second reads there.  The products are the block's, K-step by K-step in the same
+// order, with the policy's own number of hidden units.  Bound by the draw and, at 256
+// hidden units, the tanh; levels of 1,000,000 rows in blocks / here: 1 port, 32 hidden
+// units 180 / 33 us, 256 263 / 106; 8 ports 186 / 61 and 281 / 160.
+template <int NT, int K1, int HP>
+__global__ __launch_bounds__(64 * kPolWaves)
+__attribute__((amdgpu_waves_per_eu(HP == 8 ? 3 : HP == 4 ? 4 : 5))) void k_policy_few(PolicyArgs a) {
+  const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int col = lane & 15, lg = lane >> 4;
+  const int64_t e0 = ((int64_t)blockIdx.x * kPolWaves + wv) * (16 * NT);
+  if (e0 >= a.n) return;
+  const int n_e = (int)(a.n - e0 < 16 * NT ? a.n - e0 : 16 * NT);
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  const __amdgpu_buffer_rsrc_t w1 = frag_rsrc(a.w1f, 2 * kPolHP * kPolK1);
+  const __amdgpu_buffer_rsrc_t w2 = frag_rsrc(a.w2f, a.G * kPolR * kPolHP);
+  const float *obs = a.obs + e0 * a.in_dim;
+  u32x4 x[K1][NT];
+#pragma unroll
+  for (int s = 0; s < K1; ++s)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int e = 16 * n + col, f = 32 * s + 8 * lg;
+      const float *row = obs + (int64_t)e * a.in_dim + f;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (e < n_e) {
+        if (f + 8 <= a.in_dim) {
+          const f4u p = gld(reinterpret_cast<const f4u *>(row), 0), q = gld(reinterpret_cast<const f4u *>(row + 4), 0);
+          v = u32x4{pack2(p.x, p.y), pack2(p.z, p.w), pack2(q.x, q.y), pack2(q.z, q.w)};
+        } else if (f < a.in_dim) {
+          float r[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) r[j] = f + j < a.in_dim ? gld(row, j) : 0.f;
+          v = u32x4{pack2(r[0], r[1]), pack2(r[2], r[3]), pack2(r[4], r[5]), pack2(r[6], r[7])};
+        }
+      }
+      x[s][n] = v;
+    }
+  u32x4 h[HP][NT];
+#pragma unroll
+  for (int m = 0; m < HP; ++m) {
+    f32x4 c[2][NT], b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      b[i] = gld(reinterpret_cast<const f32x4 *>(a.b1 + 32 * m + 16 * i + 4 * lg), 0);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) c[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < K1; ++s) {
+        const u32x4 w = frag(w1, (2 * m + i) * kPolK1 + s);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) c[i][n] = mfma_bf16(w, x[s][n], c[i][n]);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) h[m][n] = hidden_frag(c[0][n], c[1][n], b[0], b[1]);
+  }
+  for (int grp = 0; grp < a.G; ++grp) {
+    const int port = 4 * grp + lg;
+    f32x4 c[kPolR][NT];
+#pragma unroll
+    for (int r = 0; r < kPolR; ++r) {
+      const f32x4 b = gld(reinterpret_cast<const f32x4 *>(a.b2f + (grp * kPolR + r) * 16 + 4 * lg), 0);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) c[r][n] = b;
+    }
+#pragma unroll
+    for (int s = 0; s < HP; ++s)
+#pragma unroll
+      for (int r = 0; r < kPolR; ++r) {
+        const u32x4 w = frag(w2, (grp * kPolR + r) * kPolHP + s);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) c[r][n] = mfma_bf16(w, h[s][n], c[r][n]);
+      }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int e = 16 * n + col;
+      if (port >= a.N || e >= n_e) continue;
+      if (a.logits) {
+        float *z = a.logits + ((e0 + e) * a.N + port) * (int64_t)a.L1;
+#pragma unroll
+        for (int l = 0; l < 4 * kPolR; ++l)
+          if (l < a.L1) gst(z, l, (float)c[l >> 2][n][l & 3]);
+      }
+      if (a.act) {
+        const U4 w = philox((uint32_t)(a.env0 + e0 + e), a.g, draw_index(port), kDomGum, (uint32_t)a.seed,
+                            (uint32_t)(a.seed >> 32));
+        const f32x4 cn[kPolR] = {c[0][n], c[1][n], c[2][n]};
+        gst(a.act, (e0 + e) * a.N + port, (uint8_t)sample_level(cn, a.L1, draw_uniform(draw_word(w, port))));
+      }
+    }
+  }
+}
+// Chosen by rows and ports: below about 16,384 rows its waves do not fill the chip and
+// their longer chain shows (4,000 rows of 4 ports, 256 hidden units: levels 7.8 us in
+// blocks, 9.6 here; 30,000 rows 14.2 and 9.7), and logits of more than one port group
+// leave in larger pieces from a block (200,000 rows of 4 ports, 32 hidden units 45 us
+// in blocks, 39 here, of 5 49 and 53, of 8 46 and 77).
+constexpr int kFewNT = 2;
+constexpr int64_t kFewRows = 16384;
+bool few_ports(const PolicyArgs &a) { return a.n >= kFewRows && a.N <= (a.logits ? 4 : 8); }
+static_assert((6 * 8 + 4 + 31) / 32 == 2, "k_policy_few is built for one and two K-steps of features");
+
 // Observation of the current state (the features the step kernel records).
 __global__ void k_observe(const ClassDev *cls, int64_t n_envs, const double *q, const float *u,
                           const float *p_last, const int16_t *dwell, const uint8_t *utype, const double *bsoc,
@@ -235,16 +341,24 @@ __global__ void k_observe(const ClassDev *cls, int64_t n_envs, const double *q, 
 
 hipError_t launch_policy(const PolicyArgs &a, hipStream_t st) {
   // a launch has fewer than 2^32 threads: 537 M rows each
-  constexpr int64_t kRows = 16 * kPolNT, kMaxRows = kMaxLaunchThreads / (64 * kPolWaves) * kRows;
-  for (int64_t r = 0; r < a.n; r += kMaxRows) {
+  const bool few = few_ports(a);
+  const int64_t rows = few ? 16 * kFewNT * kPolWaves : 16 * kPolNT;
+  const int64_t max_rows = kMaxLaunchThreads / (64 * kPolWaves) * rows;
+  for (int64_t r = 0; r < a.n; r += max_rows) {
     PolicyArgs b = a;
-    b.n = std::min(a.n - r, kMaxRows);
+    b.n = std::min(a.n - r, max_rows);
     b.obs += r * a.in_dim;
     if (b.act) b.act += r * a.N;
     if (b.logits) b.logits += r * a.N * a.L1;
     b.env0 += r;
-    hipLaunchKernelGGL(k_policy, dim3((unsigned)((b.n + kRows - 1) / kRows)), dim3(64 * kPolWaves), kPolLds, st, b);
-    const hipError_t e = hipGetLastError();
+    using Fn = void (*)(PolicyArgs);
+    static const Fn kFew[2][4] = {
+        {&k_policy_few<kFewNT, 1, 1>, &k_policy_few<kFewNT, 1, 2>, &k_policy_few<kFewNT, 1, 4>, &k_policy_few<kFewNT, 1, 8>},
+        {&k_policy_few<kFewNT, 2, 1>, &k_policy_few<kFewNT, 2, 2>, &k_policy_few<kFewNT, 2, 4>, &k_policy_few<kFewNT, 2, 8>}};
+    const Fn f = few ? kFew[a.K1 - 1][a.HP <= 1 ? 0 : a.HP <= 2 ? 1 : a.HP <= 4 ? 2 : 3] : &k_policy;
+    void *params[1] = {&b};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(f), dim3((unsigned)((b.n + rows - 1) / rows)),
+                                         dim3(64 * kPolWaves), params, few ? 0 : kPolLds, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

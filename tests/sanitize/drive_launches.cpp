@@ -291,6 +291,24 @@ void policy() {
   }
   // classes of other sizes take two kernels a step
   for (int ports : {3, 41}) policy_rollouts(Station(ports), 70, 128, "k_policy(");
+  // ... with a kernel of its own for 16,384 stations and more of up to 8 ports
+  policy_rollouts(Station(3), 16383, 32, "k_policy(");
+  for (int hidden : {32, 64, 96, 256}) policy_rollouts(Station(3), 16384, hidden, "k_policy_few<");
+  for (int ports : {1, 4, 5, 8, 9}) {
+    const Station st(ports);
+    Context x({&st}, {1});
+    const int in = 6 * ports + 4, out = ports * 11, hidden = 96;
+    const std::vector<uint16_t> w1((size_t)in * hidden), b1(hidden), w2((size_t)hidden * out), b2(out);
+    CK(cx_set_policy(x.c, hidden, w1.data(), b1.data(), w2.data(), b2.data()));
+    for (int64_t n : {16383, 16384, 16385, 40001}) {
+      const Dev obs((size_t)n * in * 4), act((size_t)n * ports), logits(4 * (size_t)n * out);
+      auto o = static_cast<const float *>(obs.p);
+      REQUIRE(x.count("k_policy_few<", [&] { return cx_policy_sample(x.c, o, n, 3, static_cast<uint8_t *>(act.p)); }) ==
+              (n >= 16384 && ports <= 8));
+      REQUIRE(x.count("k_policy_few<", [&] { return cx_policy_logits(x.c, o, n, static_cast<float *>(logits.p)); }) ==
+              (n >= 16384 && ports <= 4));
+    }
+  }
 }
 
 // A launch has fewer than 2^32 threads.
@@ -305,6 +323,18 @@ void grids() {
   const Dev obs((size_t)n * in * 4), act((size_t)n);
   CK(cx_policy_sample(x.c, static_cast<const float *>(obs.p), n, 3, static_cast<uint8_t *>(act.p)));
   CK(cx_synchronize(x.c));
+  // ... and for as many of nine ports, in blocks of 32 (125 GB, so only counted): two launches
+  {
+    const Station nine(9);
+    Context y({&nine}, {1});
+    const std::vector<uint16_t> v1((size_t)58 * hidden), v2((size_t)hidden * 99), c2(99);
+    CK(cx_set_policy(y.c, hidden, v1.data(), b1.data(), v2.data(), c2.data()));
+    fake_hip_only_count(true);
+    REQUIRE(y.count("k_policy(", [&] {
+      return cx_policy_sample(y.c, static_cast<const float *>(obs.p), n, 3, static_cast<uint8_t *>(act.p));
+    }) == 2);
+    fake_hip_only_count(false);
+  }
   // two packings of 40 M blocks of a wave each, which fit one by one
   const cx::SegDev segs[2] = {};
   cx::LaunchArgs a{};

@@ -545,6 +545,27 @@ void run_policy(const Launch &l) {
   if (32 * (size_t)a.N > xb) die("k_policy: %d ports", a.N);
 }
 
+// The policy kernel of few ports, <NT, K1, HP>: 4 waves a block, 16 NT observations a
+// wave, no LDS.
+void run_policy_few(const Launch &l, const std::string &w) {
+  const cx::PolicyArgs a = arg<cx::PolicyArgs>(l, 0);
+  int nt = 0, k1 = 0, hp = 0;
+  if (std::sscanf(w.c_str() + w.find('<'), "<%d, %d, %d>", &nt, &k1, &hp) != 3) die("cannot parse %s", w.c_str());
+  if (a.n <= 0) die("%s: n = %lld", w.c_str(), (long long)a.n);
+  if (l.block.x != 256 || l.lds != 0) die("%s: %u threads, %zu bytes of LDS", w.c_str(), l.block.x, l.lds);
+  if (a.HP < 1 || a.HP > hp || a.in_dim > 32 * k1 || a.L1 > 12 || 4 * a.G < a.N || a.G > 2)
+    die("%s: K1 %d HP %d G %d L1 %d in %d", w.c_str(), a.K1, a.HP, a.G, a.L1, a.in_dim);
+  need(a.obs, 4 * (size_t)(a.n * a.in_dim), "observations", w);
+  need(a.w1f, 1024 * (size_t)16 * 8, "W1 fragments", w);
+  need(a.b1, 4 * (size_t)256, "b1", w);
+  need(a.w2f, 1024 * (size_t)a.G * 3 * 8, "W2 fragments", w);
+  need(a.b2f, 4 * 16 * (size_t)a.G * 3, "b2", w);
+  if (a.act) need(a.act, (size_t)(a.n * a.N), "levels", w);
+  if (a.logits) need(a.logits, 4 * (size_t)(a.n * a.N * a.L1), "logits", w);
+  const int64_t rows = 4 * 16 * nt;
+  if ((int64_t)l.grid.x != (a.n + rows - 1) / rows) die("%s: %u blocks for %lld rows", w.c_str(), l.grid.x, (long long)a.n);
+}
+
 std::mutex lmu;                       // guards launches
 std::map<std::string, long> launches; // kernels run so far, by name
 bool only_count = false;              // launches are counted, not checked
@@ -564,6 +585,8 @@ void run_kernel(const Launch &l) {
     run_parts(l, k);
   } else if (k.name.find("k_policy(") != std::string::npos) {
     run_policy(l);
+  } else if (k.name.find("k_policy_few<") != std::string::npos) {
+    run_policy_few(l, k.name);
   } else if (k.name.find("k_reset_obs(") != std::string::npos) {
     const auto *cls = arg<const cx::ClassDev *>(l, 0);
     check_class(cls, k.name);
