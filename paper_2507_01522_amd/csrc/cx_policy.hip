@@ -1,7 +1,8 @@
 // cx_policy.hip -- policy-in-the-loop rollouts.
 //   k_policy  obs -> BF16 -> W1 (tanh) -> W2 -> logits on the matrix cores
 //             (v_mfma_f32_16x16x32_bf16, FP32 accumulation), then per port a
-//             level drawn from softmax of its logits with one Philox uniform.
+//             level drawn from softmax of its logits with one Philox uniform
+//             (k_policy_few: the same for many rows of few ports).
 // A rollout of a class of 8, 16 or 32 slots is one launch of the fused
 // persistent kernel (the rollout kernel with this MLP between its steps,
 // cx_kernels.hip): state in registers, observations only in LDS.  Other
