@@ -188,7 +188,9 @@ __global__ __launch_bounds__(64 * kPolWaves) void k_policy(PolicyArgs a) {
 // second reads there.  The products are the block's, K-step by K-step in the same
 // order, with the policy's own number of hidden units.  Bound by the draw and, at 256
 // hidden units, the tanh; levels of 1,000,000 rows in blocks / here: 1 port, 32 hidden
-// units 180 / 33 us, 256 263 / 106; 8 ports 186 / 61 and 281 / 160.
+// units 180 / 33 us, 256 263 / 106; 8 ports 186 / 61 and 281 / 160.  The bounds on
+// waves keep the compiler from loading every fragment ahead: 74, 92 and 150 registers at
+// 64, 128 and 256 hidden units, 96, 152 and 280 (one wave per SIMD) without them.
 template <int NT, int K1, int HP>
 __global__ __launch_bounds__(64 * kPolWaves)
 __attribute__((amdgpu_waves_per_eu(HP == 8 ? 3 : HP == 4 ? 4 : 5))) void k_policy_few(PolicyArgs a) {
